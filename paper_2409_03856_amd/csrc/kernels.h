@@ -215,18 +215,22 @@ hipError_t launch_kv_rollback(int32_t* cache_pos, const int32_t* accept_len, int
 // h[i] = E[tokens[i]] widened to fp32 (0 for an id outside [0, V)); d % 8 == 0.
 hipError_t launch_embed(const int32_t* tokens, int n, const uint16_t* E, int d, int V, float* out,
                         hipStream_t s);
-// y[i][j] = x[i] . W[j] (+ resid[i][j]) for i < n, j < N; W [N][K] bf16; K % 8 == 0 and
-// K <= 16384. With y_bf16 the rows are written as bf16 instead (resid and y unused).
-// RMSNorm (unit weight, bit for bit rmsnorm_vec_kernel's result) of n rows of x [n][K] as they
-// are staged, then q = xn Wq^T [n][Nq] fp32 and, for Nkv > 0, k = xn Wk^T, v = xn Wv^T [n][Nkv]
-// bf16 in one launch per 16 rows. K % 8 == 0, K <= 8192, 16-byte aligned rows.
-hipError_t launch_norm_qkv(const float* x, int n, int K, float eps, const uint16_t* Wq, int Nq,
+// One token's products: RMSNorm (unit weight, bit for bit rmsnorm_vec_kernel's result) of x [K] as
+// it is staged, then q = xn Wq^T [Nq] fp32 and, for Nkv > 0, k = xn Wk^T, v = xn Wv^T [Nkv] bf16 in
+// one launch. K % 8 == 0, K <= 8192, 16-byte aligned rows.
+hipError_t launch_norm_qkv(const float* x, int K, float eps, const uint16_t* Wq, int Nq,
                            const uint16_t* Wk, const uint16_t* Wv, int Nkv, float* yq,
                            uint16_t* yk, uint16_t* yv, hipStream_t s);
-hipError_t launch_linear(const float* x, int n, const uint16_t* W, int K, int N,
-                         const float* resid, float* y, uint16_t* y_bf16, hipStream_t s);
-// seq[slot] = argmax of the V logits (lowest index on ties); cache_pos[0] += pos_delta;
-// trace_drafted[slot - 1] = the token when given.
+// y[j] = x . W[j] (+ resid[j]) for j < N; W [N][K] bf16; K % 8 == 0, K <= 8192.
+hipError_t launch_linear(const float* x, const uint16_t* W, int K, int N, const float* resid, float* y,
+                         hipStream_t s);
+// The same products (norm_eps >= 0: of the normalised rows) for a chunk of 2..64 tokens on MFMA,
+// every weight read once per call; linear_mfma_ws(n, K) bytes of workspace, K % 8 == 0, K <= 8192.
+size_t linear_mfma_ws(int n, int K);
+hipError_t launch_linear_mfma(const float* x, int n, int K, float norm_eps, const uint16_t* Wq,
+                              int Nq, const uint16_t* Wk, const uint16_t* Wv, int Nkv,
+                              const float* resid, float* yq, uint16_t* yk, uint16_t* yv, char* ws,
+                              hipStream_t s);
 hipError_t launch_draft_tail(const float* logits, int V, int32_t* seq, int slot,
                              int32_t* cache_pos, int pos_delta, int32_t* trace_drafted,
                              hipStream_t s);

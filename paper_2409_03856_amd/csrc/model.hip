@@ -2,14 +2,14 @@
 // loop (Algorithm 1) over it with every decision kept on the device.
 //
 //  embed_kernel        h[i] = E[token_i] (bf16 rows widened; an id outside [0, V) gives 0)
-//  linear_kernel<NB>   y[i][j] = x[i] . W[j] (+ resid[i][j]) for up to NB rows of x staged in
-//                      LDS; one wave per output row (W row-major [N][K] bf16), fp32 or bf16
-//                      output (round to nearest even)
-//  norm_qkv_kernel<NB> RMSNorm of the rows as they are staged (the same sums, in the same order,
-//                      as rmsnorm_vec_kernel, so bit for bit its result), then the products of
-//                      up to three matrices in one launch: q = xn Wq^T (fp32), k = xn Wk^T and
-//                      v = xn Wv^T (bf16) -- a layer's attention inputs, or the final norm and
-//                      the LM head (q only)
+//  linear_kernel       one token: y[j] = x . W[j] (+ resid[j]), x staged in LDS, one wave per
+//                      output row (W row-major [N][K] bf16)
+//  norm_qkv_kernel     one token: RMSNorm of the row as it is staged (the same sums, in the same
+//                      order, as rmsnorm_vec_kernel, so bit for bit its result), then the
+//                      products of up to three matrices in one launch: q = xn Wq^T (fp32),
+//                      k = xn Wk^T and v = xn Wv^T (bf16) -- a layer's attention inputs, or the
+//                      final norm and the LM head (q only). Chunks of more tokens run in
+//                      linear.hip
 //  draft_tail_kernel   the sparse model's greedy draft: argmax of one logit row (lowest index
 //                      on ties) into the chunk buffer, and the cache position advanced by one
 //                      (wound back by n - 1 after the last draft, so the full model's pass
@@ -31,7 +31,7 @@ namespace {
 
 constexpr int kLinThreads = 256;
 constexpr int kLinWaves = kLinThreads / kWave;
-constexpr int kLinLds = 16384;  // floats of x staged per launch (64 KiB)
+constexpr int kLinMaxK = 8192;  // floats of x staged per launch
 constexpr int kTailThreads = 1024;
 
 __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ tokens, int n,
@@ -49,93 +49,66 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
   }
 }
 
-// Rows j = blockIdx.x * 4 + wave, + gridDim.x * 4, ...; x rows 0 .. n - 1 (n <= NB) in LDS.
-template <int NB, bool OUT_BF16>
-__global__ __launch_bounds__(kLinThreads) void linear_kernel(const float* __restrict__ x, int n,
+// Rows j = blockIdx.x * 4 + wave, + gridDim.x * 4, ...; x in LDS.
+__global__ __launch_bounds__(kLinThreads) void linear_kernel(const float* __restrict__ x,
                                                              const uint4* __restrict__ W, int K,
-                                                             int N, const float* resid, float* y,
-                                                             uint16_t* __restrict__ yb) {
-  __shared__ float4 s_x4[kLinLds / 4];
+                                                             int N, const float* resid, float* y) {
+  __shared__ float4 s_x4[kLinMaxK / 4];
   const float* xs = reinterpret_cast<const float*>(s_x4);
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int k4 = K >> 2, k8 = K >> 3;
   const float4* x4 = reinterpret_cast<const float4*>(x);
-  for (int e = tid; e < n * k4; e += kLinThreads) s_x4[e] = x4[e];
+  for (int e = tid; e < k4; e += kLinThreads) s_x4[e] = x4[e];
   __syncthreads();
   for (int j = blockIdx.x * kLinWaves + wave; j < N; j += gridDim.x * kLinWaves) {
-    float acc[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) acc[i] = 0.f;
     const uint4* wr = W + (size_t)j * k8;
-    for (int c = lane; c < k8; c += kWave) {
-      const uint4 w = wr[c];
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-        if (i < n) acc[i] = dot8(w, xs + (size_t)i * K + 8 * c, acc[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      if (i < n) {  // n is uniform over the wave
-        const float s = wave_sum(acc[i]);
-        if (lane == i) {
-          const size_t o = (size_t)i * N + j;
-          if (OUT_BF16) {
-            yb[o] = (uint16_t)f32_to_bf16(s);
-          } else {
-            y[o] = (resid != nullptr) ? resid[o] + s : s;
-          }
-        }
-      }
-    }
+    float acc = 0.f;
+    for (int c = lane; c < k8; c += kWave) acc = dot8(wr[c], xs + 8 * c, acc);
+    const float s = wave_sum(acc);
+    if (lane == 0) y[j] = (resid != nullptr) ? resid[j] + s : s;
   }
 }
 
 // Output rows j of the three products in one range: [0, Nq) of Wq into yq (fp32), then
-// [Nq, Nq + Nkv) of Wk and [Nq + Nkv, Nq + 2 Nkv) of Wv into yk, yv (bf16). The rows of x are
-// staged in LDS (every load in flight at once), then normalised there: each thread sums the
-// squares of its float4s tid + 256 u of a row as rmsnorm_vec_kernel does, the wave sums go through
-// LDS, and after one barrier each thread scales its float4s.
-template <int NB>
+// [Nq, Nq + Nkv) of Wk and [Nq + Nkv, Nq + 2 Nkv) of Wv into yk, yv (bf16). The row x is staged
+// in LDS (every load in flight at once), then normalised there: each thread sums the squares of
+// its float4s tid + 256 u as rmsnorm_vec_kernel does, the wave sums go through LDS, and after one
+// barrier each thread scales its float4s.
 __global__ __launch_bounds__(kLinThreads) void norm_qkv_kernel(
-    const float* __restrict__ x, int n, int K, float eps, const uint4* __restrict__ Wq, int Nq,
+    const float* __restrict__ x, int K, float eps, const uint4* __restrict__ Wq, int Nq,
     const uint4* __restrict__ Wk, const uint4* __restrict__ Wv, int Nkv, float* __restrict__ yq,
     uint16_t* __restrict__ yk, uint16_t* __restrict__ yv) {
   static_assert(kLinThreads == 256, "the norm's sums follow rmsnorm_vec_kernel's 256-thread layout");
-  constexpr int kPer = 8;  // K <= 8192
-  __shared__ float4 s_x4[kLinLds / 4];
-  __shared__ float s_w[NB][kLinWaves];
+  constexpr int kPer = kLinMaxK / 4 / kLinThreads;
+  __shared__ float4 s_x4[kLinMaxK / 4];
+  __shared__ float s_w[kLinWaves];
   const float* xs = reinterpret_cast<const float*>(s_x4);
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int k4 = K >> 2, k8 = K >> 3;
   const float4* x4 = reinterpret_cast<const float4*>(x);
-  for (int e = tid; e < n * k4; e += kLinThreads) s_x4[e] = x4[e];  // every row's loads in flight
-  __syncthreads();
-  for (int i = 0; i < n; ++i) {
-    float ss = 0.f;
+  float4 v[kPer];
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int e = tid + kLinThreads * u;
-      const float4 v = (e < k4) ? s_x4[i * k4 + e] : make_float4(0.f, 0.f, 0.f, 0.f);
-      ss = fmaf(v.x, v.x, ss);
-      ss = fmaf(v.y, v.y, ss);
-      ss = fmaf(v.z, v.z, ss);
-      ss = fmaf(v.w, v.w, ss);
-    }
-    ss = wave_sum(ss);
-    if (lane == 0) s_w[i][wave] = ss;
+  for (int u = 0; u < kPer; ++u) {
+    const int e = tid + kLinThreads * u;
+    v[u] = (e < k4) ? x4[e] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  __syncthreads();
-  for (int i = 0; i < n; ++i) {
-    const float tot = ((s_w[i][0] + s_w[i][1]) + s_w[i][2]) + s_w[i][3];
-    const float inv = 1.0f / sqrtf(tot / (float)K + eps);
+  float ss = 0.f;
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int e = tid + kLinThreads * u;
-      if (e < k4) {
-        const float4 t = s_x4[i * k4 + e];
-        s_x4[i * k4 + e] = make_float4(t.x * inv, t.y * inv, t.z * inv, t.w * inv);
-      }
-    }
+  for (int u = 0; u < kPer; ++u) {
+    ss = fmaf(v[u].x, v[u].x, ss);
+    ss = fmaf(v[u].y, v[u].y, ss);
+    ss = fmaf(v[u].z, v[u].z, ss);
+    ss = fmaf(v[u].w, v[u].w, ss);
+  }
+  ss = wave_sum(ss);
+  if (lane == 0) s_w[wave] = ss;
+  __syncthreads();
+  const float tot = ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
+  const float inv = 1.0f / sqrtf(tot / (float)K + eps);
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int e = tid + kLinThreads * u;
+    if (e < k4) s_x4[e] = make_float4(v[u].x * inv, v[u].y * inv, v[u].z * inv, v[u].w * inv);
   }
   __syncthreads();
   const int N = Nq + 2 * Nkv;
@@ -143,24 +116,12 @@ __global__ __launch_bounds__(kLinThreads) void norm_qkv_kernel(
     const int part = j < Nq ? 0 : (j < Nq + Nkv ? 1 : 2);  // uniform over the wave
     const int jr = part == 0 ? j : (part == 1 ? j - Nq : j - Nq - Nkv);
     const uint4* wr = (part == 0 ? Wq : (part == 1 ? Wk : Wv)) + (size_t)jr * k8;
-    float acc[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) acc[i] = 0.f;
-    for (int c = lane; c < k8; c += kWave) {
-      const uint4 w = wr[c];
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-        if (i < n) acc[i] = dot8(w, xs + (size_t)i * K + 8 * c, acc[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      if (i < n) {  // n is uniform over the wave
-        const float s = wave_sum(acc[i]);
-        if (lane == i) {
-          if (part == 0) yq[(size_t)i * Nq + jr] = s;
-          else (part == 1 ? yk : yv)[(size_t)i * Nkv + jr] = (uint16_t)f32_to_bf16(s);
-        }
-      }
+    float acc = 0.f;
+    for (int c = lane; c < k8; c += kWave) acc = dot8(wr[c], xs + 8 * c, acc);
+    const float s = wave_sum(acc);
+    if (lane == 0) {
+      if (part == 0) yq[jr] = s;
+      else (part == 1 ? yk : yv)[jr] = (uint16_t)f32_to_bf16(s);
     }
   }
 }
@@ -234,33 +195,6 @@ __global__ void period_tail_kernel(int32_t* __restrict__ seq, int n,
   if (tr_next != nullptr) tr_next[0] = (j < n) ? nxt : -1;
 }
 
-template <bool OUT_BF16>
-hipError_t launch_linear_t(const float* x, int n, const uint16_t* W, int K, int N,
-                           const float* resid, float* y, uint16_t* yb, hipStream_t s) {
-  const int nb = std::min(16, kLinLds / K);
-  for (int i0 = 0; i0 < n; i0 += nb) {
-    const int m = std::min(nb, n - i0);
-    const int grid = std::min(ceil_div(N, kLinWaves), 2048);
-    const float* xi = x + (size_t)i0 * K;
-    const float* ri = resid ? resid + (size_t)i0 * N : nullptr;
-    float* yi = y ? y + (size_t)i0 * N : nullptr;
-    uint16_t* ybi = yb ? yb + (size_t)i0 * N : nullptr;
-    const uint4* w4 = reinterpret_cast<const uint4*>(W);
-#define SIRIUS_LIN(NBV)                                                                       \
-  if (m <= NBV) {                                                                             \
-    klaunch(linear_kernel<NBV, OUT_BF16>, grid, kLinThreads, 0, s, xi, m, w4, K, N, ri, yi, ybi); \
-    hipError_t e = hipGetLastError();                                                         \
-    if (e != hipSuccess) return e;                                                            \
-    continue;                                                                                 \
-  }
-    SIRIUS_LIN(1)
-    SIRIUS_LIN(4)
-    SIRIUS_LIN(16)
-#undef SIRIUS_LIN
-  }
-  return hipSuccess;
-}
-
 }  // namespace
 
 hipError_t launch_embed(const int32_t* tokens, int n, const uint16_t* E, int d, int V, float* out,
@@ -270,45 +204,26 @@ hipError_t launch_embed(const int32_t* tokens, int n, const uint16_t* E, int d, 
   return hipGetLastError();
 }
 
-hipError_t launch_norm_qkv(const float* x, int n, int K, float eps, const uint16_t* Wq, int Nq,
-                           const uint16_t* Wk, const uint16_t* Wv, int Nkv, float* yq,
-                           uint16_t* yk, uint16_t* yv, hipStream_t s) {
-  if ((K & 7) != 0 || K > 8192 || n < 1 || Nq < 1 || Nkv < 0 ||
+hipError_t launch_norm_qkv(const float* x, int K, float eps, const uint16_t* Wq, int Nq,
+                           const uint16_t* Wk, const uint16_t* Wv, int Nkv, float* yq, uint16_t* yk,
+                           uint16_t* yv, hipStream_t s) {
+  if ((K & 7) != 0 || K > kLinMaxK || Nq < 1 || Nkv < 0 ||
       (Nkv > 0 && (Wk == nullptr || Wv == nullptr || yk == nullptr || yv == nullptr)))
     return hipErrorInvalidValue;
   ProfScope prof("norm_qkv", s);
-  const int nb = std::min(16, kLinLds / K);
-  for (int i0 = 0; i0 < n; i0 += nb) {
-    const int m = std::min(nb, n - i0);
-    const int grid = std::min(ceil_div(Nq + 2 * Nkv, kLinWaves), 2048);
-    const float* xi = x + (size_t)i0 * K;
-    float* qi = yq + (size_t)i0 * Nq;
-    uint16_t* ki = Nkv > 0 ? yk + (size_t)i0 * Nkv : nullptr;
-    uint16_t* vi = Nkv > 0 ? yv + (size_t)i0 * Nkv : nullptr;
-    const uint4* q4 = reinterpret_cast<const uint4*>(Wq);
-    const uint4* k4 = reinterpret_cast<const uint4*>(Wk);
-    const uint4* v4 = reinterpret_cast<const uint4*>(Wv);
-#define SIRIUS_NQKV(NBV)                                                                          \
-  if (m <= NBV) {                                                                                 \
-    klaunch(norm_qkv_kernel<NBV>, grid, kLinThreads, 0, s, xi, m, K, eps, q4, Nq, k4, v4, Nkv, qi, ki, vi); \
-    hipError_t e = hipGetLastError();                                                             \
-    if (e != hipSuccess) return e;                                                                \
-    continue;                                                                                     \
-  }
-    SIRIUS_NQKV(1)
-    SIRIUS_NQKV(4)
-    SIRIUS_NQKV(16)
-#undef SIRIUS_NQKV
-  }
-  return hipSuccess;
+  klaunch(norm_qkv_kernel, std::min(ceil_div(Nq + 2 * Nkv, kLinWaves), 2048), kLinThreads, 0, s, x, K,
+          eps, reinterpret_cast<const uint4*>(Wq), Nq, reinterpret_cast<const uint4*>(Wk),
+          reinterpret_cast<const uint4*>(Wv), Nkv, yq, yk, yv);
+  return hipGetLastError();
 }
 
-hipError_t launch_linear(const float* x, int n, const uint16_t* W, int K, int N,
-                         const float* resid, float* y, uint16_t* y_bf16, hipStream_t s) {
-  if ((K & 7) != 0 || K > kLinLds || n < 1) return hipErrorInvalidValue;
+hipError_t launch_linear(const float* x, const uint16_t* W, int K, int N, const float* resid, float* y,
+                         hipStream_t s) {
+  if ((K & 7) != 0 || K > kLinMaxK) return hipErrorInvalidValue;
   ProfScope prof("linear", s);
-  if (y_bf16 != nullptr) return launch_linear_t<true>(x, n, W, K, N, nullptr, nullptr, y_bf16, s);
-  return launch_linear_t<false>(x, n, W, K, N, resid, y, nullptr, s);
+  klaunch(linear_kernel, std::min(ceil_div(N, kLinWaves), 2048), kLinThreads, 0, s, x,
+          reinterpret_cast<const uint4*>(W), K, N, resid, y);
+  return hipGetLastError();
 }
 
 hipError_t launch_draft_tail(const float* logits, int V, int32_t* seq, int slot,

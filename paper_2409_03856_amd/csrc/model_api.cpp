@@ -36,7 +36,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 // Workspace of a forward pass of up to nmax tokens (and of a period with n = nmax).
 struct ModelLayout {
-  size_t h, xn, q, kb, vb, att, logits, ints, sub, total;
+  size_t h, xf, q, kb, vb, att, logits, ints, sub, total;
 };
 
 size_t ffn_ws_any(int B, int d, int F, bool sparse) {
@@ -48,7 +48,7 @@ ModelLayout model_layout(const sirius_model* m, int nmax) {
   ModelLayout L{};
   sirius::Carve c;
   L.h = c.take((size_t)nmax * d * 4);
-  L.xn = c.take((size_t)nmax * d * 4);
+  L.xf = c.take(nmax > 1 ? sirius::linear_mfma_ws(nmax, std::max(d, hq)) : 0);  // projection inputs of a chunk
   L.q = c.take((size_t)nmax * hq * 4);
   L.kb = c.take((size_t)nmax * hkv * 2);
   L.vb = c.take((size_t)nmax * hkv * 2);
@@ -130,44 +130,42 @@ hipError_t forward(const sirius_model* m, const int32_t* tokens, int n, const in
   const int hq = H * hd, hkv = Hkv * hd;
   const Strides st = strides(m);
   float* h = reinterpret_cast<float*>(ws + L.h);
-  float* xn = reinterpret_cast<float*>(ws + L.xn);
   float* q = reinterpret_cast<float*>(ws + L.q);
   uint16_t* kb = reinterpret_cast<uint16_t*>(ws + L.kb);
   uint16_t* vb = reinterpret_cast<uint16_t*>(ws + L.vb);
   float* att = reinterpret_cast<float*>(ws + L.att);
   char* sub = ws + L.sub;
   hipError_t e;
-  // the norm folds into the projections' launch when the rows take the vectorised norm (the
-  // same sums, so the same bits); otherwise the separate norm and one launch per product
-  const bool fused = (d & 3) == 0 && d <= 8192 && (reinterpret_cast<uintptr_t>(h) & 15) == 0;
+  // one token: the GEMV kernels (the norm folded in); a chunk: the MFMA projections, which read
+  // every weight once for all of its tokens
+  auto project = [&](const float* x, int K, float eps, const uint16_t* wq, int nq, const uint16_t* wk,
+                     const uint16_t* wv, int nkv, const float* resid, float* yq, uint16_t* yk,
+                     uint16_t* yv) {
+    if (n > 1)
+      return sirius::launch_linear_mfma(x, n, K, eps, wq, nq, wk, wv, nkv, resid, yq, yk, yv, ws + L.xf, s);
+    return eps < 0.f ? sirius::launch_linear(x, wq, K, nq, resid, yq, s)
+                     : sirius::launch_norm_qkv(x, K, eps, wq, nq, wk, wv, nkv, yq, yk, yv, s);
+  };
   if ((e = sirius::launch_embed(tokens, n, m->embed, d, m->vocab, h, s)) != hipSuccess) return e;
   for (int l = 0; l < m->n_layers; ++l) {
-    if (fused) {
-      if ((e = sirius::launch_norm_qkv(h, n, d, m->norm_eps, m->wq + l * st.q, hq, m->wk + l * st.kv,
-                                       m->wv + l * st.kv, hkv, q, kb, vb, s)) != hipSuccess)
-        return e;
-    } else {
-      if ((e = sirius::launch_rmsnorm(h, n, d, m->norm_eps, xn, s)) != hipSuccess) return e;
-      if ((e = sirius::launch_linear(xn, n, m->wq + l * st.q, d, hq, nullptr, q, nullptr, s)) != hipSuccess) return e;
-      if ((e = sirius::launch_linear(xn, n, m->wk + l * st.kv, d, hkv, nullptr, nullptr, kb, s)) != hipSuccess) return e;
-      if ((e = sirius::launch_linear(xn, n, m->wv + l * st.kv, d, hkv, nullptr, nullptr, vb, s)) != hipSuccess) return e;
-    }
+    if ((e = project(h, d, m->norm_eps, m->wq + l * st.q, hq, m->wk + l * st.kv, m->wv + l * st.kv, hkv,
+                     nullptr, q, kb, vb)) != hipSuccess)
+      return e;
     const sirius::AttnLayout AL = sirius::attn_layout(1, n, H, Hkv, hd, m->max_len);
     if ((e = sirius::launch_attn_kv(q, kb, vb, m->k_cache + l * st.cache, m->v_cache + l * st.cache,
                                     cache_pos, 1, n, H, Hkv, hd, m->max_len, att, sub, AL, s)) != hipSuccess)
       return e;
-    if ((e = sirius::launch_linear(att, n, m->wo + l * st.o, hq, d, h, h, nullptr, s)) != hipSuccess) return e;
+    if ((e = project(att, hq, -1.f, m->wo + l * st.o, d, nullptr, nullptr, 0, h, h, nullptr, nullptr)) !=
+        hipSuccess)
+      return e;
     const float t = sparse ? m->thresholds[l] : 0.f;
     if ((e = ffn_any(h, n, m->w_gate + l * st.ffn, m->w_up + l * st.ffn, m->w_down + l * st.ffn, d,
                      m->d_ff, sparse, t, m->norm_eps, h, h, aidx ? aidx + l * a_lstride : nullptr,
                      acnt ? acnt + l * c_lstride : nullptr, sub, s)) != hipSuccess)
       return e;
   }
-  if (fused)
-    return sirius::launch_norm_qkv(h, n, d, m->norm_eps, m->lm_head, m->vocab, nullptr, nullptr, 0,
-                                   logits, nullptr, nullptr, s);
-  if ((e = sirius::launch_rmsnorm(h, n, d, m->norm_eps, xn, s)) != hipSuccess) return e;
-  return sirius::launch_linear(xn, n, m->lm_head, d, m->vocab, nullptr, logits, nullptr, s);
+  return project(h, d, m->norm_eps, m->lm_head, m->vocab, nullptr, nullptr, 0, nullptr, logits, nullptr,
+                 nullptr);
 }
 
 }  // namespace
