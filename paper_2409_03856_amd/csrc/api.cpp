@@ -8,6 +8,7 @@
 #include <string>
 
 #include "sirius.h"
+#include "common.h"
 #include "kernels.h"
 
 namespace {
@@ -56,6 +57,19 @@ int check_ptrs(const char* fn, std::initializer_list<std::pair<const void*, cons
     if (!aligned16(p.first)) return fail(SIRIUS_EINVAL, "%s: %s is not 16-byte aligned", fn, p.second);
   }
   return SIRIUS_OK;
+}
+
+struct CalibLayout {
+  size_t act, sel, xp, total;
+};
+CalibLayout calib_layout(int N, int d, int F) {
+  sirius::Carve c;
+  CalibLayout L;
+  L.act = c.take((size_t)N * F * sizeof(float));
+  L.sel = c.take(sirius::select_ws_bytes());
+  L.xp = c.take(sirius::gate_absact_ws(N, d));
+  L.total = c.off;
+  return L;
 }
 
 bool dims_ok(int d_model, int d_ff) {
@@ -188,7 +202,7 @@ size_t sirius_workspace_size(int op, int B, int d_model, int d_ff, int T_or_V, i
       return gemv_ws(B, d_model, d_ff);
     case SIRIUS_OP_CATS_CALIBRATE:
       if (B < 1 || !dims_ok(d_model, d_ff)) return 0;
-      return (((size_t)B * d_ff * sizeof(float) + 255) & ~size_t(255)) + sirius::select_ws_bytes();
+      return calib_layout(B, d_model, d_ff).total;
     case SIRIUS_OP_GRIFFIN_SELECT:
       if (T_or_V < 1 || !dims_ok(d_model, d_ff)) return 0;
       return sirius::griffin_layout(T_or_V, d_model, d_ff).total;
@@ -299,11 +313,14 @@ int sirius_cats_calibrate(const float* x_cal, int N, const uint16_t* w_gate, int
   r = std::min<long long>(std::max<long long>(r, 1), (long long)M);
   const int k = (int)((long long)M - r + 1);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  float* absact = static_cast<float*>(ws);
-  char* sel_ws = static_cast<char*>(ws) + ((M * sizeof(float) + 255) & ~size_t(255));
-  hipError_t e = sirius::launch_gate_absact(x_cal, N, w_gate, d_model, d_ff, absact, s);
+  const CalibLayout L = calib_layout(N, d_model, d_ff);
+  char* base = static_cast<char*>(ws);
+  float* absact = reinterpret_cast<float*>(base + L.act);
+  int nzero = 0;
+  int* zero = sirius::select_zero_ints(base + L.sel, &nzero);
+  hipError_t e = sirius::launch_gate_absact(x_cal, N, w_gate, d_model, d_ff, absact, base + L.xp, zero, nzero, s);
   if (e != hipSuccess) return hip_status(e, fn);
-  return hip_status(sirius::launch_select_kth_largest(absact, (int)M, k, t_out, sel_ws, s), fn);
+  return hip_status(sirius::launch_select_kth_largest(absact, (int)M, k, t_out, base + L.sel, s), fn);
 }
 
 int sirius_griffin_select(const uint16_t* x_prompt, int T, const uint16_t* w_gate,

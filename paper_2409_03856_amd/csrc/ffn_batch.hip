@@ -185,7 +185,7 @@ __device__ __forceinline__ void run_ring(unsigned char* ring, R& rg, int nblk, i
 }
 
 // ---- x -> optional RMSNorm -> PX bf16 pieces [PX][Mpad][d]; one workgroup per padded row.
-template <int PX>
+template <int PX, bool ANY = false>
 __global__ __launch_bounds__(256) void prep_pieces_kernel(const float* __restrict__ x, int B, int d,
                                                           int mpad, float norm_eps,
                                                           uint16_t* __restrict__ xp) {
@@ -241,8 +241,12 @@ __global__ __launch_bounds__(256) void prep_pieces_kernel(const float* __restric
       uint32_t b[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        b[e] = f32_to_bf16(r[e]);
-        r[e] -= __uint_as_float(b[e] << 16);  // exact: the remainder of a bf16 rounding
+        if (ANY) {  // infinities too (calibration inputs)
+          b[e] = take_piece(r[e]);
+        } else {
+          b[e] = f32_to_bf16(r[e]);
+          r[e] -= __uint_as_float(b[e] << 16);  // exact: the remainder of a bf16 rounding
+        }
       }
       reinterpret_cast<uint2*>(xp + ((size_t)p * mpad + m) * d)[i] =
           make_uint2(b[0] | (b[1] << 16), b[2] | (b[3] << 16));
@@ -1144,6 +1148,11 @@ __global__ __launch_bounds__(kBT) void down_ring_kernel(
 int batch_mt(int B) { return (B + 15) / 16; }
 
 }  // namespace
+
+hipError_t launch_prep_pieces3(const float* x, int B, int d, int mpad, uint16_t* xp, hipStream_t stream) {
+  klaunch((prep_pieces_kernel<3, true>), mpad, 256, 0, stream, x, B, d, mpad, -1.f, xp);
+  return hipGetLastError();
+}
 
 bool batch_path_ok(int B, int d, int F) {
   return B >= 2 && B <= 64 && d % kDnCols == 0 && d <= 8192 && F >= 1 && F <= 65536;

@@ -61,8 +61,7 @@ constexpr int kXLdsFloats = 32768;          // fp32 x staged in LDS: 128 KiB (LD
 
 // kModeAct writes the signed gate activations and stops; kModeKeyed takes them (and a per-token
 // top-k key cut) from that pass instead of reading W_gate again.
-constexpr int kModeDense = 0, kModeSparse = 1, kModeAbsAct = 2, kModeAct = 3, kModeKeyed = 4;
-constexpr bool writes_act(int mode) { return mode == kModeAbsAct || mode == kModeAct; }
+constexpr int kModeDense = 0, kModeSparse = 1, kModeAct = 3, kModeKeyed = 4;
 
 template <int BM, int CPL, int MODE>
 __global__ __launch_bounds__(256) void gate_kernel(
@@ -178,10 +177,10 @@ __global__ __launch_bounds__(256) void gate_kernel(
         if (b < B && (MODE == kModeDense || fabsf(a[b]) > t)) fl |= 1u << b;
       }
       if (lane == 0 && j < nr) {
-        if (writes_act(MODE)) {
+        if (MODE == kModeAct) {
 #pragma unroll
           for (int b = 0; b < BM; ++b)
-            if (b < B) absact[(size_t)b * F + r0 + j] = (MODE == kModeAbsAct) ? fabsf(a[b]) : a[b];
+            if (b < B) absact[(size_t)b * F + r0 + j] = a[b];
         } else {
           s_flag[j] = fl;
 #pragma unroll
@@ -190,7 +189,7 @@ __global__ __launch_bounds__(256) void gate_kernel(
       }
     }
   }
-  if (writes_act(MODE)) return;  // uniform over the block
+  if (MODE == kModeAct) return;  // uniform over the block
   __syncthreads();
 
   // ---- compact the segment's kept rows (some token keeps them), ascending
@@ -705,26 +704,6 @@ hipError_t launch_gate_act(const float* x, int N, const uint16_t* wg, int d, int
         bm, cpl, dim3(nseg), (size_t)nb * d * sizeof(float), stream, x + (size_t)b0 * d, nb,
         reinterpret_cast<const uint4*>(wg), nullptr, d, F, 0.f, norm_eps, rmax, nullptr, nullptr,
         nullptr, nullptr, nullptr, act + (size_t)b0 * F);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
-hipError_t launch_gate_absact(const float* x, int N, const uint16_t* wg, int d, int F,
-                              float* absact, hipStream_t stream) {
-  const int bc = std::max(1, std::min(8, kXLdsFloats / d));
-  const int cpl = pow2_at_least(ceil_div(d / 8, kWave), 16);
-  const int nseg = gate_segments(F);
-  const int rmax = ceil_div(F, nseg);
-  if (rmax > kMaxSeg) return hipErrorInvalidValue;
-  for (int b0 = 0; b0 < N; b0 += bc) {
-    const int nb = std::min(bc, N - b0);
-    const int bm = pow2_at_least(nb, 8);
-    ProfScope prof("calib_gate", stream);
-    hipError_t e = launch_gate_mode<kModeAbsAct>(
-        bm, cpl, dim3(nseg), (size_t)nb * d * sizeof(float), stream, x + (size_t)b0 * d, nb,
-        reinterpret_cast<const uint4*>(wg), nullptr, d, F, 0.f, -1.f, rmax, nullptr, nullptr,
-        nullptr, nullptr, nullptr, absact + (size_t)b0 * F);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

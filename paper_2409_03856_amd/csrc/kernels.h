@@ -53,9 +53,13 @@ hipError_t launch_ffn_gemv(const float* x, int B, const uint16_t* wg, const uint
 hipError_t launch_gate_act(const float* x, int N, const uint16_t* wg, int d, int F,
                            float norm_eps, float* act, hipStream_t stream);
 
-// Gate activations |SiLU(W_gate x)| for N inputs into absact [N, F] (calibration).
-hipError_t launch_gate_absact(const float* x, int N, const uint16_t* wg, int d, int F,
-                              float* absact, hipStream_t stream);
+// Gate activations |SiLU(W_gate x)| for N inputs into absact [N, F] (calibration), on MFMA with
+// gate_absact_ws(N, d) bytes of workspace; zero_ints[0 .. nzero) are cleared on the way.
+size_t gate_absact_ws(int N, int d);
+hipError_t launch_gate_absact(const float* x, int N, const uint16_t* wg, int d, int F, float* absact,
+                              char* ws, int* zero_ints, int nzero, hipStream_t stream);
+// x [B][d] as three exact bf16 pieces xp [3][mpad][d], zero rows from B on; d % 4 == 0, d <= 8192.
+hipError_t launch_prep_pieces3(const float* x, int B, int d, int mpad, uint16_t* xp, hipStream_t stream);
 
 // Row-split down projection over compacted neuron lists: nseg segments of up to rmax rows
 // (uidx[seg*rmax + k], count ucnt[seg]), h values at hbuf[slot*hstride + b] for b < B <= 16,
@@ -149,10 +153,12 @@ hipError_t launch_batch_act(const float* x, int B, const uint16_t* wg, int d, in
                             float norm_eps, float* act, char* ws, const BatchLayout& L,
                             hipStream_t stream);
 
-// ---- radix select of the k-th largest non-negative float (ties resolved by index)
-hipError_t launch_select_kth_largest(const float* v, int n, int k, float* out_value,
-                                     char* ws, hipStream_t stream);
+// ---- radix select of the k-th largest of n non-negative floats (v 16-byte aligned). The counters
+// that select_zero_ints names must be zero when the call runs.
+hipError_t launch_select_kth_largest(const float* v, int n, int k, float* out_value, char* ws,
+                                     hipStream_t stream);
 size_t select_ws_bytes();
+int* select_zero_ints(char* ws, int* count);
 
 // ---- Griffin
 struct GriffinLayout {

@@ -1,11 +1,14 @@
 // Radix select of the k-th largest of n non-negative fp32 values on gfx950.
 //
-// Non-negative IEEE floats order like their bit patterns, so the k-th largest
-// is found one byte at a time, most significant first: a grid-wide histogram
-// of the current byte over the values that match the bytes already fixed
-// (LDS histograms merged with integer atomics, so the counts are exact),
-// then a one-thread pass that fixes the next byte. Four rounds give the exact
-// value. Used by the threshold calibration and by the prompt top-k.
+// Non-negative IEEE floats order like their bit patterns, so the k-th largest is found digit by
+// digit, most significant first (bits 30-20, 19-9, 8-0): a grid-wide histogram of the current
+// digit over the values that match the digits already fixed (LDS histograms merged with integer
+// atomics, so the counts are exact), whose k-th largest digit every workgroup of the next pass
+// finds for itself from the merged counts. Three passes and a last one-workgroup pick give the
+// exact value: four launches, three reads of the values (from the last-level cache after the
+// first), bound by LDS and global atomics and by launches. For 256 x 14336 values 26 us (four
+// passes of 8 bits with one-thread picks between them, nine launches: 86). Used by the threshold
+// calibration.
 #include "common.h"
 #include "kernels.h"
 #include "profile.h"
@@ -13,85 +16,147 @@
 namespace sirius {
 namespace {
 
+constexpr int kBins = 2048;          // 11-bit digits
+constexpr int kPasses = 3;
+constexpr int kSelThreads = 1024;
+constexpr int kSelWaves = kSelThreads / kWave;
+constexpr int kCopies = 4;           // LDS histograms: hot bins spread over them by lane
+constexpr int kSelBlocks = 128;     // each merges its bins with global atomics: 512 of half the size: 31 us in all, 128: 21
+
 struct SelectState {
-  uint32_t prefix;  // bytes fixed so far
-  uint32_t mask;    // which bits of prefix are fixed
+  uint32_t prefix;  // bits fixed so far
   int rem;          // rank still to find among the matching values
-  int pad;
 };
 
-constexpr int kHistBlocks = 512;
+__host__ __device__ constexpr int shift_of(int pass) { return pass == 0 ? 20 : (pass == 1 ? 9 : 0); }
+__host__ __device__ constexpr int bins_of(int pass) { return pass == 2 ? 512 : kBins; }
 
-__global__ void select_init_kernel(SelectState* st, int k, int* ghist) {
-  const int t = threadIdx.x;
-  if (t < 256) ghist[t] = 0;
-  if (t == 0) {
-    st->prefix = 0u;
-    st->mask = 0u;
-    st->rem = k;
+// The digit of the rem-th largest value in the merged histogram gh (bins in ascending digit order),
+// and the rank left inside it. Every thread of the workgroup returns both.
+__device__ void pick(const int* __restrict__ gh, int bins, int rem, int* digit, int* left) {
+  constexpr int kPer = kBins / kSelThreads;
+  __shared__ int s_w[kSelWaves], s_out[2];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+  // thread t holds the kPer bins below top - kPer t, in descending order
+  int c[kPer], sum = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int b = bins - 1 - (kPer * tid + i);
+    c[i] = b >= 0 ? gh[b] : 0;
+    sum += c[i];
   }
-}
-
-__global__ __launch_bounds__(256) void select_hist_kernel(const float* __restrict__ v, int n,
-                                                          int shift, const SelectState* st,
-                                                          int* ghist) {
-  __shared__ int h[256];
-  const uint32_t prefix = st->prefix, mask = st->mask;
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const uint32_t u = __float_as_uint(v[i]);
-    if ((u & mask) == prefix) atomicAdd(&h[(u >> shift) & 255u], 1);
+  int incl = sum;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int t = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += t;
   }
+  __syncthreads();  // an earlier pick's readers are done
+  if (lane == kWave - 1) s_w[wave] = incl;
   __syncthreads();
-  const int c = h[threadIdx.x];
-  if (c != 0) atomicAdd(&ghist[threadIdx.x], c);
-}
-
-__global__ void select_pick_kernel(int shift, SelectState* st, int* ghist, float* out_value) {
-  __shared__ int h[256];
-  h[threadIdx.x] = ghist[threadIdx.x];
-  ghist[threadIdx.x] = 0;  // ready for the next round
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int rem = st->rem;
-    int dsel = 0;
-    for (int dg = 255; dg >= 0; --dg) {
-      const int c = h[dg];
-      if (c >= rem) {
-        dsel = dg;
-        break;
+  int before = incl - sum;
+  for (int w = 0; w < wave; ++w) before += s_w[w];
+  if (before < rem && before + sum >= rem) {  // exactly one thread: the counts add up to >= rem
+    int r = rem - before, at = -1;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      if (at < 0) {
+        if (c[i] >= r) at = i;
+        else r -= c[i];
       }
-      rem -= c;
     }
-    st->rem = rem;
-    st->prefix |= (uint32_t)dsel << shift;
-    st->mask |= 255u << shift;
-    if (shift == 0) out_value[0] = __uint_as_float(st->prefix);
+    s_out[0] = bins - 1 - (kPer * tid + at);
+    s_out[1] = r;
   }
+  __syncthreads();
+  *digit = s_out[0];
+  *left = s_out[1];
+}
+
+// state[p] (p > 0): the prefix and rank going into pass p, from state[p - 1] and pass p - 1's counts.
+__device__ __forceinline__ SelectState state_of(int pass, int k, const SelectState* st, const int* ghist) {
+  SelectState s = pass <= 1 ? SelectState{0u, k} : st[pass - 1];
+  if (pass > 0) {
+    int dg, left;
+    pick(ghist + (pass - 1) * kBins, bins_of(pass - 1), s.rem, &dg, &left);
+    s.prefix |= (uint32_t)dg << shift_of(pass - 1);
+    s.rem = left;
+  }
+  return s;
+}
+
+template <int PASS>
+__global__ __launch_bounds__(kSelThreads) void select_hist_kernel(const float* __restrict__ v, int n,
+                                                                  int k, SelectState* st, int* ghist) {
+  constexpr int kShift = shift_of(PASS), kNb = bins_of(PASS);
+  constexpr int kAhead = 4;  // float4 loads in flight per thread
+  __shared__ int h[kCopies * kNb];
+  const int tid = threadIdx.x;
+  for (int i = tid; i < kCopies * kNb; i += kSelThreads) h[i] = 0;
+  const SelectState s = state_of(PASS, k, st, ghist);
+  if (PASS > 0 && blockIdx.x == 0 && tid == 0) st[PASS] = s;
+  __syncthreads();
+  const uint32_t fixed = PASS == 0 ? 0u : s.prefix >> shift_of(PASS > 0 ? PASS - 1 : 0);
+  int* hc = h + (tid & (kCopies - 1)) * kNb;
+  auto count = [&](float f) {
+    const uint32_t u = __float_as_uint(f);
+    if (PASS == 0 || (u >> shift_of(PASS > 0 ? PASS - 1 : 0)) == fixed)
+      atomicAdd(&hc[(u >> kShift) & (kNb - 1)], 1);
+  };
+  const int n4 = n >> 2, stride = gridDim.x * kSelThreads;
+  const float4* v4 = reinterpret_cast<const float4*>(v);
+  for (int i0 = blockIdx.x * kSelThreads + tid; i0 < n4; i0 += kAhead * stride) {
+    float4 f[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (i0 + u * stride < n4) f[u] = v4[i0 + u * stride];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (i0 + u * stride < n4) {
+        count(f[u].x);
+        count(f[u].y);
+        count(f[u].z);
+        count(f[u].w);
+      }
+  }
+  if (blockIdx.x == 0 && tid < (n & 3)) count(v[4 * n4 + tid]);
+  __syncthreads();
+  for (int b = tid; b < kNb; b += kSelThreads) {
+    int c = 0;
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u) c += h[u * kNb + b];
+    if (c != 0) atomicAdd(&ghist[PASS * kBins + b], c);
+  }
+}
+
+__global__ __launch_bounds__(kSelThreads) void select_pick_kernel(int k, const SelectState* st,
+                                                                  const int* ghist, float* out_value) {
+  const SelectState s = state_of(kPasses, k, st, ghist);
+  if (threadIdx.x == 0) out_value[0] = __uint_as_float(s.prefix);
 }
 
 }  // namespace
 
-size_t select_ws_bytes() { return 256 + 256 * sizeof(int); }
+size_t select_ws_bytes() { return 256 + kPasses * kBins * sizeof(int); }
+
+int* select_zero_ints(char* ws, int* count) {
+  *count = kPasses * kBins;
+  return reinterpret_cast<int*>(ws + 256);
+}
 
 hipError_t launch_select_kth_largest(const float* v, int n, int k, float* out_value, char* ws,
                                      hipStream_t stream) {
   SelectState* st = reinterpret_cast<SelectState*>(ws);
   int* ghist = reinterpret_cast<int*>(ws + 256);
+  const int blocks = std::max(1, std::min(kSelBlocks, ceil_div(n, kSelThreads * 16)));
   {
-    ProfScope prof("select_init", stream);
-    klaunch(select_init_kernel, 1, 256, 0, stream, st, k, ghist);
+    ProfScope prof("select_hist", stream);
+    klaunch(select_hist_kernel<0>, blocks, kSelThreads, 0, stream, v, n, k, st, ghist);
+    klaunch(select_hist_kernel<1>, blocks, kSelThreads, 0, stream, v, n, k, st, ghist);
+    klaunch(select_hist_kernel<2>, blocks, kSelThreads, 0, stream, v, n, k, st, ghist);
   }
-  const int blocks = std::max(1, std::min(kHistBlocks, ceil_div(n, 256 * 8)));
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    {
-      ProfScope prof("select_hist", stream);
-      klaunch(select_hist_kernel, blocks, 256, 0, stream, v, n, shift, st, ghist);
-    }
-    ProfScope prof("select_pick", stream);
-    klaunch(select_pick_kernel, 1, 256, 0, stream, shift, st, ghist, out_value);
-  }
+  ProfScope prof("select_pick", stream);
+  klaunch(select_pick_kernel, 1, kSelThreads, 0, stream, k, st, ghist, out_value);
   return hipGetLastError();
 }
 

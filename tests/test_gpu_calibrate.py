@@ -1,0 +1,58 @@
+"""GPU parity of the threshold calibration at the edges of its tiles (64 inputs x 128 neurons, 64
+columns per stage, 1024 inputs per launch) and of its radix select: ranks at both ends, ties,
+zeros, infinities. Tolerance: the nearest-rank value moves by no more than the largest error of an
+activation, fp32 sums of at most 8192 exact products: 1e-5 relative plus 2e-6 of the gate's spread
+(values near zero)."""
+
+import numpy as np
+import pytest
+
+import oracle
+from synth import ffn_weights, calibration_inputs
+from gpu_util import say, dev_bf16, dev_f32, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sr():
+    import paper_2409_03856_amd as sr
+    sr.lib()
+    return sr
+
+
+@pytest.mark.parametrize("d,f,n", [(8, 1, 1), (72, 127, 63), (264, 129, 65), (4104, 100, 64), (256, 700, 1100),
+                                   (8192, 260, 3)])
+def test_edges(sr, d, f, n):
+    say(f"calibrate d={d} f={f} N={n}")
+    wg, _, _ = ffn_weights(800 + d, d, f, 1.0 / np.sqrt(d))
+    x = calibration_inputs(800 + d, n, d)
+    xd, wd = dev_f32(x), dev_bf16(wg)
+    v = np.sort(np.abs(oracle.gate_activations(x, wg)).ravel())
+    for q in (1e-9, 0.25, 0.5, 0.9, 1.0):
+        want = v[min(max(int(np.ceil(q * v.size)), 1), v.size) - 1]
+        got = float(host(sr.sirius_cats_calibrate(xd, wd, q))[0])
+        assert abs(got - want) <= 1e-5 * want + 2e-6, (q, got, want)
+
+
+def test_ties_zeros_and_infinities(sr):
+    """Equal rows give equal values (one long run of ties), zero rows give zeros, and an input that
+    holds an infinity takes the highest ranks only."""
+    d, f, n = 264, 1000, 40
+    wg, _, _ = ffn_weights(900, d, f, 1.0 / np.sqrt(d))
+    wg[:400] = 0
+    wg[400:900] = wg[400]
+    x = np.repeat(calibration_inputs(900, 1, d), n, axis=0)
+    v = np.sort(np.abs(oracle.gate_activations(x, wg)).ravel())
+    for q in (0.1, 0.4, 0.41, 0.6, 0.95):
+        want = v[int(np.ceil(q * v.size)) - 1]
+        got = float(host(sr.sirius_cats_calibrate(dev_f32(x), dev_bf16(wg), q))[0])
+        assert abs(got - want) <= 1e-5 * want + (2e-6 if want > 0 else 0), (q, got, want)
+    clean = calibration_inputs(901, n, d)
+    wg, _, _ = ffn_weights(901, d, f, 1.0 / np.sqrt(d))
+    bad = np.concatenate([clean, clean[:1]])
+    bad[n, 7] = np.inf
+    t = float(host(sr.sirius_cats_calibrate(dev_f32(clean), dev_bf16(wg), 0.5))[0])
+    # the same rank among the clean values: all of the bad input's f activations lie above it
+    tb = float(host(sr.sirius_cats_calibrate(dev_f32(bad), dev_bf16(wg), 0.5 * n / (n + 1)))[0])
+    assert t == tb
