@@ -159,6 +159,9 @@ __global__ __launch_bounds__(kLmThreads) void linear_mfma_kernel(const uint4* __
                                     : make_uint4(0u, 0u, 0u, 0u);
     }
   };
+  // a block's products are summed from zero, the hi pieces apart from the rest, and then added to
+  // the total: the logits of an 8192-wide pass are then 4.0e-7 off 64 bits (5.8e-7 with one chain
+  // of products over all of K, 4.5e-7 by the vector kernels before)
   floatx4_t acc[RT][MT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
@@ -171,22 +174,30 @@ __global__ __launch_bounds__(kLmThreads) void linear_mfma_kernel(const uint4* __
     if (b + 1 < nblk) load_x(xnext, b + 1);
     ring_barrier();  // block b is in its buffer; every wave is done with block b - 1's reads
     const unsigned char* buf = lds + (b & 1) * kBuf;
+    bf16x8_t bw[kSteps][RT];
 #pragma unroll
-    for (int i = 0; i < kSteps; ++i) {
-      bf16x8_t bw[RT];
+    for (int i = 0; i < kSteps; ++i)
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
-        bw[rt] = *reinterpret_cast<const bf16x8_t*>(buf + (16 * rt + fr) * kPitch +
-                                                    64 * (kSteps * wave + i) + 16 * grp);
+        bw[i][rt] = *reinterpret_cast<const bf16x8_t*>(buf + (16 * rt + fr) * kPitch +
+                                                       64 * (kSteps * wave + i) + 16 * grp);
 #pragma unroll
-      for (int p = 0; p < kPieces; ++p)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
+      for (int mt = 0; mt < MT; ++mt) {
+        floatx4_t sh = floatx4_t{0.f, 0.f, 0.f, 0.f}, sl = sh;
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-            acc[rt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8_t, xcur[i][p][mt]), bw[rt], acc[rt][mt], 0, 0, 0);
-    }
+        for (int p = 2; p > 0; --p)
+#pragma unroll
+          for (int i = 0; i < kSteps; ++i)
+            sl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xcur[i][p][mt]),
+                                                         bw[i][rt], sl, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i)
+          sh = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xcur[i][0][mt]),
+                                                       bw[i][rt], sh, 0, 0, 0);
+        acc[rt][mt] += sh + sl;
+      }
   };
 #pragma unroll
   for (int u = 0; u < D; ++u)
@@ -244,12 +255,13 @@ hipError_t launch_t(const float* x, int n, int K, float eps, const LinearOut& o,
   // against 41, at 24 tokens and 16000 x 4096 34 against 54. Below that 16 rows, so that a layer's
   // projections fill the chip: 6144 x 4096 and 4096 x 4096 together 31.6 us against 43 with 32 rows
   // and 47 with 64; there one 16-token tile takes 1 KiB of a row per load and four blocks in flight
-  // (35 us with 512 bytes and two).
+  // (35 us with 512 bytes and two), unless K is too short to give every wave its part of a block.
   constexpr int kWide = 64 * 192;
   if (N >= kWide)
     klaunch(linear_mfma_kernel<MT, 4, 256, 2>, ceil_div(N, 64), kLmThreads, 0, s, xf, n, K, ksteps, o);
-  else if (MT == 1)
-    klaunch(linear_mfma_kernel<1, 1, 512, 4>, ceil_div(N, 16), kLmThreads, 0, s, xf, n, K, ksteps, o);
+  else if (MT == 1 && K >= 1024)
+    klaunch(linear_mfma_kernel<MT, 1, MT == 1 ? 512 : 256, MT == 1 ? 4 : 2>, ceil_div(N, 16), kLmThreads, 0,
+            s, xf, n, K, ksteps, o);
   else
     klaunch(linear_mfma_kernel<MT, 1, 256, 2>, ceil_div(N, 16), kLmThreads, 0, s, xf, n, K, ksteps, o);
   return hipGetLastError();
