@@ -6,88 +6,130 @@
 // rows 0 .. p + i. n = 1 is the sparse model's decode step, n = kernel size the full model's
 // verification pass over the drafted chunk. Query head h reads key/value head h / G
 // (G = H / Hkv); the G x n query rows that share a key/value head are processed together, so
-// every key and value row is read once per call.
+// every key and value row is read once per call and 64 query rows.
 //
-//  attn_partial_kernel  grid (position chunk, key/value head x row group, batch), 256 threads.
-//                       The chunk's keys and values are staged 64 rows at a time in LDS as
-//                       bf16, every load of a tile issued before the first is stored (cache
-//                       rows below p, the new rows from p on; the row-group-0 workgroup also
-//                       writes the new rows into the cache: each is written by exactly one
-//                       workgroup and never read back from the cache in the call). Scores in
-//                       fp32: with more than 16 query rows from 4 rows x 4 positions register
-//                       blocks, else each score's dot product split over four lanes; causal
-//                       mask, online softmax (running max and sum per row), P.V into 4 x 4
-//                       register blocks (with few rows, the tile's positions split over groups
-//                       of threads whose shares are summed in a fixed order); the chunk's
-//                       (max, sum, unnormalised output) per row go to the workspace. The score
-//                       tile reuses the key buffer once the scores are formed. A cache of at
-//                       most 256 rows is one chunk per workgroup (its tiles in turn), and the
-//                       kernel writes the normalised output itself: no merge launch.
-//  attn_combine_kernel  one workgroup per query row: the chunks' (max, sum) and their first
-//                       outputs (all of them, up to 64 chunks) requested together, the
-//                       weights exp(m_c - M) (one chunk per thread), then each thread sums
-//                       its output column over the chunks in order.
+//  attn_partial_kernel  grid (split, key/value head x row group, batch), four waves. The visible
+//                       rows of a batch entry are cut on the device into equal chunks (the
+//                       position lives there), so every split works whatever the cache's
+//                       capacity. Both products run on MFMA in fp32 precision: the scaled query
+//                       and the probabilities are split into three bf16 pieces that hold every
+//                       bit, keys and values are bf16 already. Scores are formed as K Q^T, whose
+//                       result layout (a lane holds one query row and 4 positions of each tile)
+//                       is the B operand of V^T P^T when its K slots are numbered accordingly:
+//                       probabilities never leave their registers, and the running max, sum and
+//                       rescaling are per lane. QW of the waves' groups take 16 query rows each,
+//                       the 4 / QW others split the positions of a tile and are merged in order at
+//                       the end. Keys are staged row by row, values transposed (four positions
+//                       of a column as one 8-byte store, swizzled), through registers one tile
+//                       ahead. The row-group-0 workgroup also writes the new rows into the cache:
+//                       each is written by exactly one workgroup and never read back in the call.
+//                       With one split the kernel writes the normalised output itself.
+//  attn_combine_kernel  one workgroup per query row: the chunks' (max, sum) and outputs
+//                       requested together, the weights exp(m_c - M) (one chunk per thread),
+//                       then each thread sums its output column over the chunks in order.
 //  kv_rollback_kernel   cache_pos[b] += min(accept_len[b] + 1, n).
+//
+// Bound: HBM for one token (2 L Hkv hd 2 bytes) and launch latency at short contexts; at 16 tokens
+// of 4 heads per key/value head the matrix work (12 n G L hd flops with the pieces) and the
+// exponentials weigh as much as the bytes. Llama-3-8B
+// heads, one token over 2048 rows: 7.9 us and 4.8 for the merge (12.0 + 4.7 with fp32 vector
+// products and chunks by capacity); 16 sequences of one token over 1500-3000 rows 35 + 4 us
+// (85 + 6); 8 sequences of 16 tokens over 3500-7000 rows 72 + 8 us (345 + 53). The high pieces'
+// sums of a score are kept apart from the rest: 2.1e-7 off 64 bits (2.3e-7 before; 3.0e-7 in one
+// chain).
 #include <math.h>
 
 #include "common.h"
 #include "kernels.h"
 #include "profile.h"
+#include "ring.h"
 
 namespace sirius {
 namespace {
 
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4_t;
+
 constexpr int kAttnThreads = 256;
-constexpr int kTile = 64;                 // positions staged per step
 constexpr int kMaxHd = 128;
 constexpr int kMaxRowsWg = 64;            // query rows per workgroup
-constexpr int kPitch = kMaxHd + 4;        // LDS row pitch (floats): 16-byte rows off the banks
-constexpr int kPPitch = kMaxRowsWg + 4;   // score tile pitch: a position's rows off the banks
-constexpr int kKVPitch8 = kMaxHd / 8 + 1; // bf16 key/value rows in 16-byte units (+1 off the banks)
-constexpr int kMaxOB = 2;                 // 4 x 4 output blocks per thread: 64 rows x 128 / 256 / 16
-constexpr int kStagePer = kTile * kMaxHd / 8 / kAttnThreads;  // 16-byte loads per thread and tile
-constexpr int kMaxSplits = 256;           // position chunks per call at most
+constexpr int kMaxSplits = 64;            // chunks per call: the merge takes them in one load batch
+constexpr int kTargetWgs = 512;           // workgroups of the partial kernel
 constexpr int kDirectMax = 256;           // caches up to this many rows: one chunk, no combine
-constexpr int kOneBatchMax = 64;          // merges of at most this many chunks: one load batch
 
-// BIG: up to 64 rows, scores in 4 x 4 register blocks; else up to 16 rows, each score's dot
-// product split over four lanes. Keys and values are staged as bf16; the score tile reuses
-// the key buffer once the scores are formed (69 KB of LDS: two workgroups per CU).
-template <bool BIG>
-__global__ __launch_bounds__(kAttnThreads) void attn_partial_kernel(
+// The high halves of two floats as a pair of bf16 (a in the low half).
+__device__ __forceinline__ uint32_t high_halves(float a, float b) {
+  return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+}
+// x less its truncation to bf16, exact; 0 where nothing is left (infinities too).
+__device__ __forceinline__ float rest(float x) {
+  const float h = __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+  return h == x ? 0.f : x - h;
+}
+
+// x less its truncation to bf16 for a finite x.
+__device__ __forceinline__ float rest_finite(float x) {
+  return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+}
+
+// e^x for x <= 0 to about one ulp: the hardware exp2 of the rounded x log2(e), times the first
+// order of what the rounding left off. Below -200 (a hidden position's -inf, a NaN) 0.
+__device__ __forceinline__ float exp_neg(float x) {
+  constexpr float kHi = 1.44269502162933349609375f, kLo = 1.9259629911e-8f, kLn2 = 0.693147180559945f;
+  x = fmaxf(x, -200.f);
+  const float t = x * kHi;
+  const float d = fmaf(x, kLo, fmaf(x, kHi, -t));
+  return __builtin_amdgcn_exp2f(t) * fmaf(d, kLn2, 1.f);
+}
+
+// KS: 32-wide steps of the head dimension (2: hd <= 64, 4: hd <= 128). QW: 16-row query tiles
+// (1, 2 or 4), one per wave group; the 4 / QW waves of a group split a tile's positions. NB: 32-position
+// blocks per wave and tile.
+template <int KS, int QW, int NB>
+__global__ __launch_bounds__(kAttnThreads, 2) void attn_partial_kernel(
     const float* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
     uint4* __restrict__ k_cache, uint4* __restrict__ v_cache, const int32_t* __restrict__ cache_pos,
-    int n, int H, int Hkv, int hd, int Lmax, int chunk, int rgroups, int R, float scale,
+    int n, int H, int Hkv, int hd, int Lmax, int rgroups, int R, float scale,
     float* __restrict__ pm, float* __restrict__ pl, float* __restrict__ po,
     float* __restrict__ out) {
-  constexpr int kRows = BIG ? kMaxRowsWg : 16;
-  __shared__ float s_q[kRows * kPitch];
-  __shared__ uint4 s_kp[kTile * kKVPitch8];  // keys (bf16), then the score tile [position][row]
-  __shared__ uint4 s_v[kTile * kKVPitch8];   // values (bf16)
-  __shared__ float s_m[kRows], s_l[kRows], s_alpha[kRows];
-  float* s_p = reinterpret_cast<float*>(s_kp);
-  const uint16_t* s_v16 = reinterpret_cast<const uint16_t*>(s_v);
-  const int tid = threadIdx.x;
+  constexpr int PW = 4 / QW;
+  constexpr int TP = PW * NB * 32;              // positions per tile
+  constexpr int kHd = KS * 32;                  // padded head dimension
+  constexpr int kC = KS * 4;                    // 16-byte chunks of a padded row
+  constexpr int kKPitch = kHd * 2 + 16;         // the 16 rows of an operand read: all banks
+  constexpr int kVCh = TP / 8;                  // 16-byte chunks of a transposed value row
+  constexpr int kVOfs = TP * kKPitch;
+  constexpr int kKLoads = TP * kC / kAttnThreads;
+  constexpr int kVTasks = TP / 4 * kC / kAttnThreads;  // four positions x 8 columns each
+  constexpr int kQBytes = QW * 16 * kC * 3 * 16;
+  constexpr int kKVBytes = kVOfs + kHd * TP * 2;
+  constexpr int kRed = PW > 1 ? 4 * 16 * kHd * 4 : 0;
+  constexpr int kLds = kQBytes > kKVBytes ? (kQBytes > kRed ? kQBytes : kRed) : (kKVBytes > kRed ? kKVBytes : kRed);
+  static_assert(TP * kC % kAttnThreads == 0 && TP / 4 * kC % kAttnThreads == 0, "whole loads");
+  static_assert(kVCh == 8 || kVCh == 16, "value swizzle");
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+  __shared__ float s_m[4][16], s_l[4][16];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+  const int fr = lane & 15, g = lane >> 4;
   const int split = blockIdx.x, nsplit = gridDim.x;
   const int kvh = blockIdx.y / rgroups, rg = blockIdx.y % rgroups, b = blockIdx.z;
-  const int G = H / Hkv;
+  const int G = H / Hkv, hd8 = hd >> 3;
+  const int r0 = rg * kMaxRowsWg, nr = min(16 * QW, R - r0);
+  const size_t rowbase = ((size_t)b * Hkv + kvh) * R + r0;  // partial row index of row r0
+  auto q_row = [&](int r) {  // row r0 + r of the group: token i, head h
+    const int rr = r0 + r, i = rr / G, h = kvh * G + (rr - i * G);
+    return (((size_t)b * n + i) * H + h) * hd;
+  };
   const int p = cache_pos[b];
   const bool valid = p >= 0 && p + n <= Lmax;
   const int L = p + n;
+  // the entry's rows in nsplit equal chunks of whole 32-position blocks
+  const int chunk = valid ? ((L + nsplit - 1) / nsplit + 31) & ~31 : 32;
   const int c0 = split * chunk, c1 = min(c0 + chunk, L);
-  const int r0 = rg * kMaxRowsWg, nr = min(kRows, R - r0);
-  const int nr4 = (nr + 3) & ~3;
-  const int hd4 = hd >> 2, hd8 = hd >> 3;
-  const size_t rowbase = ((size_t)b * Hkv + kvh) * R + r0;  // partial row index of row r0
-  // one chunk per row (out != nullptr): the output itself, out[b][i][h][:] for row r0 + r
-  auto out_row = [&](int r) {
-    const int rr = r0 + r, i = rr / G, h = kvh * G + (rr - i * G);
-    return out + (((size_t)b * n + i) * H + h) * hd;
-  };
 
   if (!valid || c0 >= L) {  // nothing visible in this chunk (or a position outside the cache)
     if (out != nullptr) {  // what the merge of empty chunks gives: 0 / 0
-      for (int e = tid; e < nr * hd; e += kAttnThreads) out_row(e / hd)[e % hd] = __builtin_nanf("");
+      for (int e = tid; e < nr * hd; e += kAttnThreads) out[q_row(e / hd) + e % hd] = __builtin_nanf("");
       return;
     }
     if (tid < nr) {
@@ -96,346 +138,261 @@ __global__ __launch_bounds__(kAttnThreads) void attn_partial_kernel(
     }
     return;
   }
-  // the direct rewrite: the new rows of this chunk go into the cache; the thread's first new-row
-  // chunk and its first query chunk are requested together, so the two take one round trip
-  const int w0 = max(c0, p);
-  const int ncw = rg == 0 ? (c1 - w0) * hd8 : 0;  // 16-byte chunks of new rows to write
-  {
-    uint4 kw0 = make_uint4(0u, 0u, 0u, 0u), vw0 = kw0;
-    size_t dst0 = 0;
-    if (tid < ncw) {
-      const int j = tid / hd8, c = tid - j * hd8, pos = w0 + j;
-      const size_t src = (((size_t)b * n + (pos - p)) * Hkv + kvh) * hd8 + c;
-      dst0 = (((size_t)b * Lmax + pos) * Hkv + kvh) * hd8 + c;
-      kw0 = k_new[src];
-      vw0 = v_new[src];
+  // ---- loads of one tile: keys and values from the cache below p, the new rows from p on, zero
+  // past the chunk. K: 16-byte chunk tid % kC of row tid / kC + ..; V: chunk of four rows.
+  const int lc = tid % kC, lr = tid / kC;
+  const bool col = lc < hd8;
+  const size_t rs = (size_t)Hkv * hd8;  // 16-byte units between positions
+  const size_t cbase = (size_t)b * Lmax * rs + (size_t)kvh * hd8 + lc;
+  const size_t nbase = (size_t)b * n * rs + (size_t)kvh * hd8 + lc;
+  uint4 kw[kKLoads], vw[kVTasks][4];
+  auto fetch = [&](const uint4* cache, const uint4* fresh, int pos) {
+    if (!col || pos >= c1) return make_uint4(0u, 0u, 0u, 0u);
+    return pos < p ? cache[cbase + pos * rs] : fresh[nbase + (pos - p) * rs];
+  };
+  auto load_tile = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < kKLoads; ++u) kw[u] = fetch(k_cache, k_new, t0 + lr + u * (kAttnThreads / kC));
+#pragma unroll
+    for (int u = 0; u < kVTasks; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        vw[u][j] = fetch(v_cache, v_new, t0 + 4 * (lr + u * (kAttnThreads / kC)) + j);
+  };
+  auto v_at = [&](int c, int chunk16) {  // byte offset of 16-byte chunk chunk16 of value column c
+    const int f = kVCh == 16 ? ((c >> 3) ^ c) & 15 : ((c >> 3) ^ (c >> 1)) & 7;
+    return kVOfs + c * (TP * 2) + 16 * (chunk16 ^ f);
+  };
+  auto store_tile = [&]() {
+#pragma unroll
+    for (int u = 0; u < kKLoads; ++u)
+      *reinterpret_cast<uint4*>(lds + (lr + u * (kAttnThreads / kC)) * kKPitch + 16 * lc) = kw[u];
+#pragma unroll
+    for (int u = 0; u < kVTasks; ++u) {
+      // positions 4 qd .. 4 qd + 3 of a 32-position block: K slots 8 (qd & 3) + 4 (qd >> 2 & 1) ..
+      const int qd = lr + u * (kAttnThreads / kC);
+      const int ch = (qd >> 3) * 4 + (qd & 3), half = (qd >> 2) & 1;
+      const uint32_t* a = &vw[u][0].x;
+      const uint32_t* bq = &vw[u][1].x;
+      const uint32_t* cq = &vw[u][2].x;
+      const uint32_t* dq = &vw[u][3].x;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+        const uint2 w = make_uint2(__builtin_amdgcn_perm(bq[e >> 1], a[e >> 1], sel),
+                                   __builtin_amdgcn_perm(dq[e >> 1], cq[e >> 1], sel));
+        *reinterpret_cast<uint2*>(lds + v_at(8 * lc + e, ch) + 8 * half) = w;
+      }
     }
-    float4 qv = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int qr = tid / hd4, qd4 = tid - qr * hd4;
-    if (tid < nr4 * hd4 && qr < nr) {
-      const int rr = r0 + qr, i = rr / G, h = kvh * G + (rr - i * G);
-      qv = reinterpret_cast<const float4*>(q + (((size_t)b * n + i) * H + h) * hd)[qd4];
-    }
-    if (tid < ncw) {
-      k_cache[dst0] = kw0;
-      v_cache[dst0] = vw0;
-    }
-    if (tid < nr4 * hd4)
-      *reinterpret_cast<float4*>(&s_q[qr * kPitch + 4 * qd4]) =
-          make_float4(qv.x * scale, qv.y * scale, qv.z * scale, qv.w * scale);
-  }
+  };
+  load_tile(c0);
+  // ---- the direct rewrite: the new rows of this chunk go into the cache
   if (rg == 0) {
-    for (int e = tid + kAttnThreads; e < ncw; e += kAttnThreads) {
+    const int w0 = max(c0, p), ncw = (c1 - w0) * hd8;
+    for (int e = tid; e < ncw; e += kAttnThreads) {
       const int j = e / hd8, c = e - j * hd8, pos = w0 + j;
-      const size_t src = (((size_t)b * n + (pos - p)) * Hkv + kvh) * hd8 + c;
-      const size_t dst = (((size_t)b * Lmax + pos) * Hkv + kvh) * hd8 + c;
+      const size_t src = ((size_t)b * n + (pos - p)) * rs + (size_t)kvh * hd8 + c;
+      const size_t dst = ((size_t)b * Lmax + pos) * rs + (size_t)kvh * hd8 + c;
       k_cache[dst] = k_new[src];
       v_cache[dst] = v_new[src];
     }
   }
-  // query rows (row r = token i * G + head g), scaled; padding rows are zero
-  for (int e = tid + kAttnThreads; e < nr4 * hd4; e += kAttnThreads) {
-    const int r = e / hd4, d4 = e - r * hd4;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (r < nr) {
-      const int rr = r0 + r, i = rr / G, h = kvh * G + (rr - i * G);
-      v = reinterpret_cast<const float4*>(q + (((size_t)b * n + i) * H + h) * hd)[d4];
-      v.x *= scale;
-      v.y *= scale;
-      v.z *= scale;
-      v.w *= scale;
-    }
-    *reinterpret_cast<float4*>(&s_q[r * kPitch + 4 * d4]) = v;
-  }
-  if (tid < nr) {
-    s_m[tid] = -INFINITY;
-    s_l[tid] = 0.f;
-  }
-  // output blocks of 4 rows x 4 columns; with few blocks the positions of a tile are split
-  // over jg groups of threads, each accumulating its own share (summed once at the end)
-  const int nob = (nr4 >> 2) * hd4;
-  const int jg = BIG ? 1 : max(1, min(8, kAttnThreads / nob));
-  const int jgrp = tid / nob, job = tid - jgrp * nob;  // group, block (non-BIG)
-  float4 acc[kMaxOB][4];
+  // ---- query rows, scaled, as three pieces in operand order [tile][step][piece][lane], then to
+  // registers; rows past the group's and columns past hd are zero
+  {
+    uint4* s_q = reinterpret_cast<uint4*>(lds);
 #pragma unroll
-  for (int u = 0; u < kMaxOB; ++u)
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) acc[u][rr] = make_float4(0.f, 0.f, 0.f, 0.f);
-
-  for (int t0 = c0; t0 < c1; t0 += kTile) {
-    const int tn = min(kTile, c1 - t0);
-    __syncthreads();  // the previous step's readers are done with s_kp, s_v
-    // ---- stage keys and values (bf16): cache rows below p, new rows from p on; zero past tn.
-    // Every load of the tile is issued before the first is stored.
-    {
-      uint4 kw[kStagePer], vw[kStagePer];
-#pragma unroll
-      for (int u = 0; u < kStagePer; ++u) {
-        const int e = tid + u * kAttnThreads;
-        const int j = e / hd8, c = e - j * hd8, pos = t0 + j;
-        kw[u] = make_uint4(0u, 0u, 0u, 0u);
-        vw[u] = make_uint4(0u, 0u, 0u, 0u);
-        if (j < tn) {
-          const size_t i = (pos < p) ? (((size_t)b * Lmax + pos) * Hkv + kvh) * hd8 + c
-                                     : (((size_t)b * n + (pos - p)) * Hkv + kvh) * hd8 + c;
-          kw[u] = ((pos < p) ? k_cache : k_new)[i];
-          vw[u] = ((pos < p) ? v_cache : v_new)[i];
+    for (int u = 0; u < QW * 16 * kC / kAttnThreads + (QW * 16 * kC % kAttnThreads != 0); ++u) {
+      const int e = tid + u * kAttnThreads, r = e / kC, c = e % kC;
+      if (r < 16 * QW) {
+        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (r < nr && c < hd8) {
+          const float4* src = reinterpret_cast<const float4*>(q + q_row(r)) + 2 * c;
+          const float4 x = src[0], y = src[1];
+          v[0] = x.x * scale; v[1] = x.y * scale; v[2] = x.z * scale; v[3] = x.w * scale;
+          v[4] = y.x * scale; v[5] = y.y * scale; v[6] = y.z * scale; v[7] = y.w * scale;
         }
-      }
 #pragma unroll
-      for (int u = 0; u < kStagePer; ++u) {
-        const int e = tid + u * kAttnThreads;
-        const int j = e / hd8, c = e - j * hd8;
-        if (j < kTile) {
-          s_kp[j * kKVPitch8 + c] = kw[u];
-          s_v[j * kKVPitch8 + c] = vw[u];
-        }
-      }
-    }
-    __syncthreads();
-    // ---- scores with the causal mask (held in registers until the keys are no longer read)
-    constexpr int CB = BIG ? 4 : 1;
-    float sc[4][CB];   // BIG: rows 4 rb.., positions cb + 16 cc; else rows of row block rbs
-    float scs[4][4];   // non-BIG: four row blocks x four rows, one position
-    if (BIG) {
-      const int rb = tid >> 4, cb = tid & 15;
+        for (int pc = 0; pc < 3; ++pc) {
+          s_q[(((r >> 4) * KS + (c >> 2)) * 3 + pc) * kWave + 16 * (c & 3) + (r & 15)] =
+              make_uint4(high_halves(v[0], v[1]), high_halves(v[2], v[3]), high_halves(v[4], v[5]),
+                         high_halves(v[6], v[7]));
 #pragma unroll
-      for (int rr = 0; rr < 4; ++rr)
-#pragma unroll
-        for (int cc = 0; cc < CB; ++cc) sc[rr][cc] = 0.f;
-      if (4 * rb < nr4) {
-        for (int d8 = 0; d8 < hd8; ++d8) {
-          float kf[CB][8];
-#pragma unroll
-          for (int cc = 0; cc < CB; ++cc) {
-            const uint4 w = s_kp[(cb + 16 * cc) * kKVPitch8 + d8];
-            kf[cc][0] = bf16_lo(w.x); kf[cc][1] = bf16_hi(w.x); kf[cc][2] = bf16_lo(w.y);
-            kf[cc][3] = bf16_hi(w.y); kf[cc][4] = bf16_lo(w.z); kf[cc][5] = bf16_hi(w.z);
-            kf[cc][6] = bf16_lo(w.w); kf[cc][7] = bf16_hi(w.w);
-          }
-#pragma unroll
-          for (int rr = 0; rr < 4; ++rr) {
-            const float4 qa = *reinterpret_cast<const float4*>(&s_q[(4 * rb + rr) * kPitch + 8 * d8]);
-            const float4 qb = *reinterpret_cast<const float4*>(&s_q[(4 * rb + rr) * kPitch + 8 * d8 + 4]);
-#pragma unroll
-            for (int cc = 0; cc < CB; ++cc) {
-              float a = sc[rr][cc];
-              a = fmaf(qa.x, kf[cc][0], a); a = fmaf(qa.y, kf[cc][1], a);
-              a = fmaf(qa.z, kf[cc][2], a); a = fmaf(qa.w, kf[cc][3], a);
-              a = fmaf(qb.x, kf[cc][4], a); a = fmaf(qb.y, kf[cc][5], a);
-              a = fmaf(qb.z, kf[cc][6], a); a = fmaf(qb.w, kf[cc][7], a);
-              sc[rr][cc] = a;
-            }
-          }
-        }
-      }
-    } else {
-      // position j = tid / 4; lane quarter dq takes head-dim chunks dq, dq + 4, ...
-      const int j = tid >> 2, dq = tid & 3;
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) scs[rb][rr] = 0.f;
-      for (int d8 = dq; d8 < hd8; d8 += 4) {
-        const uint4 w = s_kp[j * kKVPitch8 + d8];
-        const float kf[8] = {bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y),
-                             bf16_lo(w.z), bf16_hi(w.z), bf16_lo(w.w), bf16_hi(w.w)};
-#pragma unroll
-        for (int rb = 0; rb < 4; ++rb) {
-          if (4 * rb < nr4) {
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-              const float4 qa = *reinterpret_cast<const float4*>(&s_q[(4 * rb + rr) * kPitch + 8 * d8]);
-              const float4 qb = *reinterpret_cast<const float4*>(&s_q[(4 * rb + rr) * kPitch + 8 * d8 + 4]);
-              float a = scs[rb][rr];
-              a = fmaf(qa.x, kf[0], a); a = fmaf(qa.y, kf[1], a);
-              a = fmaf(qa.z, kf[2], a); a = fmaf(qa.w, kf[3], a);
-              a = fmaf(qb.x, kf[4], a); a = fmaf(qb.y, kf[5], a);
-              a = fmaf(qb.z, kf[6], a); a = fmaf(qb.w, kf[7], a);
-              scs[rb][rr] = a;
-            }
-          }
-        }
-      }
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          scs[rb][rr] += __shfl_xor(scs[rb][rr], 1, kWave);
-          scs[rb][rr] += __shfl_xor(scs[rb][rr], 2, kWave);
-        }
-    }
-    __syncthreads();  // keys read: the score tile takes their place
-    if (BIG) {
-      const int rb = tid >> 4, cb = tid & 15;
-      if (4 * rb < nr4) {
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const int r = 4 * rb + rr;
-          const int lim = p + (r0 + r) / G;  // last visible position of row r
-#pragma unroll
-          for (int cc = 0; cc < CB; ++cc) {
-            const int j = cb + 16 * cc;
-            // padding rows get 0 (they never enter the softmax); hidden positions -inf
-            s_p[j * kPPitch + r] = (r >= nr) ? 0.f : ((j < tn && t0 + j <= lim) ? sc[rr][cc] : -INFINITY);
-          }
-        }
-      }
-    } else if ((tid & 3) == 0) {
-      const int j = tid >> 2;
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
-        if (4 * rb < nr4) {
-#pragma unroll
-          for (int rr = 0; rr < 4; ++rr) {
-            const int r = 4 * rb + rr;
-            const int lim = p + (r0 + r) / G;
-            s_p[j * kPPitch + r] = (r >= nr) ? 0.f : ((j < tn && t0 + j <= lim) ? scs[rb][rr] : -INFINITY);
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // ---- online softmax: LPR lanes per row (4 for up to 64 rows, 16 for up to 16), the tile's
-    // positions split evenly over them
-    {
-      constexpr int LPR = BIG ? 4 : 16, PPL = kTile / LPR;
-      const int r = tid / LPR, part = tid % LPR;
-      float mx = -INFINITY;
-      if (r < nr) {
-#pragma unroll
-        for (int jj = 0; jj < PPL; ++jj) mx = fmaxf(mx, s_p[(part * PPL + jj) * kPPitch + r]);
-      }
-#pragma unroll
-      for (int m = 1; m < LPR; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, kWave));
-      float m_old = -INFINITY, m_new = -INFINITY;
-      if (r < nr) {
-        m_old = s_m[r];
-        m_new = fmaxf(m_old, mx);
-      }
-      float sum = 0.f;
-      if (r < nr) {
-#pragma unroll
-        for (int jj = 0; jj < PPL; ++jj) {
-          float* sp = &s_p[(part * PPL + jj) * kPPitch + r];
-          const float e = (*sp > -INFINITY) ? expf(*sp - m_new) : 0.f;
-          *sp = e;
-          sum += e;
-        }
-      }
-#pragma unroll
-      for (int m = 1; m < LPR; m <<= 1) sum += __shfl_xor(sum, m, kWave);
-      if (r < nr && part == 0) {
-        const float alpha = (m_old > -INFINITY) ? expf(m_old - m_new) : 0.f;
-        s_alpha[r] = alpha;
-        s_m[r] = m_new;
-        s_l[r] = s_l[r] * alpha + sum;
-      }
-    }
-    __syncthreads();
-    // ---- O = alpha O + P V over 4 x 4 output blocks (a thread group's share of positions)
-#pragma unroll
-    for (int u = 0; u < kMaxOB; ++u) {
-      const int ob = BIG ? tid + u * kAttnThreads : job;
-      const bool mine = BIG ? (ob < nob) : (u == 0 && jgrp < jg);
-      if (mine) {
-        const int rb = ob / hd4, d4 = ob - rb * hd4;
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const int r = 4 * rb + rr;
-          const float al = (r < nr) ? s_alpha[r] : 0.f;
-          acc[u][rr].x *= al;
-          acc[u][rr].y *= al;
-          acc[u][rr].z *= al;
-          acc[u][rr].w *= al;
-        }
-        const int span = kTile / jg, j0 = (BIG ? 0 : jgrp) * span, j1 = min(j0 + span, tn);
-#pragma unroll 4
-        for (int j = j0; j < j1; ++j) {
-          const float4 pv = *reinterpret_cast<const float4*>(&s_p[j * kPPitch + 4 * rb]);
-          const uint2 vw = *reinterpret_cast<const uint2*>(&s_v16[j * kKVPitch8 * 8 + 4 * d4]);
-          const float vv[4] = {bf16_lo(vw.x), bf16_hi(vw.x), bf16_lo(vw.y), bf16_hi(vw.y)};
-          const float pr[4] = {pv.x, pv.y, pv.z, pv.w};
-#pragma unroll
-          for (int rr = 0; rr < 4; ++rr) {
-            acc[u][rr].x = fmaf(pr[rr], vv[0], acc[u][rr].x);
-            acc[u][rr].y = fmaf(pr[rr], vv[1], acc[u][rr].y);
-            acc[u][rr].z = fmaf(pr[rr], vv[2], acc[u][rr].z);
-            acc[u][rr].w = fmaf(pr[rr], vv[3], acc[u][rr].w);
-          }
+          for (int e2 = 0; e2 < 8; ++e2) v[e2] = rest(v[e2]);
         }
       }
     }
   }
-  // ---- this chunk's partial: max, sum and the unnormalised output per row (with one chunk,
-  // the output itself: the unnormalised output over the sum, as the merge computes it)
   __syncthreads();
-  if (tid < nr && out == nullptr) {
-    pm[(rowbase + tid) * nsplit + split] = s_m[tid];
-    pl[(rowbase + tid) * nsplit + split] = s_l[tid];
-  }
-  if (BIG) {
+  const int qt = wave / PW, pw = wave % PW;
+  bf16x8_t qf[KS][3];
 #pragma unroll
-    for (int u = 0; u < kMaxOB; ++u) {
-      const int ob = tid + u * kAttnThreads;
-      if (ob < nob) {
-        const int rb = ob / hd4, d4 = ob - rb * hd4;
+  for (int i = 0; i < KS; ++i)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const int r = 4 * rb + rr;
-          if (r < nr && out != nullptr) {
-            const float l = s_l[r];
-            const float4 a = acc[u][rr];
-            reinterpret_cast<float4*>(out_row(r))[d4] = make_float4(a.x / l, a.y / l, a.z / l, a.w / l);
-          } else if (r < nr) {
-            reinterpret_cast<float4*>(po + ((rowbase + r) * nsplit + split) * hd)[d4] = acc[u][rr];
-          }
+    for (int pc = 0; pc < 3; ++pc)
+      qf[i][pc] = *reinterpret_cast<const bf16x8_t*>(lds + ((((qt * KS + i) * 3 + pc) * kWave) + lane) * 16);
+  const int row = 16 * qt + fr;                                 // this lane's query row
+  const int lim = row < nr ? p + (r0 + row) / G : -1;           // its last visible position
+  float m = -INFINITY, l = 0.f;
+  floatx4_t o[2 * KS];  // columns 16 t + 4 g + e of the row
+#pragma unroll
+  for (int t = 0; t < 2 * KS; ++t) o[t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  ring_barrier();  // the query pieces are read: the tile buffers take their place
+
+  for (int t0 = c0; t0 < c1; t0 += TP) {
+    store_tile();
+    ring_barrier();
+    if (t0 + TP < c1) load_tile(t0 + TP);
+    // ---- scores: lane holds positions 16 t + 4 g + e of its blocks
+    floatx4_t s[NB][2];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int j = (pw * NB + nb) * 32 + 16 * t;
+        floatx4_t a = floatx4_t{0.f, 0.f, 0.f, 0.f}, low = a;
+#pragma unroll
+        for (int i = 0; i < KS; ++i) {
+          const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(lds + (j + fr) * kKPitch + 64 * i + 16 * g);
+#pragma unroll
+          for (int pc = 2; pc > 0; --pc)
+            low = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[i][pc], low, 0, 0, 0);
+          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[i][0], a, 0, 0, 0);
         }
+        s[nb][t] = a + low;
+      }
+    if (t0 + TP > min(c1, p + 1)) {  // uniform: a tile with hidden positions or past the chunk
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int pos = t0 + (pw * NB + nb) * 32 + 16 * t + 4 * g + e;
+            if (pos > lim || pos >= c1) s[nb][t][e] = -INFINITY;
+          }
+    }
+    // ---- online softmax of the row
+    float mx = -INFINITY;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[nb][t][e]);
+    mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+    const float m_new = fmaxf(m, mx);
+    const float alpha = exp_neg(m - m_new);  // 0 before the first visible position
+    m = m_new;
+    l *= alpha;
+#pragma unroll
+    for (int t = 0; t < 2 * KS; ++t) o[t] *= alpha;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      float pr[8];
+      float sum = 0.f;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float w = exp_neg(s[nb][t][e] - m_new);
+          pr[4 * t + e] = w;
+          sum += w;
+        }
+      l += sum;
+      // ---- O^T += V^T P^T: the probabilities' pieces are the B operand as they are
+      bf16x8_t pf[3];
+#pragma unroll
+      for (int pc = 0; pc < 3; ++pc) {
+        const uint4 w = make_uint4(high_halves(pr[0], pr[1]), high_halves(pr[2], pr[3]),
+                                   high_halves(pr[4], pr[5]), high_halves(pr[6], pr[7]));
+        pf[pc] = __builtin_bit_cast(bf16x8_t, w);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pr[e] = rest_finite(pr[e]);
+      }
+#pragma unroll
+      for (int t = 0; t < 2 * KS; ++t) {
+        const bf16x8_t vf = *reinterpret_cast<const bf16x8_t*>(lds + v_at(16 * t + fr, (pw * NB + nb) * 4 + g));
+#pragma unroll
+        for (int pc = 0; pc < 3; ++pc) o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[pc], o[t], 0, 0, 0);
+      }
+    }
+    ring_barrier();  // every wave is done with the tile
+  }
+  // ---- this chunk's partial: max, sum and the unnormalised output per row (with one chunk, the
+  // output itself: the unnormalised output over the sum, as the merge computes it)
+  l += __shfl_xor(l, 16, kWave);
+  l += __shfl_xor(l, 32, kWave);
+  if constexpr (PW == 1) {
+    if (row < nr) {
+      float* dst = out != nullptr ? out + q_row(row) : po + ((rowbase + row) * nsplit + split) * hd;
+#pragma unroll
+      for (int t = 0; t < 2 * KS; ++t) {
+        const int c = 16 * t + 4 * g;
+        if (c < hd) {
+          const floatx4_t v = out != nullptr ? o[t] / l : o[t];
+          *reinterpret_cast<float4*>(dst + c) = make_float4(v[0], v[1], v[2], v[3]);
+        }
+      }
+      if (out == nullptr && g == 0) {
+        pm[(rowbase + row) * nsplit + split] = m;
+        pl[(rowbase + row) * nsplit + split] = l;
       }
     }
   } else {
-    // sum the position groups' shares in order through LDS (the value buffer is free)
-    float4* s_red = reinterpret_cast<float4*>(s_v);  // [group][block][4 rows]: <= 8 x 64 x 4
-    if (jgrp < jg) {
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) s_red[(jgrp * nob + job) * 4 + rr] = acc[0][rr];
+    // the PW position groups of each query tile, merged in order through LDS
+    if (g == 0) {
+      s_m[wave][fr] = m;
+      s_l[wave][fr] = l;
     }
     __syncthreads();
-    if (tid < nob) {
-      const int rb = tid / hd4, d4 = tid - rb * hd4;
+    float M = -INFINITY;
 #pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        float4 t = s_red[tid * 4 + rr];
-#pragma unroll 4
-        for (int g2 = 1; g2 < jg; ++g2) {
-          const float4 o = s_red[(g2 * nob + tid) * 4 + rr];
-          t.x += o.x;
-          t.y += o.y;
-          t.z += o.z;
-          t.w += o.w;
-        }
-        const int r = 4 * rb + rr;
-        if (r < nr && out != nullptr) {
-          const float l = s_l[r];
-          reinterpret_cast<float4*>(out_row(r))[d4] = make_float4(t.x / l, t.y / l, t.z / l, t.w / l);
-        } else if (r < nr) {
-          reinterpret_cast<float4*>(po + ((rowbase + r) * nsplit + split) * hd)[d4] = t;
+    for (int w = 0; w < PW; ++w) M = fmaxf(M, s_m[qt * PW + w][fr]);
+    const float f = m > -INFINITY ? expf(m - M) : 0.f;
+    float4* s_o = reinterpret_cast<float4*>(lds);  // [wave][row][kHd / 4], float4s swizzled by row
+#pragma unroll
+    for (int t = 0; t < 2 * KS; ++t)
+      s_o[(wave * 16 + fr) * (kHd / 4) + ((4 * t + g) ^ (fr & 7))] =
+          make_float4(o[t][0] * f, o[t][1] * f, o[t][2] * f, o[t][3] * f);
+    __syncthreads();
+    for (int e = tid; e < nr * (kHd / 4); e += kAttnThreads) {
+      const int r = e / (kHd / 4), c4 = e % (kHd / 4);
+      if (4 * c4 >= hd) continue;
+      const int w0 = (r >> 4) * PW, rr = r & 15;
+      float Mr = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < PW; ++w) Mr = fmaxf(Mr, s_m[w0 + w][rr]);
+      float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+      float lt = 0.f;
+#pragma unroll
+      for (int w = 0; w < PW; ++w) {
+        const float4 v = s_o[((w0 + w) * 16 + rr) * (kHd / 4) + (c4 ^ (rr & 7))];
+        t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+        const float mw = s_m[w0 + w][rr];
+        lt += mw > -INFINITY ? s_l[w0 + w][rr] * expf(mw - Mr) : 0.f;
+      }
+      if (out != nullptr) {
+        *reinterpret_cast<float4*>(out + q_row(r) + 4 * c4) = make_float4(t.x / lt, t.y / lt, t.z / lt, t.w / lt);
+      } else {
+        *reinterpret_cast<float4*>(po + ((rowbase + r) * nsplit + split) * hd + 4 * c4) = t;
+        if (c4 == 0) {
+          pm[(rowbase + r) * nsplit + split] = Mr;
+          pl[(rowbase + r) * nsplit + split] = lt;
         }
       }
     }
   }
 }
 
-// One workgroup (hd threads) per query row. Every thread requests its chunks' (max, sum) and
-// the first batch of chunk outputs of its column together, so the row costs about one
-// memory round trip; the maximum over the chunks, the weights exp(m_c - M) (one chunk per
-// thread, LDS) and the denominator follow, then each thread sums its output column over the
-// chunks in order, the next batch requested before the current one is added. Chunks with no
-// visible position never write their outputs: those are read but replaced by 0 (a select, so
-// whatever the buffer holds there cannot reach the sum). NB chunk outputs are requested per
-// batch: 8 when there are at most 8 chunks (the small decoder's), where unrolled guards for
-// more would cost more than they save; all of them, in one batch and one memory round trip,
-// up to 64 chunks (a 4096-row cache); else 32 per batch.
+// One workgroup (hd threads) per query row. Every thread requests its chunk's (max, sum) and
+// the chunk outputs of its column together, so the row costs about one memory round trip; the
+// maximum over the chunks, the weights exp(m_c - M) (one chunk per thread, LDS) and the
+// denominator follow, then each thread sums its output column over the chunks in order. Chunks with
+// no visible position never write their outputs: those are read but replaced by 0 (a select, so
+// whatever the buffer holds there cannot reach the sum). NB: chunks at most; unrolled guards for
+// more than there are cost more than they save.
 template <int NB>
 __device__ __forceinline__ void combine_row(int n, int H, int Hkv, int hd, int R, int nsplit,
                                             const float* __restrict__ pm,
@@ -446,65 +403,31 @@ __device__ __forceinline__ void combine_row(int n, int H, int Hkv, int hd, int R
   const int r = row % R, bk = row / R, kvh = bk % Hkv, b = bk / Hkv;
   const int G = H / Hkv, i = r / G, h = kvh * G + (r - i * G);
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-  const float* m = pm + (size_t)row * nsplit;
-  const float* l = pl + (size_t)row * nsplit;
   const float* o = po + (size_t)row * nsplit * hd + (tid < hd ? tid : 0);
-  constexpr bool kOneBatch = NB == kOneBatchMax;  // every chunk's output in the first batch
-  constexpr int kPer = kMaxSplits / kMaxHd;  // chunks per thread for the max and the weights
-  static_assert(kMaxSplits % kMaxHd == 0, "whole chunks per thread");
-  float mv[kPer], lv[kPer];
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int sp = tid + u * kMaxHd;
-    mv[u] = sp < nsplit ? m[sp] : -INFINITY;
-    lv[u] = sp < nsplit ? l[sp] : 0.f;
-  }
+  const float mv = tid < nsplit ? pm[(size_t)row * nsplit + tid] : -INFINITY;
+  const float lv = tid < nsplit ? pl[(size_t)row * nsplit + tid] : 0.f;
   float ov[NB];
 #pragma unroll
   for (int u = 0; u < NB; ++u) ov[u] = u < nsplit ? o[(size_t)u * hd] : 0.f;
 
-  float mx = -INFINITY;
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) mx = fmaxf(mx, mv[u]);
-  for (int k = 1; k < kWave; k <<= 1) mx = fmaxf(mx, __shfl_xor(mx, k, kWave));
-  if (lane == 0) s_red[wave] = mx;
-  __syncthreads();
-  float M = s_red[0];
-  for (int w = 1; w < kMaxHd / kWave; ++w) M = fmaxf(M, s_red[w]);
-  __syncthreads();
-  float den = 0.f;
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int sp = tid + u * kMaxHd;
-    if (sp < nsplit) {
-      const float w = (mv[u] > -INFINITY) ? expf(mv[u] - M) : 0.f;
-      s_w[sp] = w;
-      den = fmaf(lv[u], w, den);
-    }
+  static_assert(kMaxSplits <= kWave, "the chunks' sums and weights are the first wave's");
+  if (wave == 0) {
+    float M = mv;
+    for (int k = 1; k < kWave; k <<= 1) M = fmaxf(M, __shfl_xor(M, k, kWave));
+    const float w = (mv > -INFINITY) ? expf(mv - M) : 0.f;
+    float den = lv * w;
+    for (int k = 1; k < kWave; k <<= 1) den += __shfl_xor(den, k, kWave);
+    s_w[lane] = w;
+    if (lane == 0) s_red[0] = den;
   }
-  for (int k = 1; k < kWave; k <<= 1) den += __shfl_xor(den, k, kWave);
-  if (lane == 0) s_red[wave] = den;
   __syncthreads();
-  den = 0.f;
-  for (int w = 0; w < kMaxHd / kWave; ++w) den += s_red[w];
+  const float den = s_red[0];
   float num = 0.f;
-  for (int s0 = 0; s0 < nsplit; s0 += NB) {
-    float nx[NB];
-    const int s1 = s0 + NB;
-    if constexpr (!kOneBatch) {
 #pragma unroll
-      for (int u = 0; u < NB; ++u) nx[u] = s1 + u < nsplit ? o[(size_t)(s1 + u) * hd] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      if (s0 + u < nsplit) {
-        const float w = s_w[s0 + u];
-        num = fmaf(w > 0.f ? ov[u] : 0.f, w, num);
-      }
-    }
-    if constexpr (!kOneBatch) {
-#pragma unroll
-      for (int u = 0; u < NB; ++u) ov[u] = nx[u];
+  for (int u = 0; u < NB; ++u) {
+    if (u < nsplit) {
+      const float w = s_w[u];
+      num = fmaf(w > 0.f ? ov[u] : 0.f, w, num);
     }
   }
   if (tid < hd) out[(((size_t)b * n + i) * H + h) * hd + tid] = num / den;
@@ -513,13 +436,13 @@ __device__ __forceinline__ void combine_row(int n, int H, int Hkv, int hd, int R
 __global__ __launch_bounds__(kMaxHd) void attn_combine_kernel(
     int n, int H, int Hkv, int hd, int R, int nsplit, const float* __restrict__ pm,
     const float* __restrict__ pl, const float* __restrict__ po, float* __restrict__ out) {
-  __shared__ float s_w[kMaxSplits], s_red[kMaxHd / kWave];
+  __shared__ float s_w[kWave], s_red[1];
   if (nsplit <= 8)
     combine_row<8>(n, H, Hkv, hd, R, nsplit, pm, pl, po, out, s_w, s_red);
-  else if (nsplit <= kOneBatchMax)
-    combine_row<kOneBatchMax>(n, H, Hkv, hd, R, nsplit, pm, pl, po, out, s_w, s_red);
-  else
+  else if (nsplit <= 32)
     combine_row<32>(n, H, Hkv, hd, R, nsplit, pm, pl, po, out, s_w, s_red);
+  else
+    combine_row<kMaxSplits>(n, H, Hkv, hd, R, nsplit, pm, pl, po, out, s_w, s_red);
 }
 
 __global__ void kv_rollback_kernel(int32_t* __restrict__ cache_pos,
@@ -537,9 +460,14 @@ AttnLayout attn_layout(int B, int n, int H, int Hkv, int hd, int Lmax) {
   AttnLayout L{};
   const int R = (H / Hkv) * n;
   L.rgroups = ceil_div(R, kMaxRowsWg);
-  L.chunk = Lmax <= kDirectMax ? ceil_div(Lmax, kTile) * kTile
-                               : kTile * std::max(1, ceil_div(ceil_div(Lmax, kTile), kMaxSplits));
-  L.nsplit = ceil_div(Lmax, L.chunk);
+  const long wgs = (long)std::max(B, 1) * Hkv * L.rgroups;
+  // Two workgroups per CU (512 in all): with 256, 1024 and 2048 the 16-token chunks of 8 sequences
+  // took 95, 82 and 99 us against 78, 16 decoded tokens 41, 38 and 44 against 36; and no more chunks
+  // than a full cache has tiles.
+  const int tile = R <= 16 || hd <= 64 ? 128 : 64;
+  L.nsplit = Lmax <= kDirectMax ? 1
+                                : (int)std::max(1l, std::min<long>({(kTargetWgs + wgs - 1) / wgs,
+                                                                    (long)ceil_div(Lmax, tile), (long)kMaxSplits}));
   const size_t rows = (size_t)B * Hkv * R;
   Carve c;
   L.pm = c.take(rows * L.nsplit * sizeof(float));
@@ -563,16 +491,21 @@ hipError_t launch_attn_kv(const float* q, const uint16_t* k_new, const uint16_t*
   const bool direct = L.nsplit == 1;  // the partial kernel writes the output; no merge
   {
     ProfScope prof("attn_partial", stream);
-    if (R > 16)
-      klaunch(attn_partial_kernel<true>, grid, kAttnThreads, 0, stream, 
-          q, reinterpret_cast<const uint4*>(k_new), reinterpret_cast<const uint4*>(v_new),
-          reinterpret_cast<uint4*>(k_cache), reinterpret_cast<uint4*>(v_cache), cache_pos, n, H,
-          Hkv, hd, Lmax, L.chunk, L.rgroups, R, scale, pm, pl, po, direct ? out : nullptr);
-    else
-      klaunch(attn_partial_kernel<false>, grid, kAttnThreads, 0, stream, 
-          q, reinterpret_cast<const uint4*>(k_new), reinterpret_cast<const uint4*>(v_new),
-          reinterpret_cast<uint4*>(k_cache), reinterpret_cast<uint4*>(v_cache), cache_pos, n, H,
-          Hkv, hd, Lmax, L.chunk, L.rgroups, R, scale, pm, pl, po, direct ? out : nullptr);
+#define SIRIUS_ATTN(KS, QW, NB)                                                                       \
+  klaunch(attn_partial_kernel<KS, QW, NB>, grid, kAttnThreads, 0, stream, q,                          \
+          reinterpret_cast<const uint4*>(k_new), reinterpret_cast<const uint4*>(v_new),               \
+          reinterpret_cast<uint4*>(k_cache), reinterpret_cast<uint4*>(v_cache), cache_pos, n, H, Hkv, \
+          hd, Lmax, L.rgroups, R, scale, pm, pl, po, direct ? out : nullptr)
+    if (hd <= 64) {
+      if (R <= 16) SIRIUS_ATTN(2, 1, 1);
+      else if (R <= 32) SIRIUS_ATTN(2, 2, 2);
+      else SIRIUS_ATTN(2, 4, 4);
+    } else {
+      if (R <= 16) SIRIUS_ATTN(4, 1, 1);
+      else if (R <= 32) SIRIUS_ATTN(4, 2, 1);
+      else SIRIUS_ATTN(4, 4, 2);
+    }
+#undef SIRIUS_ATTN
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -204,7 +204,7 @@ hipError_t launch_tree_build(const float* logits, int B, int Wc, int V, const fl
 
 // ---- attention over the shared KV cache with the direct rewrite, and the rollback
 struct AttnLayout {
-  int rgroups, chunk, nsplit;    // query-row groups per kv head, positions per chunk, chunks
+  int rgroups, nsplit;           // query-row groups per kv head, chunks of the visible rows
   size_t pm, pl, po, total;      // per-chunk partials: max, sum, output
 };
 AttnLayout attn_layout(int B, int n, int H, int Hkv, int hd, int Lmax);
