@@ -3,9 +3,9 @@
 //  griffin_z_kernel       z[t, i] = SiLU(x_t . W_gate[i]) * (x_t . W_up[i]) for the
 //                         T prompt tokens: both products in one MFMA pass
 //                         (v_mfma_f32_16x16x32_bf16, exact bf16 products, fp32
-//                         accumulation). Workgroup tile 256 tokens x 112 neurons (eight
-//                         waves of 64 x 56, two per SIMD, one workgroup per CU: the 256
-//                         tiles of a 512-token prompt at d_ff = 14336 fill the chip once),
+//                         accumulation). Workgroup tiles of 64 to 256 tokens x 64 or 112
+//                         neurons (eight waves, two per SIMD, one workgroup per CU), chosen
+//                         by the rounds of 256 tiles that a prompt makes of them,
 //                         K through a five-slot LDS ring of 32-wide stages filled by direct
 //                         global-to-LDS loads, the next stage's operands read while the
 //                         current one is multiplied; the token tiles of a neuron tile run on
@@ -37,27 +37,26 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4_t;
 constexpr int kTopkThreads = 1024;
 constexpr int kTopkPer = 64;       // scores per top-k thread at most: d_ff <= 65536
 
-// griffin_z tile: 256 tokens x 112 neurons, both products (224 output columns), eight waves of
-// 64 tokens x 56 neurons each (4 x 2), one workgroup (two waves per SIMD) per CU.
-constexpr int kZT = 256;                  // tokens per workgroup tile
-constexpr int kZN = 112;                  // neurons per workgroup tile
-constexpr int kZWT = 64;                  // tokens per wave
-constexpr int kZWB = 7;                   // column blocks per wave: 7 x (8 gate + 8 up columns)
-constexpr int kZMB = kZWT / 16;           // 16-token blocks per wave
+// griffin_z: eight waves (4 token groups x 2 neuron halves) of 16 MB tokens x 8 WB neurons, both
+// products (gate and up columns alternate), one workgroup (two waves per SIMD) per CU.
 constexpr int kZThreads = 512;
 constexpr int kZK = 32;                   // K per ring stage: one 64-byte LDS row per token or weight row
-constexpr int kZRowsW = 2 * kZN;          // 224 weight rows per stage (gate and up, interleaved by 8)
-constexpr int kZRows = kZT + kZRowsW;     // 480 rows per stage
-constexpr int kZSlotBytes = kZRows * 64;  // 30 KiB per stage
-constexpr int kZSlots = 5;                // ring depth: four stages in flight while one is multiplied
-constexpr int kZPieces = kZRows * 4;      // 16-byte pieces per stage: 1920
-// direct loads per thread per stage: pieces q * 512 + tid for q = 0..3; the fourth exists for
-// the first 384 threads only (waves 0..5), so the per-wave load count is 4 or 3 (wave-uniform)
-constexpr int kZLoads = (kZPieces + kZThreads - 1) / kZThreads;
-constexpr int kZFullWaves = (kZPieces - (kZLoads - 1) * kZThreads) / kWave;
-static_assert(kZLoads == 4 && kZFullWaves == 6, "the ring's wait counts assume four or three loads per thread");
-static_assert(kZSlots * kZSlotBytes <= 160 * 1024, "the ring fits in LDS");
-static_assert(kZSlots <= 5, "wait_later counts at most four later stages");
+template <int MB, int WB>
+struct ZTile {
+  static constexpr int kT = 64 * MB;                  // tokens per workgroup tile
+  static constexpr int kN = 16 * WB;                  // neurons per workgroup tile
+  static constexpr int kRows = kT + 2 * kN;           // LDS rows per stage (weights: gate and up)
+  static constexpr int kSlotBytes = kRows * 64;
+  static constexpr int kFit = 156 * 1024 / kSlotBytes;
+  static constexpr int kSlots = kFit < 5 ? kFit : 5;  // ring depth: one stage multiplied, the others in flight
+  static constexpr int kPieces = kRows * 4;           // 16-byte pieces per stage
+  // direct loads per thread per stage: pieces q * 512 + tid; the last exists for the first
+  // kFullWaves waves only, so the per-wave load count is wave-uniform
+  static constexpr int kLoads = (kPieces + kZThreads - 1) / kZThreads;
+  static constexpr int kFullWaves = (kPieces - (kLoads - 1) * kZThreads) / kWave;
+  static_assert(kPieces % kWave == 0 && kSlots >= 3, "whole waves of pieces, two stages in flight");
+};
+constexpr int kZMinT = 64;  // tokens of the smallest tile
 
 __device__ __forceinline__ int ceil_div_dev(int a, int b) { return (a + b - 1) / b; }
 
@@ -101,8 +100,8 @@ __device__ __forceinline__ float z_silu(float g) {
 // the gate row of neuron n0 + 8j + p, row 2p + 1 its up row. A lane of a 16 x 16 result holds
 // four consecutive rows of one token column, so it holds the gate and up products of two
 // neurons side by side: every lane forms z from its own registers. Wave (wm, wn) multiplies
-// weight blocks 7 wn .. + 6 by token rows 64 wm .. + 63: 7 x 4 v_mfma_f32_16x16x32_bf16 per K
-// stage into 112 fp32 accumulators per lane. The two waves of a SIMD take turns on its MFMA
+// weight blocks WB wn .. by token rows 16 MB wm ..: WB x MB v_mfma_f32_16x16x32_bf16 per K
+// stage into 112 fp32 accumulators per lane at the largest tile. The two waves of a SIMD take turns on its MFMA
 // unit.
 //
 // K goes through a five-slot LDS ring of 32-wide stages (30 KiB each) filled by direct
@@ -115,10 +114,15 @@ __device__ __forceinline__ float z_silu(float g) {
 //
 // Rows past T or d_ff load a valid row (T - 1, d_ff - 1) whose products are never used; in a K
 // tail (d_model % 32 != 0) the chunks past d_model are loaded from a block of zeros.
+template <int MB, int WB>
 __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void griffin_z_kernel(
     const uint16_t* __restrict__ X, int T, const uint16_t* __restrict__ Wg,
     const uint16_t* __restrict__ Wu, int d, int F, float* __restrict__ Z,
     double* __restrict__ part) {
+  using G = ZTile<MB, WB>;
+  constexpr int kZT = G::kT, kZN = G::kN, kZWT = 16 * MB, kZWB = WB, kZMB = MB;
+  constexpr int kZSlots = G::kSlots, kZSlotBytes = G::kSlotBytes, kZPieces = G::kPieces;
+  constexpr int kZLoads = G::kLoads, kZFullWaves = G::kFullWaves;
   __shared__ __attribute__((aligned(16))) unsigned char s_ring[kZSlots * kZSlotBytes];
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
@@ -304,11 +308,18 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
 
 __global__ __launch_bounds__(256) void griffin_rownorm_kernel(const float* __restrict__ Z, int F,
                                                               float* __restrict__ rn2) {
+  constexpr int kAhead = 8;  // loads in flight per thread
   __shared__ double s_w[4];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const float* zr = Z + (size_t)blockIdx.x * F;
   double s = 0.0;
-  for (int i = tid; i < F; i += 256) s += (double)zr[i] * (double)zr[i];
+  for (int i0 = tid; i0 < F; i0 += 256 * kAhead) {
+    float z[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) z[u] = i0 + 256 * u < F ? zr[i0 + 256 * u] : 0.f;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) s += (double)z[u] * (double)z[u];
+  }
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m, kWave);
   if (lane == 0) s_w[wave] = s;
@@ -316,22 +327,38 @@ __global__ __launch_bounds__(256) void griffin_rownorm_kernel(const float* __res
   if (tid == 0) rn2[blockIdx.x] = (float)(((s_w[0] + s_w[1]) + s_w[2]) + s_w[3]);
 }
 
-__global__ __launch_bounds__(256) void griffin_score_kernel(const float* __restrict__ Z, int T,
-                                                            int F, const float* __restrict__ rn2,
-                                                            float* __restrict__ scores) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= F) return;
+// s_i = sqrt(sum_t z_ti^2 / ||z_t||^2): 64 neurons per workgroup, wave w takes tokens w, w + 16, ..
+// in order, eight loads in flight, the 16 sums added in wave order. (One thread per neuron over
+// all tokens, one load in flight: 95 us for 284 x 6016 values, now 9.)
+constexpr int kScoreThreads = 1024;
+__global__ __launch_bounds__(kScoreThreads) void griffin_score_kernel(const float* __restrict__ Z, int T,
+                                                                      int F, const float* __restrict__ rn2,
+                                                                      float* __restrict__ scores) {
+  constexpr int kAhead = 8, kW = kScoreThreads / kWave;
+  __shared__ double s_sum[kW][kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+  const int i = blockIdx.x * kWave + lane;
   double s = 0.0;
-  for (int t = 0; t < T; ++t) {
-    const double z = (double)Z[(size_t)t * F + i];
-    if (rn2 == nullptr) {
-      s += z * z;
-    } else {
-      const double n2 = (double)rn2[t];
-      if (n2 > 0.0) s += z * z / n2;
+  if (i < F) {
+    for (int t0 = wave; t0 < T; t0 += kW * kAhead) {
+      float z[kAhead], n2[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int t = t0 + kW * u;
+        z[u] = t < T ? Z[(size_t)t * F + i] : 0.f;
+        n2[u] = t < T ? rn2[t] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (n2[u] > 0.f) s += (double)z[u] * (double)z[u] / (double)n2[u];
     }
   }
-  scores[i] = (float)sqrt(s);
+  s_sum[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && i < F) {
+    for (int w = 1; w < kW; ++w) s += s_sum[w][lane];
+    scores[i] = (float)sqrt(s);
+  }
 }
 
 // s_i = sqrt(sum over the token tiles, in order, of the tile sums of z^2): the plain
@@ -458,13 +485,44 @@ __global__ __launch_bounds__(256) void condense_kernel(const uint4* __restrict__
 
 }  // namespace
 
+namespace {
+
+// Tiles of griffin_z and the time of a round of 256 of them (one per CU) at d_model = 4096, in us:
+// a prompt takes the tile whose rounds cost least. A round that fills part of the chip costs less
+// than a whole one but not in proportion (half of the 256 x 112 tiles: 0.64 of it). 700 tokens at
+// d_ff = 14336 (1.5 rounds of the largest tile): 226 us with it, 210 with 192-token tiles in two
+// rounds; 1000 at 8192 (d_model 3072): 175 and 135 (256 x 64); 68 at 7424: 81 and 44 (128 x 64).
+struct ZTileCost {
+  int mb, wb;
+  float us;
+};
+constexpr ZTileCost kZTiles[] = {{4, 7, 136.f}, {3, 7, 103.5f}, {2, 7, 86.f},   {1, 7, 64.4f},
+                                 {4, 4, 87.9f}, {3, 4, 75.4f},  {2, 4, 60.6f}, {1, 4, 48.7f}};
+
+int z_tile_of(int T, int F) {
+  int best = 0;
+  float best_us = 0.f;
+  for (int i = 0; i < (int)(sizeof(kZTiles) / sizeof(kZTiles[0])); ++i) {
+    const float rounds = (float)ceil_div(T, 64 * kZTiles[i].mb) * ceil_div(F, 16 * kZTiles[i].wb) / 256.f;
+    const float whole = floorf(rounds), part = rounds - whole;
+    const float us = kZTiles[i].us * (whole + (part > 0.f ? 0.4f + 0.6f * part : 0.f));
+    if (i == 0 || us < best_us) {
+      best = i;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
 GriffinLayout griffin_layout(int T, int d, int F) {
   (void)d;
   GriffinLayout L{};
   Carve c;
   L.z = c.take((size_t)T * F * sizeof(float));  // used by the normalised variant only
   L.rownorm = c.take((size_t)T * sizeof(float));
-  L.part = c.take((size_t)ceil_div(T, kZT) * F * sizeof(double));
+  L.part = c.take((size_t)ceil_div(T, kZMinT) * F * sizeof(double));
   L.scores = c.take((size_t)F * sizeof(float));
   L.total = c.off;
   return L;
@@ -479,11 +537,28 @@ hipError_t launch_griffin(const uint16_t* xp, int T, const uint16_t* wg, const u
   float* rn2 = reinterpret_cast<float*>(ws + L.rownorm);
   double* part = reinterpret_cast<double*>(ws + L.part);
   float* scores = reinterpret_cast<float*>(ws + L.scores);
-  const int ntn = ceil_div(F, kZN), ntm = ceil_div(T, kZT);
   hipError_t e;
+  const int tile = z_tile_of(T, F);
+  const int ntm = ceil_div(T, 64 * kZTiles[tile].mb);
   {
     ProfScope prof("griffin_z", stream);
-    klaunch(griffin_z_kernel, ntn * ntm, kZThreads, 0, stream, xp, T, wg, wu, d, F, Z, part);
+    const int grid = ntm * ceil_div(F, 16 * kZTiles[tile].wb);
+#define SIRIUS_Z(I, MB, WB)                                                                        \
+  case I:                                                                                          \
+    static_assert(kZTiles[I].mb == MB && kZTiles[I].wb == WB, "tile table");                       \
+    klaunch((griffin_z_kernel<MB, WB>), grid, kZThreads, 0, stream, xp, T, wg, wu, d, F, Z, part); \
+    break;
+    switch (tile) {
+      SIRIUS_Z(0, 4, 7)
+      SIRIUS_Z(1, 3, 7)
+      SIRIUS_Z(2, 2, 7)
+      SIRIUS_Z(3, 1, 7)
+      SIRIUS_Z(4, 4, 4)
+      SIRIUS_Z(5, 3, 4)
+      SIRIUS_Z(6, 2, 4)
+      SIRIUS_Z(7, 1, 4)
+    }
+#undef SIRIUS_Z
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   float* sc = scores_out != nullptr ? scores_out : scores;
@@ -494,7 +569,7 @@ hipError_t launch_griffin(const uint16_t* xp, int T, const uint16_t* wg, const u
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     ProfScope prof("griffin_score", stream);
-    klaunch(griffin_score_kernel, ceil_div(F, 256), 256, 0, stream, Z, T, F, rn2, sc);
+    klaunch(griffin_score_kernel, ceil_div(F, kWave), kScoreThreads, 0, stream, Z, T, F, rn2, sc);
   } else {
     ProfScope prof("griffin_score", stream);
     klaunch(griffin_tile_score_kernel, ceil_div(F, 256), 256, 0, stream, part, ntm, F, sc);
