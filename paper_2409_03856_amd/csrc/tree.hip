@@ -9,19 +9,21 @@
 // ascending): the logit's bits mapped to an order-preserving unsigned value above the
 // complemented token id. Keys of one row are distinct; 0 marks an empty entry.
 //
-//  tree_topw_kernel    grid (splits, B * Wc): each workgroup reads one segment of one leaf's
-//                      logit row once, in passes of 4096 with each thread holding a contiguous
-//                      run of 16 logits (all loads in flight), keeping the running softmax
-//                      statistics (max, sum of exp((v - max) / T) in fp64). The threads form G
-//                      interleaved groups (G the power of two at or above W); the pass's W
-//                      best are at least the W-th largest group maximum, so only the keys at
-//                      or above that bound (usually a handful) are gathered and ranked by
-//                      counting together with the running W best.
-//  tree_select_kernel  one 1024-thread workgroup per tree, one wave per leaf and one lane per
-//                      segment: the segment statistics merge in a fixed butterfly order into
-//                      log-likelihood (v - max) / T - log(sum), W rounds of a DPP wave maximum
-//                      over the segment lists' heads give the leaf's W best tokens, and the
-//                      Wc x W scored candidates are ranked by counting.
+//  tree_topw_kernel    grid (segments, B * Wc): each workgroup reads one segment of 2048 or 4096
+//                      logits of one leaf's row, every thread a contiguous run of 8 or 16 (all
+//                      loads in flight). W rounds of a DPP wave maximum over the lanes' largest
+//                      remaining values give each wave's W best (the lowest lane wins a tie, so
+//                      the lowest token does); one wave ranks the four lists by counting. The
+//                      softmax statistics (max, sum of exp((v - max) / T) in fp64) merge on the
+//                      common maximum.
+//  tree_select_kernel  one workgroup per tree, one wave per leaf: the segment statistics merge on
+//                      the common maximum into log-likelihood (v - max) / T - log(sum), W rounds of
+//                      a DPP wave maximum over the segment lists' heads give the leaf's W best
+//                      tokens, and the Wc x W scored candidates are ranked by counting.
+//
+// Bound: two launches of short dependent chains (a 4 x 128256 step reads 2 MB). Lists are as long
+// as the class of W (4, 8 or 16), so that a narrow tree pays for its own width only: 5.2 and 4.8 us there (8.9 and
+// 8.9 with lists of 16, per-pass group bounds and a merge of the statistics per butterfly step).
 #include <math.h>
 
 #include "common.h"
@@ -33,12 +35,9 @@ namespace sirius {
 namespace {
 
 constexpr int kTopThreads = 256;
-constexpr int kElems = 16;  // contiguous logits per thread per pass (the stats sum assumes 16)
-constexpr int kPassElems = kTopThreads * kElems;   // 4096 logits per workgroup pass
-constexpr int kKW = 16;          // tree width and current-leaf limit (list length in registers)
-constexpr int kMaxSplits = 64;   // segments per leaf row at most (one lane each in the select)
-constexpr int kSelThreads = 1024;
-constexpr int kRankBatch = 16;   // LDS reads in flight per step of a rank-by-counting loop
+constexpr int kTopWaves = kTopThreads / kWave;
+constexpr int kKW = 16;          // tree width and current-leaf limit
+constexpr int kShortRow = 64 * kTopThreads * 8;  // rows of at most 64 segments of 8 logits per thread
 
 __device__ __forceinline__ uint32_t ordered_bits(float v) {
   const uint32_t u = __float_as_uint(v);
@@ -53,12 +52,6 @@ __device__ __forceinline__ uint64_t make_key(float v, int i) {
 }
 __device__ __forceinline__ int key_token(uint64_t k) { return (int)(~(uint32_t)k); }
 __device__ __forceinline__ float key_value(uint64_t k) { return from_ordered((uint32_t)(k >> 32)); }
-
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
-  const uint32_t lo = __shfl_xor((uint32_t)v, m, kWave);
-  const uint32_t hi = __shfl_xor((uint32_t)(v >> 32), m, kWave);
-  return ((uint64_t)hi << 32) | lo;
-}
 
 // v = max(v, v moved by one DPP step); rows outside ROWS keep v
 template <int CTRL, int ROWS>
@@ -85,225 +78,210 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// running softmax statistics, merged to the larger max
-__device__ __forceinline__ void sm_merge(float& m, double& s, float om, double os, float c) {
-  const float mm = fmaxf(m, om);
-  double ns = 0.0;
-  if (s > 0.0) ns += s * (double)exp2f((m - mm) * c);
-  if (os > 0.0) ns += os * (double)exp2f((om - mm) * c);
-  m = mm;
-  s = ns;
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t max_dpp32(uint32_t v) {
+  const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xf, false);
+  return o > v ? o : v;
 }
 
+// The same for 32-bit values.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  v = max_dpp32<0xB1, 0xF>(v);
+  v = max_dpp32<0x4E, 0xF>(v);
+  v = max_dpp32<0x124, 0xF>(v);
+  v = max_dpp32<0x128, 0xF>(v);
+  v = max_dpp32<0x142, 0xA>(v);
+  v = max_dpp32<0x143, 0xC>(v);
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Softmax statistics of 64 lanes: the common maximum, and the sums brought to it and added in a
+// fixed butterfly order. A sum of 0 is an empty part (its maximum is -infinity or irrelevant).
+__device__ __forceinline__ void wave_stats(float& m, double& s, float c) {
+  float mm = m;
+#pragma unroll
+  for (int k = 1; k < kWave; k <<= 1) mm = fmaxf(mm, __shfl_xor(mm, k, kWave));
+  double t = s > 0.0 ? s * (double)exp2f((m - mm) * c) : 0.0;
+#pragma unroll
+  for (int k = 1; k < kWave; k <<= 1) t += __shfl_xor(t, k, kWave);
+  m = mm;
+  s = t;
+}
+
+typedef float f32x4_unaligned_t __attribute__((ext_vector_type(4), aligned(4)));
+
+// E logits per thread; lists of KW entries (W <= KW).
+template <int E, int KW>
 __global__ __launch_bounds__(kTopThreads) void tree_topw_kernel(
-    const float* __restrict__ logits, int V, int seg, int W, float c, float* __restrict__ rm,
+    const float* __restrict__ logits, int V, int W, float c, float* __restrict__ rm,
     double* __restrict__ rs, uint64_t* __restrict__ rk) {
-  // [0, kKW): the running W best (0 = empty); from kKW: this pass's entrants
-  __shared__ uint64_t s_cand[kKW + kPassElems + kRankBatch];
-  __shared__ uint64_t s_g[(kTopThreads / kWave) * kKW];  // group maxima per wave
-  __shared__ uint64_t s_new[kKW];
-  __shared__ uint64_t s_bound;
-  __shared__ float s_m[kTopThreads / kWave];
-  __shared__ double s_s[kTopThreads / kWave];
-  __shared__ int s_scan[kTopThreads / kWave];
+  __shared__ uint64_t s_c[kTopWaves * KW];
+  __shared__ float s_m[kTopWaves];
+  __shared__ double s_s[kTopWaves];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int split = blockIdx.x, row = blockIdx.y, splits = gridDim.x;
-  const int lo = split * seg, hi = min(V, lo + seg);
+  const int e0 = split * kTopThreads * E + tid * E;
   const float* L = logits + (size_t)row * V;
-  int G = 1;
-  while (G < W) G <<= 1;
-
+  float v[E];
+  if (e0 + E <= V) {
+    // the row starts on a 16-byte boundary only when V % 4 == 0: loads of four with 4-byte alignment
+#pragma unroll
+    for (int g = 0; g < E / 4; ++g) {
+      const f32x4_unaligned_t x = *reinterpret_cast<const f32x4_unaligned_t*>(L + e0 + 4 * g);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[4 * g + j] = x[j];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[j] = (e0 + j < V) ? L[e0 + j] : -INFINITY;
+  }
+  if (tid < kTopWaves * KW) s_c[tid] = 0;
+  // softmax statistics of the thread: exps summed pairwise in fp32 (at most 16 terms, each <= 1)
   float m = -INFINITY;
-  double s = 0.0;
-  if (tid < kKW) s_cand[tid] = 0;
-  uint64_t run_w = 0;  // the running W-th best key (0 while fewer than W)
-
-  for (int base = lo; base < hi; base += kPassElems) {
-    const int e0 = base + tid * kElems;
-    float v[kElems];
-    if ((V & 3) == 0) {  // seg is a multiple of 4, so e0 and hi are too: whole float4s
-      const float4* L4 = reinterpret_cast<const float4*>(L + e0);
 #pragma unroll
-      for (int g = 0; g < kElems / 4; ++g) {
-        const float4 x = (e0 + 4 * g < hi) ? ld_stream(L4 + g)
-                                           : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-        v[4 * g] = x.x;
-        v[4 * g + 1] = x.y;
-        v[4 * g + 2] = x.z;
-        v[4 * g + 3] = x.w;
-      }
-    } else {
+  for (int j = 0; j < E; ++j) m = fmaxf(m, v[j]);
+  float t[E / 4];
 #pragma unroll
-      for (int j = 0; j < kElems; ++j) v[j] = (e0 + j < hi) ? L[e0 + j] : -INFINITY;
-    }
-    // softmax statistics, one rescale per pass
-    float cm = m;
+  for (int g = 0; g < E / 4; ++g)
+    t[g] = (exp2_nonpos((v[4 * g] - m) * c) + exp2_nonpos((v[4 * g + 1] - m) * c)) +
+           (exp2_nonpos((v[4 * g + 2] - m) * c) + exp2_nonpos((v[4 * g + 3] - m) * c));
 #pragma unroll
-    for (int j = 0; j < kElems; ++j) cm = fmaxf(cm, v[j]);
-    float t[kElems / 4];  // the pass's exps, summed pairwise in fp32 (16 terms, each <= 1)
+  for (int k = 1; k < E / 4; k <<= 1)
 #pragma unroll
-    for (int g = 0; g < kElems / 4; ++g)
-      t[g] = (exp2_nonpos((v[4 * g] - cm) * c) + exp2_nonpos((v[4 * g + 1] - cm) * c)) +
-             (exp2_nonpos((v[4 * g + 2] - cm) * c) + exp2_nonpos((v[4 * g + 3] - cm) * c));
-    double cs = (s > 0.0) ? s * (double)exp2_nonpos((m - cm) * c) : 0.0;
-    if (cm > -INFINITY) cs += (double)((t[0] + t[1]) + (t[2] + t[3]));  // -inf logits add nothing
-    m = cm;
-    s = cs;
-    // keys; the largest key of each of G thread groups (group = thread index mod G, G the
-    // power of two at or above W)
-    uint64_t key[kElems];
-    uint64_t gk = 0;
+    for (int g = 0; g < E / 4; g += 2 * k) t[g] += t[g + k];
+  double s = m > -INFINITY ? (double)t[0] : 0.0;  // -inf logits add nothing
+  uint32_t o[E], lm = 0;
 #pragma unroll
-    for (int j = 0; j < kElems; ++j) {
-      key[j] = (e0 + j < hi) ? make_key(v[j], e0 + j) : 0;
-      gk = key[j] > gk ? key[j] : gk;
-    }
-    for (int k = G; k < kWave; k <<= 1) {
-      const uint64_t o = shfl_xor_u64(gk, k);
-      gk = o > gk ? o : gk;
-    }
-    if (lane < G) s_g[wave * kKW + lane] = gk;
-    if (tid == 0) s_bound = 0;
-    if (tid < kKW) s_new[tid] = 0;
-    __syncthreads();
-    // bound: the W-th largest group maximum (W groups hold a key at least that large, so the
-    // pass's W best are too), or the running W-th best if larger
-    if (tid < G) {
-      uint64_t gm[kKW];
-#pragma unroll
-      for (int g = 0; g < kKW; ++g) {
-        uint64_t x = 0;
-#pragma unroll
-        for (int w = 0; w < kTopThreads / kWave; ++w) {
-          const uint64_t y = s_g[w * kKW + g];
-          x = y > x ? y : x;
-        }
-        gm[g] = g < G ? x : 0;
-      }
-      uint64_t mine = 0;
-#pragma unroll
-      for (int g = 0; g < kKW; ++g) mine = g == tid ? gm[g] : mine;
-      int r = 0;
-#pragma unroll
-      for (int g = 0; g < kKW; ++g) r += gm[g] > mine;
-      if (mine != 0 && r == W - 1) s_bound = mine;
-    }
-    __syncthreads();
-    const uint64_t bound = s_bound > run_w ? s_bound : run_w;
-    int n = 0;
-#pragma unroll
-    for (int j = 0; j < kElems; ++j) n += (key[j] != 0 && key[j] >= bound);
-    int total = 0;
-    int pos = kKW + block_exclusive_scan_256(n, s_scan, &total);
-#pragma unroll
-    for (int j = 0; j < kElems; ++j)
-      if (key[j] != 0 && key[j] >= bound) s_cand[pos++] = key[j];
-    const int ncand = kKW + total;
-    const int npad = (ncand + kRankBatch - 1) / kRankBatch * kRankBatch;
-    if (tid < npad - ncand) s_cand[ncand + tid] = 0;  // empty: never counted as larger
-    __syncthreads();
-    // the new running best: rank every candidate by counting (non-empty keys are distinct)
-    for (int i = tid; i < ncand; i += kTopThreads) {
-      const uint64_t k0 = s_cand[i];
-      int r = 0;
-      for (int j = 0; j < npad; j += kRankBatch) {
-        uint64_t buf[kRankBatch];
-#pragma unroll
-        for (int q = 0; q < kRankBatch; ++q) buf[q] = s_cand[j + q];
-#pragma unroll
-        for (int q = 0; q < kRankBatch; ++q) r += (int)(buf[q] > k0);
-      }
-      if (k0 != 0 && r < W) s_new[r] = k0;
-    }
-    __syncthreads();
-    if (tid < kKW) s_cand[tid] = s_new[tid];
-    run_w = s_new[W - 1];
-    __syncthreads();
+  for (int j = 0; j < E; ++j) {
+    o[j] = (e0 + j < V) ? ordered_bits(v[j]) : 0u;
+    lm = o[j] > lm ? o[j] : lm;
   }
-
-  // softmax statistics: butterfly within the wave, then the four waves in order
+  __syncthreads();
+  // the wave's W best, best first
+  for (int r = 0; r < W; ++r) {
+    const uint32_t best = wave_max_u32(lm);
+    if (best == 0u) break;  // uniform: nothing left
+    const bool win = lane == __builtin_ctzll(__ballot(lm == best));
+    int jj = 0;
 #pragma unroll
-  for (int k = 1; k < kWave; k <<= 1) {
-    const float om = __shfl_xor(m, k, kWave);
-    const double os = __shfl_xor(s, k, kWave);
-    sm_merge(m, s, om, os, c);
+    for (int j = E - 1; j >= 0; --j) jj = o[j] == best ? j : jj;
+    if (win) s_c[wave * KW + r] = ((uint64_t)best << 32) | (uint64_t)(~(uint32_t)(e0 + jj));
+    uint32_t next = 0;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      o[j] = (win && j == jj) ? 0u : o[j];
+      next = o[j] > next ? o[j] : next;
+    }
+    lm = next;
   }
+  wave_stats(m, s, c);
   if (lane == 0) {
     s_m[wave] = m;
     s_s[wave] = s;
   }
   __syncthreads();
-  const size_t o = (size_t)row * splits + split;
-  if (tid == 0) {
-    float am = s_m[0];
-    double as = s_s[0];
-    for (int w = 1; w < kTopThreads / kWave; ++w) sm_merge(am, as, s_m[w], s_s[w], c);
-    rm[o] = am;
-    rs[o] = as;
+  if (wave != 0) return;
+  const size_t at = (size_t)row * splits + split;
+  // rank the four lists by counting (non-empty keys are distinct)
+  constexpr int kN = kTopWaves * KW;
+  const uint64_t key = lane < kN ? s_c[lane] : 0;
+  int rank = 0, n = 0;
+#pragma unroll
+  for (int i = 0; i < kN; ++i) {
+    const uint64_t k = s_c[i];
+    rank += (int)(k > key);
+    n += (int)(k != 0);
   }
-  if (tid < W) rk[o * kKW + tid] = s_cand[tid];
+  if (key != 0 && rank < W) rk[at * KW + rank] = key;
+  if (lane >= n && lane < KW) rk[at * KW + lane] = 0;
+  if (lane < KW && lane >= W) rk[at * KW + lane] = 0;
+  if (lane == 0) {
+    float am = s_m[0];
+#pragma unroll
+    for (int w = 1; w < kTopWaves; ++w) am = fmaxf(am, s_m[w]);
+    double as = 0.0;
+#pragma unroll
+    for (int w = 0; w < kTopWaves; ++w)
+      if (s_s[w] > 0.0) as += s_s[w] * (double)exp2f((s_m[w] - am) * c);
+    rm[at] = am;
+    rs[at] = as;
+  }
 }
 
-__global__ __launch_bounds__(kSelThreads) void tree_select_kernel(
+template <int KW>
+__global__ __launch_bounds__(kKW * kWave) void tree_select_kernel(
     int Wc, int W, int splits, float c, float inv_t, const float* __restrict__ rm,
     const double* __restrict__ rs, const uint64_t* __restrict__ rk,
     const float* __restrict__ cum_in, int32_t* __restrict__ tokens, int32_t* __restrict__ parents,
     float* __restrict__ cum_out) {
-  __shared__ double s_sc[kKW * kKW];  // each leaf's W best, scored: [leaf][rank]
-  __shared__ int s_tk[kKW * kKW];
+  __shared__ double s_sc[kKW * KW];  // each leaf's W best, scored: [leaf][rank]
+  __shared__ int s_tk[kKW * KW];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int b = blockIdx.x;
-  if (wave < Wc) {  // one wave per leaf, one lane per split
+  {  // one wave per leaf, one lane per segment (segments lane, lane + 64, ..)
     const size_t row = (size_t)b * Wc + wave;
-    const bool has = lane < splits;
-    uint64_t lst[kKW];  // the lane's split list, best first (0 = empty)
+    const uint64_t* lists = rk + row * splits * KW;
+    uint64_t lst[KW];  // the lane's best, best first (0 = empty)
 #pragma unroll
-    for (int p = 0; p < kKW; ++p)
-      lst[p] = (has && p < W) ? rk[(row * splits + lane) * kKW + p] : 0;
-    float m = has ? rm[row * splits + lane] : -INFINITY;
-    double s = has ? rs[row * splits + lane] : 0.0;
-    const float base = (cum_in != nullptr && lane == 0) ? cum_in[row] : 0.f;
-    // statistics of the leaf row: butterfly merge in a fixed order
+    for (int p = 0; p < KW; ++p) lst[p] = lane < splits ? lists[(size_t)lane * KW + p] : 0;
+    float m = lane < splits ? rm[row * splits + lane] : -INFINITY;
+    double s = lane < splits ? rs[row * splits + lane] : 0.0;
+    const float base = cum_in != nullptr ? cum_in[row] : 0.f;
+    for (int sp = lane + kWave; sp < splits; sp += kWave) {  // rows of more than 64 segments
+      const float om = rm[row * splits + sp];
+      const double os = rs[row * splits + sp];
+      const float mm = fmaxf(m, om);
+      double ns = s > 0.0 ? s * (double)exp2f((m - mm) * c) : 0.0;
+      if (os > 0.0) ns += os * (double)exp2f((om - mm) * c);
+      m = mm;
+      s = ns;
+      for (int q = 0; q < KW; ++q) {
+        uint64_t x = lists[(size_t)sp * KW + q];
 #pragma unroll
-    for (int k = 1; k < kWave; k <<= 1) {
-      const float om = __shfl_xor(m, k, kWave);
-      const double os = __shfl_xor(s, k, kWave);
-      sm_merge(m, s, om, os, c);
+        for (int p = 0; p < KW; ++p) {  // insert: the rest moves down
+          const uint64_t y = lst[p];
+          lst[p] = x > y ? x : y;
+          x = x > y ? y : x;
+        }
+      }
     }
+    wave_stats(m, s, c);
     const double lse = log(s);  // log of sum exp((v - m) / T)
     // the leaf's W best: W rounds of a wave maximum over the list heads
+    uint64_t mine = 0;
     for (int r = 0; r < W; ++r) {
       const uint64_t best = wave_max_u64(lst[0]);
       const bool win = best != 0 && lst[0] == best;  // non-empty keys are distinct
 #pragma unroll
-      for (int p = 0; p < kKW - 1; ++p) lst[p] = win ? lst[p + 1] : lst[p];
-      lst[kKW - 1] = win ? 0 : lst[kKW - 1];
-      if (lane == 0) {
-        const double lp = ((double)key_value(best) - (double)m) * (double)inv_t - lse;
-        s_sc[wave * kKW + r] = best != 0 ? (double)base + lp : -INFINITY;
-        s_tk[wave * kKW + r] = best != 0 ? key_token(best) : -1;
-      }
+      for (int p = 0; p < KW - 1; ++p) lst[p] = win ? lst[p + 1] : lst[p];
+      lst[KW - 1] = win ? 0 : lst[KW - 1];
+      mine = lane == r ? best : mine;
+    }
+    if (lane < W) {
+      const double lp = ((double)key_value(mine) - (double)m) * (double)inv_t - lse;
+      s_sc[wave * KW + lane] = mine != 0 ? (double)base + lp : -INFINITY;
+      s_tk[wave * KW + lane] = mine != 0 ? key_token(mine) : -1;
     }
   }
   __syncthreads();
   // the W best of the Wc x W: valid first, larger score, lower parent, lower token
   const int m2 = Wc * W;
-  for (int i = tid; i < m2; i += kSelThreads) {
+  for (int i = tid; i < m2; i += blockDim.x) {
     const int leaf = i / W, r0 = i - leaf * W;
-    const double sc = s_sc[leaf * kKW + r0];
-    const int tk = s_tk[leaf * kKW + r0];
+    const double sc = s_sc[leaf * KW + r0];
+    const int tk = s_tk[leaf * KW + r0];
     const bool ok = tk >= 0;
     int r = 0;
     for (int lj = 0; lj < Wc; ++lj) {
-      double so[kKW];
-      int to[kKW];
+      double so[KW];
+      int to[KW];
 #pragma unroll
-      for (int rj = 0; rj < kKW; ++rj) {
-        so[rj] = s_sc[lj * kKW + rj];
-        to[rj] = s_tk[lj * kKW + rj];
+      for (int rj = 0; rj < KW; ++rj) {
+        so[rj] = s_sc[lj * KW + rj];
+        to[rj] = s_tk[lj * KW + rj];
       }
 #pragma unroll
-      for (int rj = 0; rj < kKW; ++rj) {
+      for (int rj = 0; rj < KW; ++rj) {
         const bool okj = to[rj] >= 0;
         const bool tie_lower = (lj < leaf) | ((lj == leaf) & ((to[rj] < tk) | ((to[rj] == tk) & (rj < r0))));
         const bool better = (okj & !ok) | ((okj == ok) & ((so[rj] > sc) | ((so[rj] == sc) & tie_lower)));
@@ -318,19 +296,20 @@ __global__ __launch_bounds__(kSelThreads) void tree_select_kernel(
   }
 }
 
+int list_len(int W) { return W <= 4 ? 4 : (W <= 8 ? 8 : kKW); }
+
 }  // namespace
 
 TreeBuildLayout tree_build_layout(int B, int Wc, int W, int V) {
   TreeBuildLayout L{};
   const int rows = std::max(1, B * Wc);
-  int splits = ceil_div(V, kPassElems);
-  splits = std::min(splits, kMaxSplits);
-  L.splits = std::max(1, splits);
+  // eight logits per thread (twice the workgroups) while a leaf's segments fit the select's lanes
+  L.splits = ceil_div(V, kTopThreads * (V <= kShortRow ? 8 : 16));
   const size_t n = (size_t)rows * L.splits;
   Carve c;
   L.rm = c.take(n * sizeof(float));
   L.rs = c.take(n * sizeof(double));
-  L.rk = c.take(n * kKW * sizeof(uint64_t));
+  L.rk = c.take(n * list_len(W) * sizeof(uint64_t));
   L.total = c.off;
   return L;
 }
@@ -339,25 +318,41 @@ hipError_t launch_tree_build(const float* logits, int B, int Wc, int V, const fl
                              float temperature, int32_t* tokens, int32_t* parents,
                              float* cum_out, char* ws, const TreeBuildLayout& L,
                              hipStream_t stream) {
-  if (W < 1 || W > kKW || Wc < 1 || Wc > kKW || L.splits > kMaxSplits)
-    return hipErrorInvalidValue;
-  const int splits = L.splits;
-  int seg = ceil_div(V, splits);
-  seg = (seg + 3) & ~3;
+  if (W < 1 || W > kKW || Wc < 1 || Wc > kKW) return hipErrorInvalidValue;
   float* rm = reinterpret_cast<float*>(ws + L.rm);
   double* rs = reinterpret_cast<double*>(ws + L.rs);
   uint64_t* rk = reinterpret_cast<uint64_t*>(ws + L.rk);
   const float c = (float)(1.4426950408889634 / (double)temperature);
+  const dim3 grid(L.splits, B * Wc);
   {
     ProfScope prof("tree_topw", stream);
-    klaunch(tree_topw_kernel, dim3(splits, B * Wc), kTopThreads, 0, stream, logits, V, seg, W, c, rm, rs,
-                                                                     rk);
+#define SIRIUS_TOPW(KW)                                                                              \
+  if (V <= kShortRow)                                                                                \
+    klaunch((tree_topw_kernel<8, KW>), grid, kTopThreads, 0, stream, logits, V, W, c, rm, rs, rk);   \
+  else                                                                                               \
+    klaunch((tree_topw_kernel<16, KW>), grid, kTopThreads, 0, stream, logits, V, W, c, rm, rs, rk)
+    if (W <= 4) {
+      SIRIUS_TOPW(4);
+    } else if (W <= 8) {
+      SIRIUS_TOPW(8);
+    } else {
+      SIRIUS_TOPW(16);
+    }
+#undef SIRIUS_TOPW
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   ProfScope prof("tree_select", stream);
-  klaunch(tree_select_kernel, B, kSelThreads, 0, stream, Wc, W, splits, c, (float)(1.0 / temperature),
-                                                    rm, rs, rk, cum_ll, tokens, parents, cum_out);
+  const float inv_t = (float)(1.0 / temperature);
+  if (W <= 4)
+    klaunch(tree_select_kernel<4>, B, Wc * kWave, 0, stream, Wc, W, L.splits, c, inv_t, rm, rs, rk, cum_ll,
+            tokens, parents, cum_out);
+  else if (W <= 8)
+    klaunch(tree_select_kernel<8>, B, Wc * kWave, 0, stream, Wc, W, L.splits, c, inv_t, rm, rs, rk, cum_ll,
+            tokens, parents, cum_out);
+  else
+    klaunch(tree_select_kernel<16>, B, Wc * kWave, 0, stream, Wc, W, L.splits, c, inv_t, rm, rs, rk, cum_ll,
+            tokens, parents, cum_out);
   return hipGetLastError();
 }
 
