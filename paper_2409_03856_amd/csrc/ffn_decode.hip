@@ -320,7 +320,9 @@ hipError_t launch_mode(int cpl, int G, hipStream_t s, const float* x, const uint
 
 Decode1Layout decode1_layout(int d, int F) {
   Decode1Layout L{};
-  L.nseg = std::max(1, std::min(kSegs, ceil_div(F, kMinRows)));
+  // A small layer is bound by latency: a row per wave, and half the partials for what follows.
+  const int rows = (long)d * F <= (1l << 20) ? kWaves : kMinRows;
+  L.nseg = std::max(1, std::min(kSegs, ceil_div(F, rows)));
   L.rmax = ceil_div(F, L.nseg);
   Carve c;
   L.uidx = c.take((size_t)L.nseg * L.rmax * 4);
@@ -360,6 +362,7 @@ hipError_t launch_ffn_decode1(const float* x, const uint16_t* wg, const uint16_t
                                   uidx, ucnt, part, nullptr, nullptr);
     if (e != hipSuccess) return e;
   }
+  if (y == nullptr) return hipSuccess;
   ProfScope prof(topk ? "topk_reduce" : (thr ? "cats_reduce" : "dense_reduce"), stream);
   if (mode != kFfnModeDense && active_idx != nullptr)
     return launch_reduce(part, L.nseg, 1, d, resid, y, stream, F, L.nseg, L.rmax, uidx, ucnt,

@@ -86,6 +86,8 @@ struct Decode1Layout {
 hipError_t launch_decode1_act(const float* x, const uint16_t* wg, int d, int F, float norm_eps,
                               float* act, hipStream_t stream);
 Decode1Layout decode1_layout(int d, int F);
+// With y == nullptr the segment partials are left in the workspace (L.part, [L.nseg][d]) for a caller
+// that adds them itself.
 hipError_t launch_ffn_decode1(const float* x, const uint16_t* wg, const uint16_t* wu,
                               const uint16_t* wd, int d, int F, int mode, float t, float norm_eps,
                               const float* resid, float* y, int32_t* active_idx,
@@ -221,12 +223,33 @@ hipError_t launch_kv_rollback(int32_t* cache_pos, const int32_t* accept_len, int
 // h[i] = E[tokens[i]] widened to fp32 (0 for an id outside [0, V)); d % 8 == 0.
 hipError_t launch_embed(const int32_t* tokens, int n, const uint16_t* E, int d, int V, float* out,
                         hipStream_t s);
-// One token's products: RMSNorm (unit weight, bit for bit rmsnorm_vec_kernel's result) of x [K] as
-// it is staged, then q = xn Wq^T [Nq] fp32 and, for Nkv > 0, k = xn Wk^T, v = xn Wv^T [Nkv] bf16 in
-// one launch. K % 8 == 0, K <= 8192, 16-byte aligned rows.
-hipError_t launch_norm_qkv(const float* x, int K, float eps, const uint16_t* Wq, int Nq,
-                           const uint16_t* Wk, const uint16_t* Wv, int Nkv, float* yq,
-                           uint16_t* yk, uint16_t* yv, hipStream_t s);
+// The row that a one-token projection starts from: x itself; a token's embedding (embed set: of
+// token[0], or with logits set of their argmax, which is then stored as seq[slot] and
+// trace_drafted[slot - 1] with cache_pos[0] advanced by one, as launch_draft_tail does); or x + the
+// batch-1 FFN's nseg partial rows (part set). The last two write the row to h_out, which is not x.
+struct StepSource {
+  const float* x = nullptr;
+  const int32_t* token = nullptr;
+  const uint16_t* embed = nullptr;
+  int V = 0;
+  const float* logits = nullptr;
+  int32_t* seq = nullptr;
+  int slot = 0;
+  int32_t* cache_pos = nullptr;
+  int32_t* trace_drafted = nullptr;
+  const float* part = nullptr;
+  int nseg = 0;
+  float* h_out = nullptr;
+};
+// Whether every workgroup of the projection can form its row itself for less than a launch.
+bool step_takes_partials(int K, int nseg);
+bool step_takes_logits(int V, int N);  // N output rows
+// One token's products: RMSNorm (unit weight, bit for bit rmsnorm_vec_kernel's result) of the row
+// [K], then q = xn Wq^T [Nq] fp32 and, for Nkv > 0, k = xn Wk^T, v = xn Wv^T [Nkv] bf16 in one launch.
+// K % 8 == 0, K <= 8192, 16-byte aligned rows.
+hipError_t launch_norm_qkv(const StepSource& src, int K, float eps, const uint16_t* Wq, int Nq,
+                           const uint16_t* Wk, const uint16_t* Wv, int Nkv, float* yq, uint16_t* yk,
+                           uint16_t* yv, hipStream_t s);
 // y[j] = x . W[j] (+ resid[j]) for j < N; W [N][K] bf16; K % 8 == 0, K <= 8192.
 hipError_t launch_linear(const float* x, const uint16_t* W, int K, int N, const float* resid, float* y,
                          hipStream_t s);

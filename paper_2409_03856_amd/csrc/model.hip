@@ -32,7 +32,27 @@ namespace {
 constexpr int kLinThreads = 256;
 constexpr int kLinWaves = kLinThreads / kWave;
 constexpr int kLinMaxK = 8192;  // floats of x staged per launch
+constexpr int kLinMaxPartK = 512;  // widest row summed from FFN partials on the way in
+constexpr int kPartBlocks = 128;   // workgroups that read the FFN's partials at most
 constexpr int kTailThreads = 1024;
+static_assert(kLinMaxPartK <= 4 * kLinThreads && kLinMaxPartK / 4 * 16 <= kLinMaxK / 4, "one column per thread; LDS");
+
+// Where the row of a one-token projection comes from (norm_qkv_kernel).
+struct StepRow {
+  const float* x;        // kSrcRow: the row; kSrcPartials: the residual
+  const int32_t* token;  // kSrcToken
+  const uint2* embed;
+  int V;
+  const float* logits;   // kSrcToken after a draft: the previous step's logits, else null
+  int32_t* seq;
+  int slot;
+  int32_t* cache_pos;
+  int32_t* trace_drafted;
+  const float* part;     // kSrcPartials: [nseg][K]
+  int nseg;
+  float* h_out;          // kSrcToken, kSrcPartials: the row, for the residuals that follow
+};
+constexpr int kSrcRow = 0, kSrcToken = 1, kSrcPartials = 2;
 
 __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ tokens, int n,
                                                     const uint4* __restrict__ E, int d8, int V,
@@ -69,13 +89,66 @@ __global__ __launch_bounds__(kLinThreads) void linear_kernel(const float* __rest
   }
 }
 
+// Argmax over one row of V logits, lowest index on ties: (value, index) pairs reduced so
+// that the larger value wins and, on equal values, the smaller index.
+__device__ __forceinline__ void better(float& v, int& i, float ov, int oi) {
+  if (ov > v || (ov == v && oi < i)) {
+    v = ov;
+    i = oi;
+  }
+}
+
+template <int THREADS>
+__device__ int block_argmax(const float* __restrict__ row, int V) {
+  constexpr int kAhead = 4;  // loads in flight per thread
+  __shared__ float s_v[THREADS / kWave];
+  __shared__ int s_i[THREADS / kWave];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+  float bv = -INFINITY;
+  int bi = INT32_MAX;
+  for (int v0 = tid; v0 < V; v0 += THREADS * kAhead) {
+    float x[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) x[u] = v0 + u * THREADS < V ? row[v0 + u * THREADS] : -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (v0 + u * THREADS < V) better(bv, bi, x[u], v0 + u * THREADS);
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    const float ov = __shfl_xor(bv, m, kWave);
+    const int oi = __shfl_xor(bi, m, kWave);
+    better(bv, bi, ov, oi);
+  }
+  if (lane == 0) {
+    s_v[wave] = bv;
+    s_i[wave] = bi;
+  }
+  __syncthreads();
+  bv = s_v[0];
+  bi = s_i[0];
+  for (int w = 1; w < THREADS / kWave; ++w) better(bv, bi, s_v[w], s_i[w]);
+  return bi == INT32_MAX ? 0 : bi;  // a row of NaNs only
+}
+
 // Output rows j of the three products in one range: [0, Nq) of Wq into yq (fp32), then
-// [Nq, Nq + Nkv) of Wk and [Nq + Nkv, Nq + 2 Nkv) of Wv into yk, yv (bf16). The row x is staged
-// in LDS (every load in flight at once), then normalised there: each thread sums the squares of
-// its float4s tid + 256 u as rmsnorm_vec_kernel does, the wave sums go through LDS, and after one
-// barrier each thread scales its float4s.
+// [Nq, Nq + Nkv) of Wk and [Nq + Nkv, Nq + 2 Nkv) of Wv into yk, yv (bf16). The row x is formed
+// in every workgroup (SRC, see StepRow; workgroup 0 writes it to h_out), then normalised: each
+// thread sums the squares of its float4s tid + 256 u as rmsnorm_vec_kernel does, the wave sums go
+// through LDS, and each thread scales its float4s into LDS.
+//   kSrcRow       x is the row given.
+//   kSrcToken     x is a token's embedding. The token is given, or (logits != nullptr) it is the
+//                 argmax of the previous step's logits, which every workgroup finds for itself;
+//                 workgroup 0 then does what draft_tail_kernel does.
+//   kSrcPartials  x = resid + the batch-1 FFN's segment partials, added in reduce_kernel's order
+//                 (16 groups of every 16th row, then the groups), so the same bits.
+// The last two save a dependent launch of 2-4 us each at the loop's small decoder, where they add
+// 1-2 us to this one: two periods of 16 drafts on the 2-layer, 256-wide decoder 1827 -> 1607 us.
+constexpr int kPartGroups = 16;  // reduce_kernel's groups of partial rows
+
+template <int SRC>
 __global__ __launch_bounds__(kLinThreads) void norm_qkv_kernel(
-    const float* __restrict__ x, int K, float eps, const uint4* __restrict__ Wq, int Nq,
+    StepRow in, int K, float eps, const uint4* __restrict__ Wq, int Nq,
     const uint4* __restrict__ Wk, const uint4* __restrict__ Wv, int Nkv, float* __restrict__ yq,
     uint16_t* __restrict__ yk, uint16_t* __restrict__ yv) {
   static_assert(kLinThreads == 256, "the norm's sums follow rmsnorm_vec_kernel's 256-thread layout");
@@ -85,12 +158,91 @@ __global__ __launch_bounds__(kLinThreads) void norm_qkv_kernel(
   const float* xs = reinterpret_cast<const float*>(s_x4);
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int k4 = K >> 2, k8 = K >> 3;
-  const float4* x4 = reinterpret_cast<const float4*>(x);
   float4 v[kPer];
+  if (SRC == kSrcRow) {
+    const float4* x4 = reinterpret_cast<const float4*>(in.x);
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int e = tid + kLinThreads * u;
-    v[u] = (e < k4) ? x4[e] : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int u = 0; u < kPer; ++u) {
+      const int e = tid + kLinThreads * u;
+      v[u] = (e < k4) ? x4[e] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  } else if (SRC == kSrcToken) {
+    int tok;
+    if (in.logits != nullptr) {  // uniform
+      tok = block_argmax<kLinThreads>(in.logits, in.V);
+      if (blockIdx.x == 0 && tid == 0) {
+        in.seq[in.slot] = tok;
+        in.cache_pos[0] += 1;
+        if (in.trace_drafted != nullptr) in.trace_drafted[in.slot - 1] = tok;
+      }
+    } else {
+      tok = in.token[0];
+    }
+    const bool ok = tok >= 0 && tok < in.V;
+    const uint2* row = in.embed + (size_t)(ok ? tok : 0) * k4;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = tid + kLinThreads * u;
+      const uint2 w = (ok && e < k4) ? row[e] : make_uint2(0u, 0u);
+      v[u] = make_float4(bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y));
+    }
+  } else {
+    // (group, column) pairs of kPartGroups x k4 (k4 <= 128): at most eight per thread, the loads of
+    // four partial rows of every pair in flight
+    constexpr int kPairs = kLinMaxPartK / 4 * kPartGroups / kLinThreads, kAhead = 4;
+    const float4* p4 = reinterpret_cast<const float4*>(in.part);
+    float4 s[kPairs];
+#pragma unroll
+    for (int k = 0; k < kPairs; ++k) s[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int r0 = 0; r0 < in.nseg; r0 += kPartGroups * kAhead) {
+      float4 w[kAhead][kPairs];
+#pragma unroll
+      for (int a = 0; a < kAhead; ++a)
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k) {
+          const int pair = tid + kLinThreads * k, g = pair / k4, c = pair - g * k4;
+          const int r = r0 + kPartGroups * a + g;
+          w[a][k] = (g < kPartGroups && r < in.nseg) ? p4[(size_t)r * k4 + c] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+      for (int a = 0; a < kAhead; ++a)
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k) {
+          s[k].x += w[a][k].x;
+          s[k].y += w[a][k].y;
+          s[k].z += w[a][k].z;
+          s[k].w += w[a][k].w;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kPairs; ++k) {
+      const int pair = tid + kLinThreads * k;
+      if (pair < kPartGroups * k4) s_x4[pair] = s[k];  // [group][column]
+    }
+    __syncthreads();
+    v[0] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int u = 1; u < kPer; ++u) v[u] = v[0];
+    if (tid < k4) {
+      float4 t = s_x4[tid];
+      for (int g = 1; g < kPartGroups; ++g) {
+        const float4 a = s_x4[g * k4 + tid];
+        t.x += a.x;
+        t.y += a.y;
+        t.z += a.z;
+        t.w += a.w;
+      }
+      const float4 r = reinterpret_cast<const float4*>(in.x)[tid];
+      v[0] = make_float4(r.x + t.x, r.y + t.y, r.z + t.z, r.w + t.w);
+    }
+    __syncthreads();  // the partials are read: the normalised row takes their place
+  }
+  if (SRC != kSrcRow && blockIdx.x == 0) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = tid + kLinThreads * u;
+      if (e < k4) reinterpret_cast<float4*>(in.h_out)[e] = v[u];
+    }
   }
   float ss = 0.f;
 #pragma unroll
@@ -126,43 +278,10 @@ __global__ __launch_bounds__(kLinThreads) void norm_qkv_kernel(
   }
 }
 
-// Argmax over one row of V logits, lowest index on ties: (value, index) pairs reduced so
-// that the larger value wins and, on equal values, the smaller index.
-__device__ __forceinline__ void better(float& v, int& i, float ov, int oi) {
-  if (ov > v || (ov == v && oi < i)) {
-    v = ov;
-    i = oi;
-  }
-}
-
-__device__ int block_argmax(const float* __restrict__ row, int V) {
-  __shared__ float s_v[kTailThreads / kWave];
-  __shared__ int s_i[kTailThreads / kWave];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-  float bv = -INFINITY;
-  int bi = INT32_MAX;
-  for (int v = tid; v < V; v += kTailThreads) better(bv, bi, row[v], v);
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    const float ov = __shfl_xor(bv, m, kWave);
-    const int oi = __shfl_xor(bi, m, kWave);
-    better(bv, bi, ov, oi);
-  }
-  if (lane == 0) {
-    s_v[wave] = bv;
-    s_i[wave] = bi;
-  }
-  __syncthreads();
-  bv = s_v[0];
-  bi = s_i[0];
-  for (int w = 1; w < kTailThreads / kWave; ++w) better(bv, bi, s_v[w], s_i[w]);
-  return bi == INT32_MAX ? 0 : bi;  // a row of NaNs only
-}
-
 __global__ __launch_bounds__(kTailThreads) void draft_tail_kernel(
     const float* __restrict__ logits, int V, int32_t* __restrict__ seq, int slot,
     int32_t* __restrict__ cache_pos, int pos_delta, int32_t* __restrict__ trace_drafted) {
-  const int tok = block_argmax(logits, V);
+  const int tok = block_argmax<kTailThreads>(logits, V);
   if (threadIdx.x == 0) {
     seq[slot] = tok;
     cache_pos[0] += pos_delta;
@@ -204,17 +323,36 @@ hipError_t launch_embed(const int32_t* tokens, int n, const uint16_t* E, int d, 
   return hipGetLastError();
 }
 
-hipError_t launch_norm_qkv(const float* x, int K, float eps, const uint16_t* Wq, int Nq,
+hipError_t launch_norm_qkv(const StepSource& src, int K, float eps, const uint16_t* Wq, int Nq,
                            const uint16_t* Wk, const uint16_t* Wv, int Nkv, float* yq, uint16_t* yk,
                            uint16_t* yv, hipStream_t s) {
   if ((K & 7) != 0 || K > kLinMaxK || Nq < 1 || Nkv < 0 ||
-      (Nkv > 0 && (Wk == nullptr || Wv == nullptr || yk == nullptr || yv == nullptr)))
+      (Nkv > 0 && (Wk == nullptr || Wv == nullptr || yk == nullptr || yv == nullptr)) ||
+      (src.part != nullptr && K > kLinMaxPartK))
     return hipErrorInvalidValue;
   ProfScope prof("norm_qkv", s);
-  klaunch(norm_qkv_kernel, std::min(ceil_div(Nq + 2 * Nkv, kLinWaves), 2048), kLinThreads, 0, s, x, K,
-          eps, reinterpret_cast<const uint4*>(Wq), Nq, reinterpret_cast<const uint4*>(Wk),
-          reinterpret_cast<const uint4*>(Wv), Nkv, yq, yk, yv);
+  const StepRow in{src.x, src.token, reinterpret_cast<const uint2*>(src.embed), src.V, src.logits, src.seq,
+                   src.slot, src.cache_pos, src.trace_drafted, src.part, src.nseg, src.h_out};
+  const int grid = std::min(ceil_div(Nq + 2 * Nkv, kLinWaves), src.part != nullptr ? kPartBlocks : 2048);
+  const uint4* q4 = reinterpret_cast<const uint4*>(Wq);
+  const uint4* k4 = reinterpret_cast<const uint4*>(Wk);
+  const uint4* v4 = reinterpret_cast<const uint4*>(Wv);
+  if (src.part != nullptr)
+    klaunch(norm_qkv_kernel<kSrcPartials>, grid, kLinThreads, 0, s, in, K, eps, q4, Nq, k4, v4, Nkv, yq, yk, yv);
+  else if (src.embed != nullptr)
+    klaunch(norm_qkv_kernel<kSrcToken>, grid, kLinThreads, 0, s, in, K, eps, q4, Nq, k4, v4, Nkv, yq, yk, yv);
+  else
+    klaunch(norm_qkv_kernel<kSrcRow>, grid, kLinThreads, 0, s, in, K, eps, q4, Nq, k4, v4, Nkv, yq, yk, yv);
   return hipGetLastError();
+}
+
+// What every workgroup of the launch reads for itself comes from L2 at about 8 TB/s over the chip:
+// at most 2 us of partials (the launch that it saves takes 3-4) and 1 us of logits.
+bool step_takes_partials(int K, int nseg) {
+  return K <= kLinMaxPartK && (size_t)kPartBlocks * nseg * K * sizeof(float) <= (size_t)16 << 20;
+}
+bool step_takes_logits(int V, int N) {
+  return (size_t)std::min(ceil_div(N, kLinWaves), 2048) * V * sizeof(float) <= (size_t)8 << 20;
 }
 
 hipError_t launch_linear(const float* x, const uint16_t* W, int K, int N, const float* resid, float* y,

@@ -36,7 +36,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 // Workspace of a forward pass of up to nmax tokens (and of a period with n = nmax).
 struct ModelLayout {
-  size_t h, xf, q, kb, vb, att, logits, ints, sub, total;
+  size_t h, h2, xf, q, kb, vb, att, logits, ints, sub, total;
 };
 
 size_t ffn_ws_any(int B, int d, int F, bool sparse) {
@@ -48,6 +48,7 @@ ModelLayout model_layout(const sirius_model* m, int nmax) {
   ModelLayout L{};
   sirius::Carve c;
   L.h = c.take((size_t)nmax * d * 4);
+  L.h2 = c.take((size_t)d * 4);
   L.xf = c.take(nmax > 1 ? sirius::linear_mfma_ws(nmax, std::max(d, hq)) : 0);  // projection inputs of a chunk
   L.q = c.take((size_t)nmax * hq * 4);
   L.kb = c.take((size_t)nmax * hkv * 2);
@@ -121,11 +122,85 @@ hipError_t ffn_any(const float* x, int B, const uint16_t* wg, const uint16_t* wu
                                 resid, y, aidx, acnt, ws, s);
 }
 
+// What the first launch of a drafting step does besides: the draft of the step before.
+struct DraftBefore {
+  const float* logits;
+  int32_t* seq;
+  int slot;
+  int32_t* trace_drafted;
+};
+
+// One pass over one token (see forward). The embedding row is formed in the first projection's
+// launch (with `draft`, of the token that it drafts), and at small layers the FFN's partials are
+// added in the next projection's launch, the rows alternating between two buffers.
+hipError_t forward_one(const sirius_model* m, const int32_t* token, const DraftBefore* draft,
+                       int32_t* cache_pos, bool sparse, float* logits, int32_t* aidx,
+                       size_t a_lstride, int32_t* acnt, size_t c_lstride, char* ws,
+                       const ModelLayout& L, hipStream_t s) {
+  const int d = m->d_model, H = m->n_heads, Hkv = m->n_kv_heads, hd = m->head_dim, F = m->d_ff;
+  const int hq = H * hd, hkv = Hkv * hd;
+  const Strides st = strides(m);
+  float* rows[2] = {reinterpret_cast<float*>(ws + L.h), reinterpret_cast<float*>(ws + L.h2)};
+  float* h = rows[0];
+  float* q = reinterpret_cast<float*>(ws + L.q);
+  uint16_t* kb = reinterpret_cast<uint16_t*>(ws + L.kb);
+  uint16_t* vb = reinterpret_cast<uint16_t*>(ws + L.vb);
+  float* att = reinterpret_cast<float*>(ws + L.att);
+  char* sub = ws + L.sub;
+  const sirius::Decode1Layout DL = sirius::decode1_layout(d, F);
+  const bool partials = aidx == nullptr && sirius::step_takes_partials(d, DL.nseg);
+  const float* part = reinterpret_cast<const float*>(sub + DL.part);
+  sirius::StepSource src;
+  src.embed = m->embed;
+  src.V = m->vocab;
+  src.token = token;
+  src.h_out = h;
+  if (draft != nullptr) {
+    src.logits = draft->logits;
+    src.seq = draft->seq;
+    src.slot = draft->slot;
+    src.cache_pos = cache_pos;
+    src.trace_drafted = draft->trace_drafted;
+  }
+  hipError_t e;
+  // the source of the projection that follows an FFN
+  auto after_ffn = [&]() {
+    src = sirius::StepSource{};
+    src.x = h;
+    if (partials) {
+      src.part = part;
+      src.nseg = DL.nseg;
+      src.h_out = h = h == rows[0] ? rows[1] : rows[0];
+    }
+  };
+  for (int l = 0; l < m->n_layers; ++l) {
+    if ((e = sirius::launch_norm_qkv(src, d, m->norm_eps, m->wq + l * st.q, hq, m->wk + l * st.kv,
+                                     m->wv + l * st.kv, hkv, q, kb, vb, s)) != hipSuccess)
+      return e;
+    const sirius::AttnLayout AL = sirius::attn_layout(1, 1, H, Hkv, hd, m->max_len);
+    if ((e = sirius::launch_attn_kv(q, kb, vb, m->k_cache + l * st.cache, m->v_cache + l * st.cache,
+                                    cache_pos, 1, 1, H, Hkv, hd, m->max_len, att, sub, AL, s)) != hipSuccess)
+      return e;
+    if ((e = sirius::launch_linear(att, m->wo + l * st.o, hq, d, h, h, s)) != hipSuccess) return e;
+    if ((e = sirius::launch_ffn_decode1(
+             h, m->w_gate + l * st.ffn, m->w_up + l * st.ffn, m->w_down + l * st.ffn, d, F,
+             sparse ? sirius::kFfnModeThreshold : sirius::kFfnModeDense, sparse ? m->thresholds[l] : 0.f,
+             m->norm_eps, h, partials ? nullptr : h, aidx ? aidx + l * a_lstride : nullptr,
+             acnt ? acnt + l * c_lstride : nullptr, sub, DL, s)) != hipSuccess)
+      return e;
+    after_ffn();
+  }
+  return sirius::launch_norm_qkv(src, d, m->norm_eps, m->lm_head, m->vocab, nullptr, nullptr, 0, logits,
+                                 nullptr, nullptr, s);
+}
+
 // One pass over n tokens at the device-held position. Active lists (sparse only) go to
 // aidx + l * a_lstride, acnt + l * c_lstride for layer l.
-hipError_t forward(const sirius_model* m, const int32_t* tokens, int n, const int32_t* cache_pos,
+hipError_t forward(const sirius_model* m, const int32_t* tokens, int n, int32_t* cache_pos,
                    bool sparse, float* logits, int32_t* aidx, size_t a_lstride, int32_t* acnt,
                    size_t c_lstride, char* ws, const ModelLayout& L, hipStream_t s) {
+  if (n == 1)
+    return forward_one(m, tokens, nullptr, cache_pos, sparse, logits, aidx, a_lstride, acnt, c_lstride, ws, L, s);
   const int d = m->d_model, H = m->n_heads, Hkv = m->n_kv_heads, hd = m->head_dim;
   const int hq = H * hd, hkv = Hkv * hd;
   const Strides st = strides(m);
@@ -136,15 +211,11 @@ hipError_t forward(const sirius_model* m, const int32_t* tokens, int n, const in
   float* att = reinterpret_cast<float*>(ws + L.att);
   char* sub = ws + L.sub;
   hipError_t e;
-  // one token: the GEMV kernels (the norm folded in); a chunk: the MFMA projections, which read
-  // every weight once for all of its tokens
+  // the MFMA projections read every weight once for all of the chunk's tokens
   auto project = [&](const float* x, int K, float eps, const uint16_t* wq, int nq, const uint16_t* wk,
                      const uint16_t* wv, int nkv, const float* resid, float* yq, uint16_t* yk,
                      uint16_t* yv) {
-    if (n > 1)
-      return sirius::launch_linear_mfma(x, n, K, eps, wq, nq, wk, wv, nkv, resid, yq, yk, yv, ws + L.xf, s);
-    return eps < 0.f ? sirius::launch_linear(x, wq, K, nq, resid, yq, s)
-                     : sirius::launch_norm_qkv(x, K, eps, wq, nq, wk, wv, nkv, yq, yk, yv, s);
+    return sirius::launch_linear_mfma(x, n, K, eps, wq, nq, wk, wv, nkv, resid, yq, yk, yv, ws + L.xf, s);
   };
   if ((e = sirius::launch_embed(tokens, n, m->embed, d, m->vocab, h, s)) != hipSuccess) return e;
   for (int l = 0; l < m->n_layers; ++l) {
@@ -197,7 +268,7 @@ int sirius_model_forward(const sirius_model* model, const int32_t* tokens, int n
   const ModelLayout L = model_layout(model, n);
   if (ws_bytes < L.total)
     return fail(SIRIUS_EWORKSPACE, "%s: workspace %zu bytes < %zu needed", fn, ws_bytes, L.total);
-  return hip_status(forward(model, tokens, n, cache_pos, sparse != 0, logits, active_idx,
+  return hip_status(forward(model, tokens, n, const_cast<int32_t*>(cache_pos), sparse != 0, logits, active_idx,
                             (size_t)n * model->d_ff, active_cnt, (size_t)n, static_cast<char*>(ws),
                             L, static_cast<hipStream_t>(stream)),
                     fn);
@@ -241,12 +312,22 @@ int sirius_generate(const sirius_model* model, int32_t* seq, int32_t* cache_pos,
         aidx = trace->active_idx + step * Ln * F;
         acnt = trace->active_cnt + step * Ln;
       }
-      hipError_t e = forward(model, seq + i, 1, cache_pos, true, logits, aidx, (size_t)F, acnt, 1,
-                             w, L, s);
+      // the token of step i >= 1 is drafted by this step's first launch where that is cheaper than
+      // a launch of its own
+      int32_t* drafted = (trace && trace->drafted) ? trace->drafted + (size_t)p * n : nullptr;
+      const DraftBefore draft{logits, seq, i, drafted};
+      const bool fold = i > 0 && sirius::step_takes_logits(V, (model->n_heads + 2 * model->n_kv_heads) * model->head_dim);
+      if (i > 0 && !fold) {
+        hipError_t e = sirius::launch_draft_tail(logits, V, seq, i, cache_pos, 1, drafted, s);
+        if (e != hipSuccess) return hip_status(e, fn);
+      }
+      hipError_t e = forward_one(model, seq + i, fold ? &draft : nullptr, cache_pos, true, logits, aidx,
+                                 (size_t)F, acnt, 1, w, L, s);
       if (e != hipSuccess) return hip_status(e, fn);
-      e = sirius::launch_draft_tail(logits, V, seq, i + 1, cache_pos, (i + 1 < n) ? 1 : 1 - n,
-                                    (trace && trace->drafted) ? trace->drafted + (size_t)p * n : nullptr, s);
-      if (e != hipSuccess) return hip_status(e, fn);
+      if (i + 1 == n) {  // the last draft, and the position wound back to the period's first
+        e = sirius::launch_draft_tail(logits, V, seq, n, cache_pos, 1 - n, drafted, s);
+        if (e != hipSuccess) return hip_status(e, fn);
+      }
     }
     // the check: the full model over seq[0 .. n - 1] at P (rewriting rows P .. P + n - 1)
     hipError_t e = forward(model, seq, n, cache_pos, false, logits, nullptr, 0, nullptr, 0, w, L, s);
