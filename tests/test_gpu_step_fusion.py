@@ -1,0 +1,78 @@
+"""One-token passes form their rows in the next projection's launch (the drafted token's embedding, the
+residual with the FFN's partials) where sizes allow. On both sides of each size rule the results are
+those of the separate launches bit for bit: a pass that also returns the kept lists keeps the separate
+FFN sum, and a loop of single passes drafts with torch's argmax."""
+
+import numpy as np
+import pytest
+
+from synth import ModelShape, model_weights, prompt_tokens
+from gpu_util import say, dev_bf16, dev_i32, host
+
+pytestmark = pytest.mark.gpu
+
+# layers, d_model, d_ff, heads, kv heads, head_dim, vocab
+CASES = [
+    (2, 256, 688, 4, 2, 64, 1000),     # both: the draft and the partials
+    (3, 512, 300, 8, 2, 64, 2600),     # the widest row that takes partials, eight pairs per thread
+    (2, 512, 2600, 4, 4, 32, 700),     # more partials than the rule takes
+    (2, 520, 400, 2, 1, 40, 333),      # wider than the rule takes
+    (2, 136, 90, 3, 1, 24, 9000),      # a vocabulary past the draft rule at these rows or inside it
+    (1, 72, 17, 1, 1, 8, 60001),       # one partial row group, a vocabulary past the rule
+    (2, 264, 1500, 2, 2, 128, 5),      # a vocabulary of five
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_same_bits_as_separate_launches(case):
+    import torch
+    import paper_2409_03856_amd as sr
+    layers, d, f, h, hkv, hd, v = case
+    say(f"step fusion {case}")
+    s = ModelShape("fusion", layers, d, f, h, hkv, hd, v, 64, 6.0)
+    w = {k: dev_bf16(b) for k, b in model_weights(d + f, s).items()}
+    models = [sr.Model(w, h, hkv, hd, 64, [0.2] * layers) for _ in range(3)]
+    prompt = prompt_tokens(9, 6, v)
+    pos = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for m in models:
+        sr.sirius_model_forward(m, dev_i32(prompt), pos, False)
+    # one token, with and without the lists
+    pos.fill_(6)
+    a, _, _ = sr.sirius_model_forward(models[0], dev_i32(prompt[:1]), pos, True)
+    b, idx, cnt = sr.sirius_model_forward(models[1], dev_i32(prompt[:1]), pos, True, want_active=True)
+    assert np.array_equal(host(a), host(b)) and np.all(host(cnt) <= f)
+    # a period by generate, with and without the lists, and by single passes
+    n = 5
+    runs = []
+    for m, active in ((models[0], False), (models[1], True)):
+        seq = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+        seq[0] = int(prompt[2])
+        p = torch.full((1,), 6, dtype=torch.int32, device="cuda")
+        out, cnt, tr = sr.sirius_generate(m, seq, p, n, 0.1, 1, trace=True, trace_active=active)
+        runs.append([host(x) for x in (out, cnt, p, seq[:1], tr["drafted"], tr["accept_len"], tr["q"], m.k_cache.float(),
+                                       m.v_cache.float())])
+    for x, y in zip(*runs):
+        assert np.array_equal(x, y)
+    toks = [int(prompt[2])]
+    for i in range(n):
+        pos.fill_(6 + i)
+        lg, _, _ = sr.sirius_model_forward(models[2], dev_i32(np.array([toks[i]], np.int32)), pos, True, want_active=True)
+        toks.append(int(torch.argmax(lg[0])))
+    assert runs[0][4][0].tolist() == toks[1:]
+
+
+def test_dense_one_token_pass_and_unknown_token():
+    """A full-model pass of one token takes the same launches; an id outside the vocabulary embeds as
+    zeros, so its logits are those of a zero row (all equal to W_lm's product with 0)."""
+    import torch
+    import paper_2409_03856_amd as sr
+    s = ModelShape("fusion", 2, 256, 300, 4, 2, 64, 500, 64, 6.0)
+    m = sr.Model({k: dev_bf16(b) for k, b in model_weights(5, s).items()}, 4, 2, 64, 64, [0.1] * 2)
+    pos = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for bad in (-1, 500):
+        lg, _, _ = sr.sirius_model_forward(m, dev_i32(np.array([bad], np.int32)), pos, False)
+        assert np.all(host(lg) == 0)
+    one, _, _ = sr.sirius_model_forward(m, dev_i32(np.array([7], np.int32)), pos, False)
+    two, _, _ = sr.sirius_model_forward(m, dev_i32(np.array([7, 8], np.int32)), pos, False)
+    a, b = host(one)[0], host(two)[0]
+    assert np.max(np.abs(a - b)) <= 1e-4 * np.sqrt(np.mean(b * b))
