@@ -7,7 +7,7 @@
 //                  rows, one workgroup per CU. In order:
 //                  * the first gate row of every wave is requested before x is staged in
 //                    LDS (fp32, optionally RMS-normalised with unit weight);
-//                  * gate rows: wave w takes rows w, w + 16, ...; with d_model <= 4096 two
+//                  * gate rows: wave w takes rows w, w + 16, ...; with d_model <= 5120 two
 //                    rows are in flight per wave (the next one is requested before the
 //                    current one is reduced); a = SiLU(W_gate[i].x), kept iff |a| > t;
 //                  * a wave ballot + popcount compacts the kept rows in ascending order;
@@ -103,7 +103,9 @@ __global__ __launch_bounds__(kThreads) void decode1_kernel(
   __shared__ float s_ss[kWaves];
   float* xs = reinterpret_cast<float*>(s_x4);
 
-  constexpr int NB = CPL <= 8 ? 2 : 1;  // rows in flight per wave in the gate and up phases
+  // rows in flight per wave in the gate and up phases: two of up to 5120 columns fit in 128 VGPRs
+  // next to the rest (dense, which also holds W_down rows then: two of 4096)
+  constexpr int NB = CPL <= 8 || (CPL <= 10 && MODE != kModeDense) ? 2 : 1;
   // dense with d_model <= 4096: every row is kept, so a wave takes the gate and up rows of one
   // neuron together (two rows in flight) and the separate up phase and the compaction go away
   constexpr bool kFused = MODE == kModeDense && NB == 2;
@@ -287,10 +289,13 @@ __global__ __launch_bounds__(kThreads) void decode1_kernel(
   }
 }
 
-int pow2_cpl(int nch) {
-  int p = 1;
-  while (p * kWave < nch && p < 16) p <<= 1;
-  return p;
+// Chunks per lane and row: 1, 2 and every second value from 4. A class wider than the row spends
+// registers and issue slots on loads that are masked off: with 4, 8 and 16 only, 5120 columns took
+// 16 chunks for 10 and one row in flight (5120 x 13824 threshold decode call 55.5 -> 53.2 us, dense
+// 74.3 -> 72.4; 6144 x 16384 74.8 -> 73.1).
+int cpl_of(int nch) {
+  const int p = ceil_div(nch, kWave);
+  return p <= 2 ? p : (p + 1) & ~1;
 }
 
 template <int MODE>
@@ -307,7 +312,11 @@ hipError_t launch_mode(int cpl, int G, hipStream_t s, const float* x, const uint
     SIRIUS_DECODE1(1)
     SIRIUS_DECODE1(2)
     SIRIUS_DECODE1(4)
+    SIRIUS_DECODE1(6)
     SIRIUS_DECODE1(8)
+    SIRIUS_DECODE1(10)
+    SIRIUS_DECODE1(12)
+    SIRIUS_DECODE1(14)
     SIRIUS_DECODE1(16)
     default:
       return hipErrorInvalidValue;
@@ -346,7 +355,7 @@ hipError_t launch_ffn_decode1(const float* x, const uint16_t* wg, const uint16_t
   const uint4* wg4 = reinterpret_cast<const uint4*>(wg);
   const uint4* wu4 = reinterpret_cast<const uint4*>(wu);
   const uint4* wd4 = reinterpret_cast<const uint4*>(wd);
-  const int cpl = pow2_cpl(d / 8);
+  const int cpl = cpl_of(d / 8);
   const bool thr = mode == kFfnModeThreshold, topk = mode == kFfnModeTopK;
   hipError_t e;
   {
@@ -375,7 +384,7 @@ hipError_t launch_decode1_act(const float* x, const uint16_t* wg, int d, int F, 
   const Decode1Layout L = decode1_layout(d, F);
   if (d > kMaxD || (d & 7) != 0 || L.rmax > kMaxRows || L.nseg > kSegs) return hipErrorInvalidValue;
   ProfScope prof("topk_gate", stream);
-  return launch_mode<kModeAct>(pow2_cpl(d / 8), L.nseg, stream, x, reinterpret_cast<const uint4*>(wg),
+  return launch_mode<kModeAct>(cpl_of(d / 8), L.nseg, stream, x, reinterpret_cast<const uint4*>(wg),
                                nullptr, nullptr, d, F, 0.f, norm_eps, L.rmax, nullptr, nullptr, nullptr,
                                nullptr, nullptr, act);
 }
