@@ -6,32 +6,31 @@
 // far below the bf16 MFMA ridge (about 300).
 //
 //  prep_pieces_kernel  x -> optional RMSNorm -> PX bf16 pieces, zero-padded to whole 16-token
-//                      tiles. PX = 1: x rounded to bf16 (the full model's pass, as before).
-//                      PX = 3: x = hi + mid + lo exactly (each piece the bf16 rounding of what
-//                      the previous ones leave), so the MFMA products of the three pieces sum to
-//                      the fp32 product: the threshold, top-k and small-batch paths keep fp32
-//                      inputs.
-//  gu_ring_kernel      dense: H = SiLU(X W_gate^T) * (X W_up^T) for one segment of at most 56
-//                      neurons per workgroup; gate rows, up rows and the x pieces of every
-//                      token tile move into an LDS ring by direct global-to-LDS loads, two to
-//                      four K blocks in flight; wave (tile, product) multiplies with
-//                      v_mfma_f32_16x16x32_bf16.
-//  gu_unit_kernel      the same for 8..16 tokens with d_model a multiple of 2048: the weights
-//                      move through LDS in units of 16 rows x 2048 columns, each row's 4 KiB
-//                      requested by one wave with consecutive 1 KiB direct loads (the order in
-//                      which HBM streams a row fastest), x held in registers.
-//  cats_unit_kernel    the same modes as cats_ring_kernel for at most 4 tokens with d_model a
-//                      multiple of 2048 on the unit layout: the three pieces of the four tokens
-//                      are the 12 rows of one MFMA operand tile, held in registers.
-//  cats_ring_kernel    per-token sparsity over one segment: the gate rows alone through the ring
-//                      (threshold mode and the top-k gate pass), SiLU, the per-token keep
-//                      decision (|a| > t, or the top-k key against the token's cut), the union of
-//                      the tokens' kept neurons compacted in ascending order with a wave ballot,
-//                      then the up rows of that union only through the ring; h = a u where the
-//                      token keeps the neuron, 0 elsewhere, stored per segment position. Up rows
-//                      outside the union are never read. Dense and condensed calls of fewer than
-//                      8 tokens run here too, every neuron kept, so that a threshold below 0
-//                      gives the dense result bit for bit.
+//                      tiles, in rows (the unit kernels and the calibration read them so).
+//                      PX = 1: x rounded to bf16 (the full model's pass). PX = 3: x = hi + mid
+//                      + lo exactly (each piece the bf16 rounding of what the previous ones
+//                      leave), so the MFMA products of the three pieces sum to the fp32 product:
+//                      the threshold, top-k and small-batch paths keep fp32 inputs.
+//  prep_frag_kernel    (linear.hip) the same pieces in the order of the MFMA operand registers.
+//  gu_unit_kernel      dense: H = SiLU(X W_gate^T) * (X W_up^T) for one segment of at most 56
+//                      neurons per workgroup, for 8..16 tokens with d_model a multiple of 2048:
+//                      the weights move through LDS in units of 16 rows x 2048 columns, each
+//                      row's 4 KiB requested by one wave with consecutive 1 KiB direct loads (the
+//                      order in which HBM streams a row fastest), x held in registers.
+//  gu_frag_kernel      the same for every other call: the weights go through registers into two
+//                      LDS buffers, the x pieces from L2 into registers in operand order.
+//  cats_frag_kernel    per-token sparsity over one segment: the gate rows alone (threshold mode
+//                      and the top-k gate pass), SiLU, the per-token keep decision (|a| > t, or
+//                      the top-k key against the token's cut), the union of the tokens' kept
+//                      neurons compacted in ascending order with a wave ballot, then the up rows
+//                      of that union only; h = a u where the token keeps the neuron, 0 elsewhere,
+//                      stored per segment position. Up rows outside the union are never read.
+//                      Dense and condensed calls of fewer than 8 tokens run here too, every
+//                      neuron kept, so that a threshold below 0 gives the dense result bit for
+//                      bit.
+//  cats_unit_kernel    the modes of cats_frag_kernel for at most 4 tokens with d_model a multiple
+//                      of 2048 on the unit layout: the three pieces of the four tokens are the 12
+//                      rows of one MFMA operand tile, held in registers.
 //  down_ring_kernel    Y_partial over one 256-column tile and one range of 64-position blocks of
 //                      the segment layout: a segment's rows (dense) or its union rows (gathered
 //                      by index), so W_down rows outside the union are never read.
@@ -62,11 +61,6 @@ constexpr int kLdsRing = 150 * 1024;     // LDS the rings may take
 constexpr int kDnCols = 256;             // output columns per down workgroup
 constexpr int kDnBlock = 64;             // rows per down block
 
-// 16 zero bytes in global memory: the source of direct loads past d_model (a K tail)
-__device__ __align__(16) uint4 g_zero16[1] = {{0u, 0u, 0u, 0u}};
-
-__device__ __forceinline__ int swz(int r, int c) { return c ^ (r & 7); }
-
 // vmcnt wait until at most `later` blocks of L loads each are still in flight (later <= 10)
 template <int L>
 __device__ __forceinline__ void wait_later(int later) {
@@ -82,105 +76,6 @@ __device__ __forceinline__ void wait_later(int later) {
     case 8: wait_vm<(8 * L > 63 ? 63 : 8 * L)>(); break;
     case 9: wait_vm<(9 * L > 63 ? 63 : 9 * L)>(); break;
     default: wait_vm<(10 * L > 63 ? 63 : 10 * L)>(); break;
-  }
-}
-
-// Geometry of an LDS ring (compile-time): ROWS rows of KS bf16 per slot (KS * 2 bytes), as many
-// slots (at most 12) as fit in LDS bytes. Slots hold only rows that carry data (the real tokens
-// of a batch rounded up to a token class, not a whole 16-token tile), so small batches get deep
-// rings and many weight bytes in flight.
-template <int ROWS, int KS, int LDS>
-struct RingGeom {
-  static constexpr int kRowBytes = KS * 2;
-  static constexpr int kCpr = kRowBytes / 16;   // 16-byte chunks per row
-  static constexpr int kRowQuant = kWave / kCpr; // rows per wave instruction
-  static constexpr int kRows = (ROWS + kRowQuant - 1) / kRowQuant * kRowQuant;
-  static constexpr int kSlotBytes = kRows * kRowBytes;
-  static constexpr int kPieces = kRows * kCpr;
-  static constexpr int kLoads = (kPieces + kBT - 1) / kBT;
-  static constexpr int kFullWaves = (kPieces - (kLoads - 1) * kBT) / kWave;
-  static constexpr int slots_for() {
-    int s = LDS / kSlotBytes;
-    if (s > 12) s = 12;
-    while (s > 2 && (s - 2) * kLoads > 63) --s;  // vmcnt range of the waits
-    return s;
-  }
-  static constexpr int kSlots = slots_for();
-  static_assert(kSlots >= 3, "at least two blocks in flight");
-  static_assert(kLoads <= 8, "loads per thread");
-};
-
-// LDS ring filled by 16-byte direct global-to-LDS loads from kBT threads. A wave instruction
-// writes 64 consecutive 16-byte pieces, i.e. kRowQuant whole rows, so a lane fetches the chunk
-// that its piece holds under the swizzle c ^ (r & 7); the 16-row MFMA operand reads of one chunk
-// are then spread over the banks. Piece q * kBT + tid is load q of thread tid; the last load
-// exists for the first kFullWaves waves only, so every wave knows its own count and the ring
-// waits on exact vmcnt values. Row pointers come from row_of(r); nullptr marks a row of zeros
-// (rows past the data), whose pieces all come from one 16-byte zero block in the cache.
-template <class G>
-struct Ring {
-  const uint16_t* src[G::kLoads];
-  int kofs[G::kLoads];
-  int lds[G::kLoads];
-  bool full;  // wave-uniform: this wave issues the last load
-  template <class RowOf>
-  __device__ __forceinline__ Ring(int tid, int wave, RowOf row_of) {
-    full = wave < G::kFullWaves;
-#pragma unroll
-    for (int q = 0; q < G::kLoads; ++q) {
-      const int gp = min(q * kBT + tid, G::kPieces - 1);  // past the last piece: never issued
-      const int r = gp / G::kCpr, c = swz(r, gp % G::kCpr);
-      src[q] = row_of(r);
-      kofs[q] = 8 * c;
-      lds[q] = (q * kBT + wave * kWave) * 16;  // wave-uniform: lane l lands at + 16 l
-    }
-  }
-  // w_rows: the slot's first rows hold weights (read once: non-temporal loads)
-  __device__ __forceinline__ void issue(unsigned char* slot, int blk, int d, int w_rows) {
-    const int k0 = blk * (G::kRowBytes / 2);
-    const bool tail = k0 + G::kRowBytes / 2 > d;  // uniform
-    const int w_pieces = w_rows * G::kCpr;
-    const int wbase = __builtin_amdgcn_readfirstlane(threadIdx.x & ~(kWave - 1));
-#pragma unroll
-    for (int q = 0; q < G::kLoads; ++q) {
-      if (q == G::kLoads - 1 && !full) break;  // wave-uniform
-      const int k = k0 + kofs[q];
-      const void* gp = (src[q] == nullptr || (tail && k >= d)) ? static_cast<const void*>(g_zero16)
-                                                                : static_cast<const void*>(src[q] + k);
-      auto* lp = reinterpret_cast<__attribute__((address_space(3))) void*>(
-          reinterpret_cast<size_t>(slot + lds[q]));
-      if (q * kBT + wbase < w_pieces)
-        __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 2);
-      else
-        __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 0);
-    }
-  }
-  // at most `later` blocks of this wave's loads still in flight
-  __device__ __forceinline__ void wait(int later) {
-    if (full) wait_later<G::kLoads>(later);
-    else wait_later<G::kLoads - 1>(later);
-  }
-};
-
-// Runs the ring over nblk K blocks: compute(slot) for each block in order, with the kSlots - 1
-// blocks after it in flight. Block b: wait for it, barrier (every wave is done reading block
-// b - 1, whose slot is refilled with block b + kSlots - 1), compute.
-template <class G, class R, class Compute>
-__device__ __forceinline__ void run_ring(unsigned char* ring, R& rg, int nblk, int d, int w_rows,
-                                         Compute compute) {
-  constexpr int S = G::kSlots, SB = G::kSlotBytes;
-  static_assert(S - 2 <= 10, "wait_l covers ten later blocks");
-#pragma unroll
-  for (int p = 0; p < S - 1; ++p)
-    if (p < nblk) rg.issue(ring + p * SB, p, d, w_rows);
-  int slot = 0, refill = S - 1;
-  for (int b = 0; b < nblk; ++b) {
-    rg.wait(min(S - 2, nblk - 1 - b));
-    ring_barrier();
-    if (b + S - 1 < nblk) rg.issue(ring + refill * SB, b + S - 1, d, w_rows);
-    compute(ring + slot * SB);
-    slot = slot + 1 == S ? 0 : slot + 1;
-    refill = refill + 1 == S ? 0 : refill + 1;
   }
 }
 
@@ -256,17 +151,25 @@ __global__ __launch_bounds__(256) void prep_pieces_kernel(const float* __restric
 
 // Segment geometry: nseg segments of np neurons over n_rows rows, np a multiple of 4 of at most
 // 56, small enough that there are at least 256 segments (one workgroup per CU) when n_rows allows.
+// Above 256 full segments the rows are split over whole rounds of 256 workgroups: 15104 rows are
+// 472 segments of 32 and not 270 of 56, whose second round was nearly empty (gate/up at 3 tokens
+// of 4608 columns 97 -> 55 us with the operand-order pipeline, 40 tokens 196 -> 105).
 struct Seg {
   int nseg, np;
 };
 constexpr int kSegTarget = 256;
 __host__ __device__ inline Seg seg_of(int n_rows) {
-  int np = (n_rows + kSegTarget - 1) / kSegTarget;
+  const int rounds = (n_rows + kSegTarget * kSegN - 1) / (kSegTarget * kSegN);
+  int np = (n_rows + kSegTarget * rounds - 1) / (kSegTarget * rounds);
   np = (np + 3) & ~3;
   if (np > kSegN) np = kSegN;
   if (np < 4) np = 4;
   return Seg{(n_rows + np - 1) / np, np};
 }
+// Positions a segment owns in h and the down blocks: whole 16-neuron tiles. 48 next to 32 and 64:
+// the down pass streams a row for every position (8192 columns, 22671 rows in segments of 48, 40 tokens:
+// 92 us with 64 positions, 80 with 48).
+__host__ __device__ constexpr int seg_positions(int np) { return np <= 16 ? 16 : (np <= 32 ? 32 : (np <= 48 ? 48 : kSegPad)); }
 
 // h = SiLU(g) u as a bf16 pair (hi, lo): hi = bf16(h), lo = bf16(h - hi)
 __device__ __forceinline__ void store_h(uint16_t* hhi, uint16_t* hlo, size_t at, float h) {
@@ -288,127 +191,11 @@ __device__ __forceinline__ void zero_h_tail(uint16_t* hhi, uint16_t* hlo, int hs
   }
 }
 
-// Token classes: a batch of B tokens occupies TB slot rows per input piece (B rounded up to 4, 8,
-// 16, 32, 48 or 64); rows past B load zeros. MFMA tiles are 16 tokens: MT = ceil(TB / 16).
-__host__ __device__ inline int token_class(int B) {
-  return B <= 4 ? 4 : (B <= 8 ? 8 : (B <= 16 ? 16 : (B <= 32 ? 32 : (B <= 48 ? 48 : 64))));
-}
-// K per ring block: 128 (256-byte rows) when three slots fit in the LDS budget, else 64
-constexpr int ks_for(int rows, int lds) { return rows * 256 * 3 <= lds ? 128 : 64; }
-// LDS for the rings of the gate/up kernels (dynamic), next to their own static arrays
-constexpr int kGuLds = 144 * 1024;
-constexpr int kCatsLds = 124 * 1024;
-
-// NPM: neurons per segment at most (kSegN, or kSegSmall for short segments, whose smaller slots
-// leave room for a deeper ring)
-constexpr int kSegSmall = 32;
-template <int TB, int NPM>
-struct GuGeom {
-  static constexpr int kRowsData = 2 * NPM + TB;
-  using G = RingGeom<kRowsData, ks_for(kRowsData, kGuLds), kGuLds>;
-};
-template <int TB, int NPM>
-struct CatsGeom {
-  static constexpr int kRowsData = NPM + 3 * TB;
-  using G = RingGeom<kRowsData, ks_for(kRowsData, kCatsLds), kCatsLds>;
-};
-template <int TB, int NPM>
-struct AllGeom {
-  static constexpr int kRowsData = 2 * NPM + 3 * TB;
-  using G = RingGeom<kRowsData, ks_for(kRowsData, kCatsLds), kCatsLds>;
-};
-
-// ---- dense gate/up on the bf16-rounded input: one workgroup per segment of np neurons over
-// F16 rows (rows past d_ff give h = 0). Slot rows: gate rows [0, np), up rows [np, 2 np), then
-// TB token rows (zeros past B). Wave w: 16-neuron tile w / 2 of the gate (w even) or up (w odd)
-// rows; its A operand for tile mt reads token row min(16 mt + r, TB - 1), so a tile's padding
-// tokens (never stored) repeat a loaded row instead of occupying slot rows.
-template <int TB, int NPM>
-__global__ __launch_bounds__(kBT) void gu_ring_kernel(const uint16_t* __restrict__ xp, int B,
-                                                      const uint16_t* __restrict__ wg,
-                                                      const uint16_t* __restrict__ wu, int d,
-                                                      int F, int hs, int np, int sp,
-                                                      uint16_t* __restrict__ hhi,
-                                                      uint16_t* __restrict__ hlo) {
-  using G = typename GuGeom<TB, NPM>::G;
-  constexpr int MT = (TB + 15) / 16, KS = G::kRowBytes / 2;
-  extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-  const int fr = lane & 15, grp = lane >> 4;
-  const int n0 = blockIdx.x * np;
-  const int x0 = 2 * np;  // first token row of a slot
-  const int nblk = (d + KS - 1) / KS;
-  Ring<G> rg(tid, wave, [&](int r) -> const uint16_t* {
-    if (r < x0) {
-      const int j = r < np ? r : r - np;
-      const int n = min(n0 + j, F - 1);  // rows past d_ff: a valid row, h = 0 there
-      return (r < np ? wg : wu) + (size_t)n * d;
-    }
-    if (r < x0 + B) return xp + (size_t)(r - x0) * d;
-    return nullptr;
-  });
-
-  const int tau = wave >> 1, mu = wave & 1;
-  const bool active = 16 * tau < np;
-  const int wrow = mu * np + 16 * tau + fr;  // B operand row (past np: never stored)
-  floatx4_t acc[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) acc[mt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  run_ring<G>(ring, rg, nblk, d, x0, [&](const unsigned char* slot) {
-    if (!active) return;
-    constexpr int kSteps = KS / 32;
-    bf16x8_t bw[kSteps], ax[kSteps][MT];
-#pragma unroll
-    for (int i = 0; i < kSteps; ++i) {  // every operand of the block first, then the MFMAs
-      const int c = 4 * i + grp;
-      bw[i] = *reinterpret_cast<const bf16x8_t*>(slot + wrow * G::kRowBytes + 16 * swz(wrow, c));
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const int xr = x0 + min(16 * mt + fr, TB - 1);
-        ax[i][mt] = *reinterpret_cast<const bf16x8_t*>(slot + xr * G::kRowBytes + 16 * swz(xr, c));
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kSteps; ++i)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax[i][mt], bw[i], acc[mt], 0, 0, 0);
-  });
-
-  // epilogue: the up wave of each tile hands its sums to the gate wave through LDS
-  __syncthreads();  // every wave is done with the ring
-  floatx4_t* s_up = reinterpret_cast<floatx4_t*>(ring);  // [tile][mt][lane]
-  if (active && mu == 1) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) s_up[(tau * MT + mt) * kWave + lane] = acc[mt];
-  }
-  __syncthreads();
-  // h goes to the segment's positions [0, sp) (sp >= np, whole 16-neuron tiles): position j of
-  // segment s holds neuron s np + j, and h = 0 at the positions past the segment's rows, past
-  // d_ff and for the padding tokens, so the down pass can take whole 64-position blocks
-  if (mu == 0 && 16 * tau < sp) {
-    const int j = 16 * tau + fr, n = n0 + j;
-    const bool real = active && j < np && n < F;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const floatx4_t u4 = active ? s_up[(tau * MT + mt) * kWave + lane] : floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = 16 * mt + 4 * grp + r;
-        // C layout: lane holds neuron fr and tokens 4 (lane / 16) + r
-        store_h(hhi, hlo, (size_t)m * hs + (size_t)blockIdx.x * sp + j,
-                (real && m < B) ? silu(acc[mt][r]) * u4[r] : 0.f);
-      }
-    }
-  }
-  if (blockIdx.x == gridDim.x - 1) zero_h_tail(hhi, hlo, hs, gridDim.x * sp, 16 * MT);
-}
-
 // ---- dense gate/up of 8..16 tokens on the bf16-rounded input with d_model a multiple of 2048.
 // HBM streams a weight row fastest when its bytes are requested close together in time: one wave
 // reading a row's aligned 4 KiB with consecutive 1 KiB loads moves about 6.8 TB/s over the chip,
 // the same bytes requested 256 or 512 bytes per row per instruction, or spread over later
-// instructions, 5.0-6.0. The ring kernel above requests each row 256 bytes per K block; this one
+// instructions, 5.0-6.0. This kernel
 // moves the weights through LDS in units of 16 rows x 2048 columns, wave w requesting row w of
 // the unit with four consecutive 1 KiB direct loads, two unit buffers (128.5 KiB of LDS).
 // Segment rows: gate rows [0, np), up rows [np, 2 np), padded to whole 16-row tiles with zero
@@ -541,7 +328,7 @@ __global__ __launch_bounds__(kUnitThreads) void gu_unit_kernel(
                             : nullptr;
       },
       xa);
-  // h at the segment's positions [0, sp), as the ring kernel writes it: neuron n0 + j, zero past
+  // h at the segment's positions [0, sp), as gu_frag_kernel writes it: neuron n0 + j, zero past
   // the segment's rows, past d_ff and for the padding tokens
   for (int i = tid; i < 16 * sp; i += kUnitThreads) {
     const int m = i / sp, j = i - m * sp;
@@ -556,7 +343,7 @@ __global__ __launch_bounds__(kUnitThreads) void gu_unit_kernel(
 // top-k keyed pass, every neuron kept), d_model a multiple of 2048, on the unit pipeline: the
 // three bf16 pieces of the four tokens are the 12 rows of one MFMA operand tile (row 4 p + m), so
 // the whole input stays in registers. Phase A streams the segment's gate rows, phase B the up rows
-// of the tokens' union; keep decisions, lists and h as cats_ring_kernel forms them. A row's sum is
+// of the tokens' union; keep decisions, lists and h as cats_frag_kernel forms them. A row's sum is
 // its three pieces' sums added in piece order. With every neuron kept the gate and up rows go in
 // one pass (each row's result is the same wherever it sits in the sequence), so a threshold below
 // 0 still gives the dense result bit for bit.
@@ -655,7 +442,7 @@ __global__ __launch_bounds__(kUnitThreads) void cats_unit_kernel(
     const unsigned long long mk = __ballot(keep);
     if (lane == 0) s_keep[m] = mk;
     if (m < B && bidx != nullptr) {
-      if (keep) bidx[((size_t)m * nseg + seg) * kSegPad + __popcll(mk & ((1ull << lane) - 1ull))] = r0 + lane;
+      if (keep) bidx[((size_t)m * nseg + seg) * sp + __popcll(mk & ((1ull << lane) - 1ull))] = r0 + lane;
       if (lane == 0) bcnt[m * nseg + seg] = __popcll(mk);
     }
   }
@@ -697,295 +484,259 @@ __global__ __launch_bounds__(kUnitThreads) void cats_unit_kernel(
   if (seg == nseg - 1) zero_h_tail(hhi, hlo, hs, nseg * sp, kMpad);
 }
 
-// ---- every neuron kept (the dense and condensed FFN of small batches on the exact input) in one
-// ring pass over the segment's gate rows [0, np), up rows [np, 2 np) and the token rows (piece p,
-// token m) at 2 np + p TB + m. Wave w keeps the gate and up sums of 16-neuron tile w & 3 over the
-// K steps of half w >> 2 of each block, in the order in which the two-phase segment kernel below
-// forms them (same K blocks, steps, pieces and token tiles; the halves added in the same order),
-// so its results are bitwise those of the threshold path with t < 0, with one pass over K instead
-// of two.
-template <int TB, int NPM>
-__global__ __launch_bounds__(kBT) void all_ring_kernel(
-    const uint16_t* __restrict__ xp, int B, const uint16_t* __restrict__ wg,
-    const uint16_t* __restrict__ wu, int d, int F, int np, uint16_t* __restrict__ hhi,
-    uint16_t* __restrict__ hlo, int hs, int sp, int32_t* __restrict__ uidx,
-    int32_t* __restrict__ ucnt) {
-  using G = typename AllGeom<TB, NPM>::G;
-  static_assert(G::kRowBytes == CatsGeom<TB, NPM>::G::kRowBytes,
-                "the K blocks of the two-phase kernel, and so its sums");
-  constexpr int MT = (TB + 15) / 16, KS = G::kRowBytes / 2;
-  constexpr int kMpad = 16 * MT;
-  extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
+// ---- the operand-order pipeline of the other batches (any d_model % 256 == 0, up to 64 tokens): one
+// workgroup of eight waves per segment. The weight rows come through registers, two blocks of 256
+// columns ahead, into two LDS buffers (whole runs of a row per request; the 16 rows of an MFMA
+// operand from LDS); wave w multiplies columns 32 w .. + 31 of every block by the x pieces, which
+// it reads from L2 in operand order into registers. The eight waves' sums (an eighth of K each) are
+// added in wave order. A row's result does not depend on its place in the sequence. Bound by HBM; the
+// earlier kernels copied the pieces (up to 4 x 3 token tiles) through an LDS ring next to the weights
+// in every workgroup, which cost more LDS writes than the weights themselves from 17 tokens on.
+// Gate/up, ring -> here: threshold call 14336 x 4096 at 40 tokens 91 -> 68 us, 22671 x 8192 at 40
+// tokens 342 -> 209; dense 15104 x 4608 at 16 tokens 66 -> 43; even at 14336 x 4096 and 16 tokens or
+// fewer in the dense modes (39 -> 39), where the weights alone fill the time; threshold mode 48.5 -> 45.5
+// there. Four blocks ahead instead of two: 47.5, eight: 51; 1024 threads on 512 columns: 48.5.
+constexpr int kFrThreads = 512;
+constexpr int kFrWaves = kFrThreads / kWave;
+constexpr int kFrK = 256;                       // columns per block: one K step per wave
+constexpr int kFrCpr = kFrK / 8;                // 16-byte chunks per row and block
+constexpr int kFrPitch = kFrK * 2 + 16;         // the 16 rows of an operand read: all banks
+constexpr int kFrRowStep = kFrThreads / kFrCpr; // rows between a thread's loads (16)
+static_assert(kFrK / 32 == kFrWaves && kFrRowStep == 16, "one K step per wave, one row tile per load");
+
+template <int MT, int RT>
+struct FrLds {
+  static constexpr int kBuf = 16 * RT * kFrPitch;
+  static constexpr int kRed = kFrWaves * RT * kWave * 16;            // one token tile's partials
+  static constexpr int kRes = 16 * RT * 16 * MT * 4;
+  static constexpr int kBytes = 2 * kBuf > kRed + kRes ? 2 * kBuf : kRed + kRes;
+};
+
+// nrows (<= 16 RT) rows from row_of(r), r < nrows; returns res[16 MT * row + token] in lds. xf: px
+// pieces in operand order (prep_frag_kernel).
+template <int PX, int MT, int RT, class RowOf>
+__device__ __forceinline__ const float* frag_pass(unsigned char* lds, int nrows, RowOf row_of,
+                                                  const uint4* __restrict__ xf, int d) {
+  using S = FrLds<MT, RT>;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int fr = lane & 15, grp = lane >> 4;
-  const int seg = blockIdx.x, nseg = gridDim.x;
-  const int r0 = seg * np;
-  const int nr = min(np, F - r0);  // neurons of this segment (>= 1)
-  const int nblk = (d + KS - 1) / KS;
-  const int tau = wave & 3, kap = wave >> 2;
-  constexpr int kSteps = KS / 32;
-  constexpr int kHalf = kSteps / 2;
-  const int x0 = 2 * np;  // first token row of a slot
-
-  Ring<G> rg(tid, wave, [&](int r) -> const uint16_t* {
-    if (r < np) return wg + (size_t)(r0 + min(r, nr - 1)) * d;
-    if (r < x0) return wu + (size_t)(r0 + min(r - np, nr - 1)) * d;
-    if (r < x0 + 3 * TB) {
-      const int p = (r - x0) / TB, m = (r - x0) % TB;
-      return m < B ? xp + ((size_t)p * kMpad + m) * d : nullptr;
-    }
-    return nullptr;
-  });
-  floatx4_t accg[MT], accu[MT];
+  const int T = (nrows + 15) >> 4;               // row tiles
+  const int nblk = d / kFrK;                     // d % 256 == 0
+  const int ch = tid % kFrCpr, row0 = tid / kFrCpr;
+  const uint4* src[RT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i)  // rows past the last of a tile: the last one again, never used
+    src[i] = reinterpret_cast<const uint4*>(row_of(min(16 * i + row0, nrows - 1))) + ch;
+  constexpr int D = 2;  // blocks in flight, as many as LDS and x buffers
+  uint4 wr[D][RT];
+  auto load_w = [&](uint4(&r)[RT], int b) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+      if (i < T) r[i] = ld_stream(src[i] + b * kFrCpr);
+  };
+  uint4 xa[2][PX][MT];
+  auto load_x = [&](uint4(&r)[PX][MT], int b) {
+#pragma unroll
+    for (int p = 0; p < PX; ++p)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        r[p][mt] = xf[(((size_t)(b * kFrWaves + wave) * PX + p) * MT + mt) * kWave + lane];
+  };
+  floatx4_t acc[RT][MT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[t][mt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  auto step = [&](uint4(&wcur)[RT], uint4(&xcur)[PX][MT], uint4(&xnext)[PX][MT],
+                  int b) {
+    unsigned char* buf = lds + (b & 1) * S::kBuf;
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+      if (i < T) *reinterpret_cast<uint4*>(buf + (16 * i + row0) * kFrPitch + 16 * ch) = wcur[i];
+    if (b + D < nblk) load_w(wcur, b + D);
+    if (b + 1 < nblk) load_x(xnext, b + 1);
+    ring_barrier();  // block b is in its buffer; every wave is done reading block b - 1
+    // every tile of the class, also those past T (stale rows, never used): branches around a tile's
+    // products would split the block between the MFMAs and what reads their results
+    bf16x8_t bw[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+      bw[t] = *reinterpret_cast<const bf16x8_t*>(buf + (16 * t + fr) * kFrPitch + 64 * wave + 16 * grp);
+#pragma unroll
+    for (int p = PX - 1; p >= 0; --p)
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(xcur[p][mt]), bw[t], acc[t][mt], 0, 0, 0);
+  };
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+    if (u < nblk) load_w(wr[u], u);
+  load_x(xa[0], 0);
+  for (int b = 0; b < nblk; b += D) {
+#pragma unroll
+    for (int u = 0; u < D; ++u)
+      if (b + u < nblk) step(wr[u], xa[u], xa[1 - u], b + u);
+  }
+  // the waves' totals, one token tile at a time
+  floatx4_t* red = reinterpret_cast<floatx4_t*>(lds);
+  float* res = reinterpret_cast<float*>(lds + S::kRed);
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-    accg[mt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    accu[mt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  }
-  const int wrow = 16 * tau + fr;  // past np: never stored
-  const bool active = 16 * tau < np;
-  run_ring<G>(ring, rg, nblk, d, x0, [&](const unsigned char* slot) {
-    if (!active) return;
-    bf16x8_t bg[kHalf], bu[kHalf], ax[kHalf][3][MT];
+    __syncthreads();
 #pragma unroll
-    for (int i2 = 0; i2 < kHalf; ++i2) {
-      const int c = 4 * (kap * kHalf + i2) + grp;
-      bg[i2] = *reinterpret_cast<const bf16x8_t*>(slot + wrow * G::kRowBytes + 16 * swz(wrow, c));
-      bu[i2] = *reinterpret_cast<const bf16x8_t*>(slot + (np + wrow) * G::kRowBytes + 16 * swz(np + wrow, c));
+    for (int t = 0; t < RT; ++t)
+      if (t < T) red[(wave * RT + t) * kWave + lane] = acc[t][mt];
+    __syncthreads();
+    for (int i = tid; i < T * kWave; i += kFrThreads) {
+      floatx4_t v = red[i];
 #pragma unroll
-      for (int p = 0; p < 3; ++p)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const int xr = x0 + p * TB + min(16 * mt + fr, TB - 1);
-          ax[i2][p][mt] = *reinterpret_cast<const bf16x8_t*>(slot + xr * G::kRowBytes + 16 * swz(xr, c));
-        }
-    }
-#pragma unroll
-    for (int i2 = 0; i2 < kHalf; ++i2)
-#pragma unroll
-      for (int p = 0; p < 3; ++p)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          accg[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax[i2][p][mt], bg[i2], accg[mt], 0, 0, 0);
-          accu[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax[i2][p][mt], bu[i2], accu[mt], 0, 0, 0);
-        }
-  });
-  // the second K half hands its sums to the first through LDS
-  __syncthreads();
-  floatx4_t* s_h = reinterpret_cast<floatx4_t*>(ring);  // [gate 0..3 | up 4..7][mt][lane]
-  if (kap == 1) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      s_h[(tau * MT + mt) * kWave + lane] = accg[mt];
-      s_h[((4 + tau) * MT + mt) * kWave + lane] = accu[mt];
+      for (int w = 1; w < kFrWaves; ++w) v += red[w * RT * kWave + i];
+      // C layout: lane l holds weight row l & 15 of the tile and tokens 4 (l >> 4) + e
+      const int t = i >> 6, l = i & (kWave - 1);
+      *reinterpret_cast<floatx4_t*>(&res[(16 * t + (l & 15)) * (16 * MT) + 16 * mt + 4 * (l >> 4)]) = v;
     }
   }
   __syncthreads();
-  if (kap == 0) {
-    const int k = 16 * tau + fr;  // position = neuron r0 + k
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const floatx4_t og = s_h[(tau * MT + mt) * kWave + lane];
-      const floatx4_t ou = s_h[((4 + tau) * MT + mt) * kWave + lane];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        accg[mt][r] += og[r];
-        accu[mt][r] += ou[r];
-        const int m = 16 * mt + 4 * grp + r;  // C layout: neuron fr, tokens 4 (lane / 16) + r
-        const float h = (k < nr && m < B) ? silu(accg[mt][r]) * accu[mt][r] : 0.f;
-        if (k < sp) store_h(hhi, hlo, (size_t)m * hs + seg * sp + k, h);
-      }
-    }
-  }
-  // the kept list of every neuron, as the two-phase kernel writes it for t < 0
-  if (tid < nr) uidx[seg * sp + tid] = r0 + tid;
-  if (tid == 0) ucnt[seg] = nr;
-  if (seg == nseg - 1) zero_h_tail(hhi, hlo, hs, nseg * sp, kMpad);
+  return res;
 }
 
-// ---- per-token sparse gate/up over one segment (threshold, top-k gate pass, top-k keyed pass,
-// every neuron kept) on the exact input. Slot rows: the segment's gate (phase A) or union up
-// (phase B) rows [0, np), then the token rows (piece p, token m) at np + p TB + m (zeros past B).
-// Wave w: 16-neuron tile w & 3, K steps of half w >> 2 of each block; the halves are added in a
-// fixed order. The A operand for piece p and tile mt reads token row min(16 mt + r, TB - 1).
-// (The modes are those of cats_unit_kernel above. kModeAll keeps every neuron: the dense and
-// condensed FFN of small batches on the exact input, through the same kernels, and so the same
-// sums, as the threshold path with t < 0.)
+// Dense gate/up on the bf16-rounded input: gate rows [0, np), up rows [np, 2 np) in one pass.
+template <int MT, int RT>
+__global__ __launch_bounds__(kFrThreads, 2) void gu_frag_kernel(
+    const uint4* __restrict__ xf, int B, const uint16_t* __restrict__ wg,
+    const uint16_t* __restrict__ wu, int d, int F, int hs, int np, int sp,
+    uint16_t* __restrict__ hhi, uint16_t* __restrict__ hlo) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_u[];
+  const int n0 = blockIdx.x * np;
+  const float* res = frag_pass<1, MT, RT>(
+      lds_u, 2 * np,
+      [&](int r) {
+        return r < np ? wg + (size_t)min(n0 + r, F - 1) * d : wu + (size_t)min(n0 + r - np, F - 1) * d;
+      },
+      xf, d);
+  for (int i = threadIdx.x; i < 16 * MT * sp; i += kFrThreads) {
+    const int m = i / sp, j = i - m * sp;
+    const bool real = j < np && n0 + j < F && m < B;
+    store_h(hhi, hlo, (size_t)m * hs + (size_t)blockIdx.x * sp + j,
+            real ? silu(res[j * (16 * MT) + m]) * res[(np + j) * (16 * MT) + m] : 0.f);
+  }
+  if (blockIdx.x == gridDim.x - 1) zero_h_tail(hhi, hlo, hs, gridDim.x * sp, 16 * MT);
+}
 
-template <int TB, int MODE, int NPM>
-__global__ __launch_bounds__(kBT) void cats_ring_kernel(
-    const uint16_t* __restrict__ xp, int B, const uint16_t* __restrict__ wg,
+// Per-token sparse gate/up on the exact input, and every neuron kept (kModeAll: the dense and condensed
+// FFN of small batches, gate and up rows in one pass; a row's result is the same wherever it sits,
+// so a threshold below 0 gives the dense result bit for bit). The modes are those of
+// cats_unit_kernel above.
+// RT: row tiles of a segment's np rows, or of its 2 np (kModeAll).
+template <int MT, int RT, int MODE>
+__global__ __launch_bounds__(kFrThreads, 2) void cats_frag_kernel(
+    const uint4* __restrict__ xf, int B, const uint16_t* __restrict__ wg,
     const uint16_t* __restrict__ wu, int d, int F, int np, float t, float* __restrict__ act,
     const unsigned long long* __restrict__ cut, uint16_t* __restrict__ hhi,
     uint16_t* __restrict__ hlo, int hs, int sp, int32_t* __restrict__ uidx,
     int32_t* __restrict__ ucnt, int32_t* __restrict__ bidx, int32_t* __restrict__ bcnt) {
-  using G = typename CatsGeom<TB, NPM>::G;
-  constexpr int MT = (TB + 15) / 16, KS = G::kRowBytes / 2;
   constexpr int kMpad = 16 * MT;
-  extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
-  __shared__ float s_a[kMpad][kSegPad];             // a = SiLU(g) per token and position
-  __shared__ unsigned long long s_keep[kMpad];      // kept positions per token
-  __shared__ int s_u[kSegPad];                      // union positions, ascending
-  __shared__ int s_nu;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_u[];
+  __shared__ float s_a[kMpad][kSegPad];         // a = SiLU(g) per token and position
+  __shared__ unsigned long long s_keep[kMpad];  // kept positions per token
+  __shared__ int s_u[kSegPad];                  // union positions, ascending
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-  const int fr = lane & 15, grp = lane >> 4;
   const int seg = blockIdx.x, nseg = gridDim.x;
   const int r0 = seg * np;
   const int nr = min(np, F - r0);  // neurons of this segment (>= 1)
-  const int nblk = (d + KS - 1) / KS;
-  const int tau = wave & 3, kap = wave >> 2;
-  constexpr int kSteps = KS / 32;  // 32-wide K steps per block
-  static_assert(kSteps % 2 == 0 || kSteps == 2, "the K steps split in two halves");
-  constexpr int kHalf = kSteps / 2;
 
-  // ring over the segment's rows w_row(j), j < np, and the token pieces; per-wave sums, the
-  // second K half added into the first
-  auto ring_pass = [&](auto w_row, floatx4_t (&acc)[MT]) {
-    Ring<G> rg(tid, wave, [&](int r) -> const uint16_t* {
-      if (r < np) return w_row(r);
-      if (r < np + 3 * TB) {
-        const int p = (r - np) / TB, m = (r - np) % TB;
-        return m < B ? xp + ((size_t)p * kMpad + m) * d : nullptr;
-      }
-      return nullptr;
-    });
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    const int wrow = 16 * tau + fr;  // past np: never stored
-    const bool active = 16 * tau < np;  // a tile past the segment's rows skips its MFMAs
-    run_ring<G>(ring, rg, nblk, d, np, [&](const unsigned char* slot) {
-      if (!active) return;
-      bf16x8_t bw[kHalf], ax[kHalf][3][MT];
-#pragma unroll
-      for (int i2 = 0; i2 < kHalf; ++i2) {  // every operand of the block first, then the MFMAs
-        const int c = 4 * (kap * kHalf + i2) + grp;
-        bw[i2] = *reinterpret_cast<const bf16x8_t*>(slot + wrow * G::kRowBytes + 16 * swz(wrow, c));
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            const int xr = np + p * TB + min(16 * mt + fr, TB - 1);
-            ax[i2][p][mt] = *reinterpret_cast<const bf16x8_t*>(slot + xr * G::kRowBytes + 16 * swz(xr, c));
-          }
-      }
-#pragma unroll
-      for (int i2 = 0; i2 < kHalf; ++i2)
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax[i2][p][mt], bw[i2], acc[mt], 0, 0, 0);
-    });
-    // the second K half hands its sums to the first through LDS (the ring is free afterwards)
-    __syncthreads();
-    floatx4_t* s_h = reinterpret_cast<floatx4_t*>(ring);  // [tile][mt][lane]
-    if (kap == 1) {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) s_h[(tau * MT + mt) * kWave + lane] = acc[mt];
+  if (MODE == kModeAll) {
+    const float* res = frag_pass<3, MT, RT>(
+        lds_u, 2 * np,
+        [&](int r) {
+          return r < np ? wg + (size_t)(r0 + min(r, nr - 1)) * d : wu + (size_t)(r0 + min(r - np, nr - 1)) * d;
+        },
+        xf, d);
+    for (int i = tid; i < kMpad * sp; i += kFrThreads) {
+      const int m = i / sp, k = i - m * sp;
+      const float h = (m < B && k < nr) ? silu(res[k * kMpad + m]) * res[(np + k) * kMpad + m] : 0.f;
+      store_h(hhi, hlo, (size_t)m * hs + (size_t)seg * sp + k, h);
     }
-    __syncthreads();
-    if (kap == 0) {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const floatx4_t o = s_h[(tau * MT + mt) * kWave + lane];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[mt][r] += o[r];
-      }
-    }
-    __syncthreads();  // the ring may be refilled by the next pass
-  };
+    // the kept list of every neuron, as the threshold path writes it for t < 0
+    if (tid < nr) uidx[seg * sp + tid] = r0 + tid;
+    if (tid == 0) ucnt[seg] = nr;
+    if (seg == nseg - 1) zero_h_tail(hhi, hlo, hs, nseg * sp, kMpad);
+    return;
+  }
 
   // ---- phase A: the gate (threshold mode and the top-k gate pass) or the stored activations
   if (MODE != kModeKeyed) {
-    floatx4_t acc[MT];
-    ring_pass([&](int j) { return wg + (size_t)(r0 + min(j, nr - 1)) * d; }, acc);
-    if (kap == 0) {
-      const int j = 16 * tau + fr;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = 16 * mt + 4 * grp + r;  // C layout: neuron fr, tokens 4 (lane / 16) + r
-          const float a = silu(acc[mt][r]);
-          if (MODE == kModeAct) {
-            if (m < B && j < nr) act[(size_t)m * F + r0 + j] = a;
-          } else {
-            s_a[m][j] = a;
-          }
-        }
+    const float* res = frag_pass<3, MT, RT>(
+        lds_u, np, [&](int r) { return wg + (size_t)(r0 + min(r, nr - 1)) * d; }, xf, d);
+    for (int i = tid; i < kMpad * np; i += kFrThreads) {
+      const int j = i % np, m = i / np;
+      const float a = silu(res[j * kMpad + m]);
+      if (MODE == kModeAct) {
+        if (m < B && j < nr) act[(size_t)m * F + r0 + j] = a;
+      } else {
+        s_a[m][j] = a;
+      }
     }
     if (MODE == kModeAct) return;  // uniform
-    __syncthreads();
   } else {
-    for (int i = tid; i < kMpad * kSegPad; i += kBT) {
+    for (int i = tid; i < kMpad * kSegPad; i += kFrThreads) {
       const int m = i / kSegPad, j = i % kSegPad;
       s_a[m][j] = (m < B && j < nr) ? act[(size_t)m * F + r0 + j] : 0.f;
     }
-    __syncthreads();
   }
+  __syncthreads();
 
   // ---- keep decisions per token (a wave ballot over the segment's positions), per-token lists
-  for (int m = wave; m < kMpad; m += kBT / kWave) {
-    const float a = s_a[m][lane];
+  for (int m = wave; m < kMpad; m += kFrWaves) {
     bool keep = false;
     if (m < B && lane < nr) {
+      const float a = s_a[m][lane];
       if (MODE == kModeKeyed) keep = topk_key(a, r0 + lane) >= cut[m];
-      else if (MODE == kModeAll) keep = true;
       else keep = fabsf(a) > t;
     }
     const unsigned long long mk = __ballot(keep);
     if (lane == 0) s_keep[m] = mk;
     if (m < B && bidx != nullptr) {
-      if (keep) bidx[((size_t)m * nseg + seg) * kSegPad + __popcll(mk & ((1ull << lane) - 1ull))] = r0 + lane;
+      if (keep) bidx[((size_t)m * nseg + seg) * sp + __popcll(mk & ((1ull << lane) - 1ull))] = r0 + lane;
       if (lane == 0) bcnt[m * nseg + seg] = __popcll(mk);
     }
   }
   __syncthreads();
-  // ---- union of the tokens' kept positions, ascending
-  if (wave == 0) {
-    unsigned long long un = 0ull;
-    for (int m = 0; m < B && m < kMpad; ++m) un |= s_keep[m];
-    const bool in = (un >> lane) & 1ull;
-    const int pos = __popcll(un & ((1ull << lane) - 1ull));
-    if (in) {
-      s_u[pos] = lane;
-      uidx[seg * sp + pos] = r0 + lane;
-    }
-    if (lane == 0) {
-      s_nu = __popcll(un);
-      ucnt[seg] = __popcll(un);
-    }
+  // ---- union of the tokens' kept positions, ascending: every wave forms it for itself
+  unsigned long long un = lane < B ? s_keep[lane] : 0ull;
+  static_assert(kMpad <= kWave, "a lane per token");
+  for (int off = kWave / 2; off > 0; off >>= 1) un |= __shfl_xor(un, off, kWave);
+  const int nu = __popcll(un);
+  const int pos = __popcll(un & ((1ull << lane) - 1ull));
+  if ((un >> lane) & 1ull) {
+    s_u[pos] = lane;  // the same value from every wave
+    if (wave == 0) uidx[seg * sp + pos] = r0 + lane;
   }
-  __syncthreads();
-  const int nu = s_nu;
+  if (tid == 0) ucnt[seg] = nu;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the wave's own list, read across its lanes
 
   // ---- phase B: the up rows of the union only; h = a u where the token keeps the neuron
-  floatx4_t acc[MT];
-  if (nu > 0) {  // uniform
-    // union rows past nu load the segment's first union row again (in L2, never stored)
-    ring_pass([&](int k) { return wu + (size_t)(r0 + s_u[min(k, nu - 1)]) * d; }, acc);
-  }
-  if (kap == 0) {
-    const int k = 16 * tau + fr;  // union position
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = 16 * mt + 4 * grp + r;
-        float h = 0.f;
-        if (k < nu) {
-          const int j = s_u[k];
-          if ((s_keep[m] >> j) & 1ull) h = s_a[m][j] * acc[mt][r];
-        }
-        if (k < sp) store_h(hhi, hlo, (size_t)m * hs + seg * sp + k, h);  // 0 past nu
-      }
+  const float* res = nullptr;
+  if (nu > 0)  // uniform
+    res = frag_pass<3, MT, RT>(
+        lds_u, nu, [&](int k) { return wu + (size_t)(r0 + s_u[k]) * d; }, xf, d);
+  for (int i = tid; i < kMpad * sp; i += kFrThreads) {
+    const int m = i / sp, k = i - m * sp;
+    float h = 0.f;
+    if (m < B && k < nu) {
+      const int j = s_u[k];
+      if ((s_keep[m] >> j) & 1ull) h = s_a[m][j] * res[k * kMpad + m];
+    }
+    store_h(hhi, hlo, (size_t)m * hs + (size_t)seg * sp + k, h);  // 0 past nu
   }
   if (seg == nseg - 1) zero_h_tail(hhi, hlo, hs, nseg * sp, kMpad);
 }
 
 // ---- down product: Y_partial[rho][m][c] over one 256-column tile and one range of 64-row blocks.
 // Block b is positions 64 b .. + 63 of the segment layout (segment s owns positions s sp .. +
-// sp - 1, sp in {16, 32, 64}). Whole segments (GATHER = 0, the dense gate/up kernel): position
+// sp - 1, sp in {16, 32, 48, 64}). Whole segments (GATHER = 0, the dense gate/up kernel): position
 // s sp + k is W_down row s np + k for k < np (and below d_ff). Kept lists (GATHER = 1): it is row
 // uidx[s sp + k] for k < ucnt[s]. Any other position has no row (h = 0 there; W_down row 0 is
 // loaded, an L2 hit). The 64-row blocks of whole segments measured faster than blocks of 64
@@ -1169,7 +920,7 @@ BatchLayout batch_layout(int B, int d, int F, int px) {
   const Seg s = seg_of(F);
   L.nseg = s.nseg;
   L.np = s.np;
-  L.sp = s.np <= 16 ? 16 : (s.np <= 32 ? 32 : kSegPad);
+  L.sp = seg_positions(L.np);
   L.nblocks = (L.nseg * L.sp + kDnBlock - 1) / kDnBlock;
   L.hs = L.nblocks * kDnBlock;
   // down ranges: about 256 workgroups in all, at most 16 blocks per range (the gathered row list)
@@ -1181,7 +932,7 @@ BatchLayout batch_layout(int B, int d, int F, int px) {
   L.hlo = c.take((size_t)L.mpad * L.hs * 2);
   L.uidx = c.take((size_t)L.hs * 4);
   L.ucnt = c.take((size_t)L.nseg * 4);
-  L.bidx = c.take((size_t)B * L.nseg * kSegPad * 4);
+  L.bidx = c.take((size_t)B * L.nseg * L.sp * 4);
   L.bcnt = c.take((size_t)B * L.nseg * 4);
   L.part = c.take((size_t)L.gr * B * d * 4);
   L.total = c.off;
@@ -1195,18 +946,6 @@ hipError_t allow_dynamic_lds(const void* kernel, int bytes) {
   return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-template <int TB, int NPM>
-hipError_t launch_gu_np(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
-                        const uint16_t* wg, const uint16_t* wu, int d, int F, uint16_t* hhi,
-                        uint16_t* hlo) {
-  using G = typename GuGeom<TB, NPM>::G;
-  static const hipError_t attr =
-      allow_dynamic_lds(reinterpret_cast<const void*>(gu_ring_kernel<TB, NPM>), kGuLds);
-  if (attr != hipSuccess) return attr;
-  klaunch(gu_ring_kernel<TB, NPM>, L.nseg, kBT, (uint32_t)(G::kSlots * G::kSlotBytes), stream, xp, B,
-          wg, wu, d, F, L.hs, L.np, L.sp, hhi, hlo);
-  return hipGetLastError();
-}
 template <int NSPAN>
 hipError_t launch_gu_unit_n(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
                             const uint16_t* wg, const uint16_t* wu, int d, int F, uint16_t* hhi,
@@ -1231,65 +970,52 @@ hipError_t launch_gu_unit(const BatchLayout& L, hipStream_t stream, const uint16
     default: return hipErrorInvalidValue;
   }
 }
-// short segments (np <= kSegSmall) of the small token classes take the deeper ring
-template <int TB>
-hipError_t launch_gu(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
-                     const uint16_t* wg, const uint16_t* wu, int d, int F, uint16_t* hhi,
-                     uint16_t* hlo) {
-  if (TB <= 16 && L.np <= kSegSmall)
-    return launch_gu_np<TB, (TB <= 16 ? kSegSmall : kSegN)>(L, stream, xp, B, wg, wu, d, F, hhi, hlo);
-  return launch_gu_np<TB, kSegN>(L, stream, xp, B, wg, wu, d, F, hhi, hlo);
-}
+constexpr int kSegSmall = 32;  // segments of at most this many neurons take fewer row tiles
 
-template <int TB, int MODE, int NPM>
-hipError_t launch_cats_np(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
-                          const uint16_t* wg, const uint16_t* wu, int d, int F, float t, float* act,
-                          const unsigned long long* cut, uint16_t* hhi, uint16_t* hlo,
-                          int32_t* uidx, int32_t* ucnt, int32_t* bidx, int32_t* bcnt) {
-  using G = typename CatsGeom<TB, NPM>::G;
-  static const hipError_t attr =
-      allow_dynamic_lds(reinterpret_cast<const void*>(cats_ring_kernel<TB, MODE, NPM>), kCatsLds);
+template <int MT, int RT>
+hipError_t launch_gu_frag_n(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
+                            const uint16_t* wg, const uint16_t* wu, int d, int F, uint16_t* hhi,
+                            uint16_t* hlo) {
+  constexpr int kLds = FrLds<MT, RT>::kBytes;
+  static const hipError_t attr = allow_dynamic_lds(reinterpret_cast<const void*>(gu_frag_kernel<MT, RT>), kLds);
   if (attr != hipSuccess) return attr;
-  klaunch(cats_ring_kernel<TB, MODE, NPM>, L.nseg, kBT, (uint32_t)(G::kSlots * G::kSlotBytes), stream,
-          xp, B, wg, wu, d, F, L.np, t, act, cut, hhi, hlo, L.hs, L.sp, uidx, ucnt, bidx, bcnt);
+  klaunch((gu_frag_kernel<MT, RT>), L.nseg, kFrThreads, (uint32_t)kLds, stream,
+          reinterpret_cast<const uint4*>(xp), B, wg, wu, d, F, L.hs, L.np, L.sp, hhi, hlo);
   return hipGetLastError();
 }
-template <int TB, int MODE>
-hipError_t launch_cats(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
-                       const uint16_t* wg, const uint16_t* wu, int d, int F, float t, float* act,
-                       const unsigned long long* cut, uint16_t* hhi, uint16_t* hlo,
-                       int32_t* uidx, int32_t* ucnt, int32_t* bidx, int32_t* bcnt) {
-  if (TB <= 16 && L.np <= kSegSmall)
-    return launch_cats_np<TB, MODE, (TB <= 16 ? kSegSmall : kSegN)>(L, stream, xp, B, wg, wu, d, F, t, act,
-                                                                     cut, hhi, hlo, uidx, ucnt, bidx, bcnt);
-  return launch_cats_np<TB, MODE, kSegN>(L, stream, xp, B, wg, wu, d, F, t, act, cut, hhi, hlo, uidx,
-                                         ucnt, bidx, bcnt);
+template <int MT>
+hipError_t launch_gu_frag(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
+                          const uint16_t* wg, const uint16_t* wu, int d, int F, uint16_t* hhi,
+                          uint16_t* hlo) {
+  return L.np <= kSegSmall ? launch_gu_frag_n<MT, 4>(L, stream, xp, B, wg, wu, d, F, hhi, hlo)
+                           : launch_gu_frag_n<MT, kUnitTiles>(L, stream, xp, B, wg, wu, d, F, hhi, hlo);
 }
 
-template <int TB, int NPM>
-hipError_t launch_all_np(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
-                         const uint16_t* wg, const uint16_t* wu, int d, int F, uint16_t* hhi,
-                         uint16_t* hlo, int32_t* uidx, int32_t* ucnt) {
-  using G = typename AllGeom<TB, NPM>::G;
+template <int MT, int RT, int MODE>
+hipError_t launch_cats_frag_n(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
+                              const uint16_t* wg, const uint16_t* wu, int d, int F, float t, float* act,
+                              const unsigned long long* cut, uint16_t* hhi, uint16_t* hlo,
+                              int32_t* uidx, int32_t* ucnt, int32_t* bidx, int32_t* bcnt) {
+  constexpr int kLds = FrLds<MT, RT>::kBytes;
   static const hipError_t attr =
-      allow_dynamic_lds(reinterpret_cast<const void*>(all_ring_kernel<TB, NPM>), kCatsLds);
+      allow_dynamic_lds(reinterpret_cast<const void*>(cats_frag_kernel<MT, RT, MODE>), kLds);
   if (attr != hipSuccess) return attr;
-  klaunch(all_ring_kernel<TB, NPM>, L.nseg, kBT, (uint32_t)(G::kSlots * G::kSlotBytes), stream, xp, B,
-          wg, wu, d, F, L.np, hhi, hlo, L.hs, L.sp, uidx, ucnt);
+  klaunch((cats_frag_kernel<MT, RT, MODE>), L.nseg, kFrThreads, (uint32_t)kLds, stream,
+          reinterpret_cast<const uint4*>(xp), B, wg, wu, d, F, L.np, t, act, cut, hhi, hlo, L.hs, L.sp, uidx,
+          ucnt, bidx, bcnt);
   return hipGetLastError();
 }
-
-hipError_t launch_gu_tb(int B, const BatchLayout& L, hipStream_t stream, const uint16_t* xp,
-                        const uint16_t* wg, const uint16_t* wu, int d, int F, uint16_t* hhi,
-                        uint16_t* hlo) {
-  switch (token_class(B)) {
-    case 4: return launch_gu<4>(L, stream, xp, B, wg, wu, d, F, hhi, hlo);
-    case 8: return launch_gu<8>(L, stream, xp, B, wg, wu, d, F, hhi, hlo);
-    case 16: return launch_gu<16>(L, stream, xp, B, wg, wu, d, F, hhi, hlo);
-    case 32: return launch_gu<32>(L, stream, xp, B, wg, wu, d, F, hhi, hlo);
-    case 48: return launch_gu<48>(L, stream, xp, B, wg, wu, d, F, hhi, hlo);
-    default: return launch_gu<64>(L, stream, xp, B, wg, wu, d, F, hhi, hlo);
-  }
+template <int MT, int MODE>
+hipError_t launch_cats_frag(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
+                            const uint16_t* wg, const uint16_t* wu, int d, int F, float t, float* act,
+                            const unsigned long long* cut, uint16_t* hhi, uint16_t* hlo,
+                            int32_t* uidx, int32_t* ucnt, int32_t* bidx, int32_t* bcnt) {
+  constexpr int kSmall = MODE == kModeAll ? 4 : 2, kLarge = MODE == kModeAll ? kUnitTiles : kCatsUnitTiles;
+  return L.np <= kSegSmall
+             ? launch_cats_frag_n<MT, kSmall, MODE>(L, stream, xp, B, wg, wu, d, F, t, act, cut, hhi, hlo, uidx,
+                                                    ucnt, bidx, bcnt)
+             : launch_cats_frag_n<MT, kLarge, MODE>(L, stream, xp, B, wg, wu, d, F, t, act, cut, hhi, hlo, uidx,
+                                                    ucnt, bidx, bcnt);
 }
 
 // the unit kernel of the exact-input modes: at most 4 tokens, d_model = 2048, 4096, 6144 or 8192
@@ -1335,17 +1061,17 @@ hipError_t launch_cats_tb(int B, const BatchLayout& L, hipStream_t stream, const
   if (cats_unit_ok(B, d))
     return launch_cats_unit<MODE>(L, stream, xp, B, wg, wu, d, F, t, act, cut, hhi, hlo, uidx, ucnt,
                                   bidx, bcnt);
-#define SIRIUS_CATS_TB(TBV)                                                                     \
-  case TBV:                                                                                     \
-    return launch_cats<TBV, MODE>(L, stream, xp, B, wg, wu, d, F, t, act, cut, hhi, hlo, uidx,  \
-                                  ucnt, bidx, bcnt);
-  switch (token_class(B)) {
-    SIRIUS_CATS_TB(4) SIRIUS_CATS_TB(8) SIRIUS_CATS_TB(16) SIRIUS_CATS_TB(32) SIRIUS_CATS_TB(48)
-    default:
-      return launch_cats<64, MODE>(L, stream, xp, B, wg, wu, d, F, t, act, cut, hhi, hlo, uidx,
-                                   ucnt, bidx, bcnt);
+#define SIRIUS_CATS_MT(MTV)                                                                     \
+  case MTV:                                                                                     \
+    return launch_cats_frag<MTV, MODE>(L, stream, xp, B, wg, wu, d, F, t, act, cut, hhi, hlo,   \
+                                       uidx, ucnt, bidx, bcnt);
+  if constexpr (MODE == kModeAll) {  // every neuron kept: fewer than 8 tokens
+    switch (batch_mt(B)) { SIRIUS_CATS_MT(1) }
+  } else {
+    switch (batch_mt(B)) { SIRIUS_CATS_MT(1) SIRIUS_CATS_MT(2) SIRIUS_CATS_MT(3) SIRIUS_CATS_MT(4) }
   }
-#undef SIRIUS_CATS_TB
+  return hipErrorInvalidValue;
+#undef SIRIUS_CATS_MT
 }
 
 }  // namespace
@@ -1373,6 +1099,7 @@ hipError_t launch_ffn_batch(const float* x, int B, const uint16_t* wg, const uin
   int32_t* bcnt = lists ? reinterpret_cast<int32_t*>(ws + L.bcnt) : nullptr;
   float* part = reinterpret_cast<float*>(ws + L.part);
   const bool thr = mode == kFfnModeThreshold, topk = mode == kFfnModeTopK;
+  const bool unit = exact ? cats_unit_ok(B, d) : gu_unit_ok(B, d);  // else the operand-order pipeline
   const char* pfx_prep = "batch_prep";
   const char* pfx_gu = topk ? "batch_topk_up"
                        : thr ? "batch_cats_up"
@@ -1382,25 +1109,31 @@ hipError_t launch_ffn_batch(const float* x, int B, const uint16_t* wg, const uin
   hipError_t e;
   {
     ProfScope prof(pfx_prep, stream);
-    if (L.px == 3) klaunch(prep_pieces_kernel<3>, L.mpad, 256, 0, stream, x, B, d, L.mpad, norm_eps, xp);
+    if (!unit) e = launch_prep_frag(x, B, d, norm_eps, L.px, reinterpret_cast<char*>(xp), stream);
+    else if (L.px == 3) klaunch(prep_pieces_kernel<3>, L.mpad, 256, 0, stream, x, B, d, L.mpad, norm_eps, xp);
     else klaunch(prep_pieces_kernel<1>, L.mpad, 256, 0, stream, x, B, d, L.mpad, norm_eps, xp);
+    if (!unit && e != hipSuccess) return e;
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   {
     ProfScope prof(pfx_gu, stream);
     if (!exact) {
-      e = gu_unit_ok(B, d) ? launch_gu_unit(L, stream, xp, B, wg, wu, d, F, hhi, hlo)
-                           : launch_gu_tb(B, L, stream, xp, wg, wu, d, F, hhi, hlo);
+      if (unit) {
+        e = launch_gu_unit(L, stream, xp, B, wg, wu, d, F, hhi, hlo);
+      } else {
+        switch (mt) {
+          case 1: e = launch_gu_frag<1>(L, stream, xp, B, wg, wu, d, F, hhi, hlo); break;
+          case 2: e = launch_gu_frag<2>(L, stream, xp, B, wg, wu, d, F, hhi, hlo); break;
+          case 3: e = launch_gu_frag<3>(L, stream, xp, B, wg, wu, d, F, hhi, hlo); break;
+          default: e = launch_gu_frag<4>(L, stream, xp, B, wg, wu, d, F, hhi, hlo); break;
+        }
+      }
     } else if (thr) {
       e = launch_cats_tb<kModeThr>(B, L, stream, xp, wg, wu, d, F, t, nullptr, nullptr, hhi, hlo,
                                    uidx, ucnt, bidx, bcnt);
     } else if (topk) {
       e = launch_cats_tb<kModeKeyed>(B, L, stream, xp, wg, wu, d, F, 0.f, const_cast<float*>(act),
                                      cut, hhi, hlo, uidx, ucnt, bidx, bcnt);
-    } else if (token_class(B) <= 8 && L.np <= kSegSmall && !cats_unit_ok(B, d)) {  // every neuron kept: one ring pass
-      e = token_class(B) == 4
-              ? launch_all_np<4, kSegSmall>(L, stream, xp, B, wg, wu, d, F, hhi, hlo, uidx, ucnt)
-              : launch_all_np<8, kSegSmall>(L, stream, xp, B, wg, wu, d, F, hhi, hlo, uidx, ucnt);
     } else {
       e = launch_cats_tb<kModeAll>(B, L, stream, xp, wg, wu, d, F, 0.f, nullptr, nullptr, hhi, hlo,
                                    uidx, ucnt, bidx, bcnt);
@@ -1425,7 +1158,7 @@ hipError_t launch_ffn_batch(const float* x, int B, const uint16_t* wg, const uin
   }
   ProfScope prof(pfx_red, stream);
   if (lists)
-    return launch_reduce(part, L.gr, B, d, resid, y, stream, F, L.nseg, kSegPad, bidx, bcnt,
+    return launch_reduce(part, L.gr, B, d, resid, y, stream, F, L.nseg, L.sp, bidx, bcnt,
                          active_idx, active_cnt);
   return launch_reduce(part, L.gr, B, d, resid, y, stream);
 }
@@ -1438,8 +1171,13 @@ hipError_t launch_batch_act(const float* x, int B, const uint16_t* wg, int d, in
   hipError_t e;
   {
     ProfScope prof("batch_topk_prep", stream);
-    klaunch(prep_pieces_kernel<3>, L.mpad, 256, 0, stream, x, B, d, L.mpad, norm_eps, xp);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (cats_unit_ok(B, d)) {
+      klaunch(prep_pieces_kernel<3>, L.mpad, 256, 0, stream, x, B, d, L.mpad, norm_eps, xp);
+      e = hipGetLastError();
+    } else {
+      e = launch_prep_frag(x, B, d, norm_eps, 3, reinterpret_cast<char*>(xp), stream);
+    }
+    if (e != hipSuccess) return e;
   }
   ProfScope prof("batch_topk_gate", stream);
   return launch_cats_tb<kModeAct>(B, L, stream, xp, wg, nullptr, d, F, 0.f, act, nullptr, nullptr,

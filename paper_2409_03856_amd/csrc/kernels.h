@@ -119,13 +119,13 @@ hipError_t launch_ffn_mfma(const float* x, int B, const uint16_t* wg, const uint
                            const uint16_t* wd, int d, int F, float norm_eps, const float* resid,
                            float* y, char* ws, const MfmaLayout& L, hipStream_t stream);
 
-// ---- batched FFN on MFMA rings (2 <= B <= 64, d_model % 256 == 0): dense / condensed with the
+// ---- batched FFN on MFMA (2 <= B <= 64, d_model % 256 == 0): dense / condensed with the
 // input as px bf16 pieces (1: rounded to bf16; 3: exact fp32), per-token threshold or top-k
 // sparsity (three pieces) reading up and down rows of the tokens' union only
 struct BatchLayout {
   int mpad, px;      // tokens padded to whole 16-token tiles; input pieces
   int nseg, np;      // gate/up segments and neurons per segment (<= 56)
-  int sp;            // positions per segment in the segment layout (16, 32 or 64)
+  int sp;            // positions per segment in the segment layout (16, 32, 48 or 64)
   int hs;            // h row stride: nseg * sp rounded up to whole 64-position down blocks
   int nblocks, gr;   // 64-position down blocks and down ranges
   size_t xp, hhi, hlo, uidx, ucnt, bidx, bcnt, part, total;  // workspace offsets / size
@@ -256,6 +256,9 @@ hipError_t launch_linear(const float* x, const uint16_t* W, int K, int N, const 
 // The same products (norm_eps >= 0: of the normalised rows) for a chunk of 2..64 tokens on MFMA,
 // every weight read once per call; linear_mfma_ws(n, K) bytes of workspace, K % 8 == 0, K <= 8192.
 size_t linear_mfma_ws(int n, int K);
+// The rows of x (norm_eps >= 0: normalised) as 1..3 bf16 pieces in MFMA operand order,
+// [K / 32 rounded up][piece][16-token tile][lane][8]; zero past n and K. K % 8 == 0, K <= 8192.
+hipError_t launch_prep_frag(const float* x, int n, int K, float norm_eps, int pieces, char* xf, hipStream_t s);
 hipError_t launch_linear_mfma(const float* x, int n, int K, float norm_eps, const uint16_t* Wq,
                               int Nq, const uint16_t* Wk, const uint16_t* Wv, int Nkv,
                               const float* resid, float* yq, uint16_t* yk, uint16_t* yv, char* ws,

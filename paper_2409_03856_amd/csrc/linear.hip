@@ -4,7 +4,8 @@
 //
 //  prep_frag_kernel        x -> optional RMSNorm -> three bf16 pieces (hi + mid + lo = x exactly,
 //                          each the bf16 rounding of what the previous ones leave, so the MFMA
-//                          products of the pieces sum to the fp32 product), stored in the order
+//                          products of the pieces sum to the fp32 product; the first alone is x
+//                          rounded to bf16, the batched FFN's dense input), stored in the order
 //                          in which the lanes of an MFMA take them, zero past the last token
 //                          and past K.
 //  linear_mfma_kernel<..>  one workgroup per 16 RT weight rows: the rows stream through LDS in
@@ -32,63 +33,63 @@ constexpr int kLmWaves = kLmThreads / kWave;
 constexpr int kPieces = 3;
 
 // x pieces: [K step of 32][piece][16-token tile][lane][8 values]; lane = 16 (k % 32 / 8) + m % 16.
-// One workgroup per padded token row. The RMSNorm sums are those of rmsnorm_vec_kernel (thread t
-// takes float4s t + 256 u in ascending order, the wave sums in wave order), so the normalised row
-// is bit for bit that kernel's; the row then passes through LDS so that a thread holds the eight
-// values of one operand chunk.
-__global__ __launch_bounds__(256) void prep_frag_kernel(const float* __restrict__ x, int n, int K,
-                                                        int ksteps, float norm_eps, int MT,
-                                                        uint4* __restrict__ xf) {
-  constexpr int kPer = 8;  // K <= 8192
+// One workgroup per padded token row, which passes through LDS. The RMSNorm sums are those of
+// rmsnorm_vec_kernel (thread t of 256 takes float4s t + 256 u in ascending order, the wave sums in
+// wave order), so the normalised row is bit for bit that kernel's; then each thread forms the pieces
+// of one operand chunk of eight values. Bound by latency: 1024 threads, of which the first 256 form
+// the sums, take 4.7 us at 4096 columns and 6-7 at 8192 (256 threads: 5.5 and 8.2-9.5).
+constexpr int kPrepThreads = 1024;
+__global__ __launch_bounds__(kPrepThreads) void prep_frag_kernel(const float* __restrict__ x, int n, int K,
+                                                                 int ksteps, float norm_eps, int MT,
+                                                                 int pieces, uint4* __restrict__ xf) {
   __shared__ float s_w[4];
   __shared__ float4 s_x[2048];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int m = blockIdx.x, mt = m >> 4;
   const int k4 = K >> 2, k8 = K >> 3;
+  float inv = 1.f;
   if (m < n) {  // uniform over the workgroup
     const float4* xr = reinterpret_cast<const float4*>(x + (size_t)m * K);
-    float4 v[kPer];
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int e = tid + 256 * u;
-      v[u] = (e < k4) ? xr[e] : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int u = 0; u < 2; ++u) {  // K <= 8192
+      const int e = tid + kPrepThreads * u;
+      if (e < k4) s_x[e] = xr[e];
     }
-    float inv = 1.f;
+    __syncthreads();
     if (norm_eps >= 0.f) {
-      float ss = 0.f;
+      if (wave < 4) {
+        float ss = 0.f;
 #pragma unroll
-      for (int u = 0; u < kPer; ++u) {
-        ss = fmaf(v[u].x, v[u].x, ss);
-        ss = fmaf(v[u].y, v[u].y, ss);
-        ss = fmaf(v[u].z, v[u].z, ss);
-        ss = fmaf(v[u].w, v[u].w, ss);
+        for (int u = 0; u < 8; ++u) {
+          const int e = tid + 256 * u;
+          const float4 v = (e < k4) ? s_x[e] : make_float4(0.f, 0.f, 0.f, 0.f);
+          ss = fmaf(v.x, v.x, ss);
+          ss = fmaf(v.y, v.y, ss);
+          ss = fmaf(v.z, v.z, ss);
+          ss = fmaf(v.w, v.w, ss);
+        }
+        ss = wave_sum(ss);
+        if (lane == 0) s_w[wave] = ss;
       }
-      ss = wave_sum(ss);
-      if (lane == 0) s_w[wave] = ss;
       __syncthreads();
       const float tot = ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
       inv = 1.0f / sqrtf(tot / (float)K + norm_eps);
     }
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int e = tid + 256 * u;
-      if (e < k4) s_x[e] = make_float4(v[u].x * inv, v[u].y * inv, v[u].z * inv, v[u].w * inv);
-    }
-    __syncthreads();
   }
-  for (int c = tid; c < 4 * ksteps; c += 256) {  // operand chunk c: values 8 c .. 8 c + 7
+  for (int c = tid; c < 4 * ksteps; c += kPrepThreads) {  // operand chunk c: values 8 c .. 8 c + 7
     float r[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (m < n && c < k8) {
       const float4 a = s_x[2 * c], b = s_x[2 * c + 1];
-      r[0] = a.x; r[1] = a.y; r[2] = a.z; r[3] = a.w;
-      r[4] = b.x; r[5] = b.y; r[6] = b.z; r[7] = b.w;
+      r[0] = a.x * inv; r[1] = a.y * inv; r[2] = a.z * inv; r[3] = a.w * inv;
+      r[4] = b.x * inv; r[5] = b.y * inv; r[6] = b.z * inv; r[7] = b.w * inv;
     }
 #pragma unroll
     for (int p = 0; p < kPieces; ++p) {
+      if (p == pieces) break;  // uniform
       uint32_t b[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) b[e] = take_piece(r[e]);
-      xf[(((size_t)(c >> 2) * kPieces + p) * MT + mt) * kWave + 16 * (c & 3) + (m & 15)] =
+      xf[(((size_t)(c >> 2) * pieces + p) * MT + mt) * kWave + 16 * (c & 3) + (m & 15)] =
           make_uint4(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16),
                      b[6] | (b[7] << 16));
     }
@@ -237,6 +238,18 @@ __global__ __launch_bounds__(kLmThreads) void linear_mfma_kernel(const uint4* __
   }
 }
 
+}  // namespace
+
+hipError_t launch_prep_frag(const float* x, int n, int K, float eps, int pieces, char* xf, hipStream_t s) {
+  if ((K & 7) != 0 || K > 8192 || n < 1 || pieces < 1 || pieces > kPieces) return hipErrorInvalidValue;
+  const int MT = ceil_div(n, 16);
+  klaunch(prep_frag_kernel, 16 * MT, kPrepThreads, 0, s, x, n, K, ceil_div(K, 32), eps, MT, pieces,
+          reinterpret_cast<uint4*>(xf));
+  return hipGetLastError();
+}
+
+namespace {
+
 template <int MT>
 hipError_t launch_t(const float* x, int n, int K, float eps, const LinearOut& o, char* ws,
                     hipStream_t s) {
@@ -244,8 +257,7 @@ hipError_t launch_t(const float* x, int n, int K, float eps, const LinearOut& o,
   uint4* xf = reinterpret_cast<uint4*>(ws);
   {
     ProfScope prof("linear_prep", s);
-    klaunch(prep_frag_kernel, 16 * MT, 256, 0, s, x, n, K, ksteps, eps, MT, xf);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_prep_frag(x, n, K, eps, kPieces, ws, s);
     if (e != hipSuccess) return e;
   }
   ProfScope prof("linear_mfma", s);

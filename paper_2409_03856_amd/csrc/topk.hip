@@ -6,7 +6,7 @@
 // three:
 //  1. the gate pass: a = SiLU(W_gate xn) for every neuron into a [B, d_ff] buffer; the whole
 //     gate is read once, as in the threshold path (batch 1: the decode kernel's gate phase
-//     alone, ffn_decode.hip; 2..64 tokens with d_model % 256 == 0: cats_ring_kernel's gate
+//     alone, ffn_decode.hip; 2..64 tokens with d_model % 256 == 0: cats_frag_kernel's gate
 //     phase on the exact three-piece input, ffn_batch.hip; other batches: gate_kernel in
 //     activation mode, ffn_gemv.hip).
 //  2. topk_cut_kernel: one 1024-thread workgroup per token finds the k-th largest top-k key
@@ -16,7 +16,7 @@
 //     which are placed by a
 //     block scan and ranked by counting on the full key; when every value bit is decided
 //     first, a block scan over the threads' contiguous index ranges settles the ties.
-//  3. the keyed FFN pass: decode1_kernel (batch 1), cats_ring_kernel + down_ring_kernel
+//  3. the keyed FFN pass: decode1_kernel (batch 1), cats_frag_kernel + down_ring_kernel
 //     (batched, one pass over the tokens' union) or gate_kernel + down_kernel (other small
 //     batches) read the stored activations, keep a neuron iff its key reaches the token's cut,
 //     and stream W_up and W_down for the kept neurons only; reduce_kernel sums the partials
