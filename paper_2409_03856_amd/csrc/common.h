@@ -22,20 +22,30 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f) {
   return u >> 16;
 }
 
+// Whether x is an infinity or NaN, or its bf16 rounding an infinity.
+__device__ __forceinline__ bool rounds_to_inf(float x) {
+  return (__float_as_uint(x) & 0x7fffffffu) >= 0x7f7f8000u;
+}
+
 // The next bf16 piece of r (its round-to-nearest-even value), which is taken off r: three pieces
-// hold every bit of an fp32 value, h0 + h1 + h2 = r exactly. An infinity or NaN is its own first
-// piece and leaves 0, and a value that would round to infinity is truncated instead.
+// hold every bit of an fp32 value, h0 + h1 + h2 = r exactly. Not for a value that rounds_to_inf.
 __device__ __forceinline__ uint32_t take_piece(float& r) {
-  const uint32_t u = __float_as_uint(r);
-  uint32_t h = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-  if (((u >> 16) & 0x7f80u) == 0x7f80u) {
-    h = (u >> 16) | ((u & 0x007fffffu) != 0u ? 0x40u : 0u);
-    r = 0.f;
-    return h;
-  }
-  if ((h & 0x7f80u) == 0x7f80u) h = u >> 16;
+  const uint32_t h = f32_to_bf16(r);
   r -= __uint_as_float(h << 16);  // exact: the remainder of a bf16 rounding
   return h;
+}
+
+// The same for any value: an infinity or NaN is its own first piece and leaves 0, and a finite
+// value whose rounding is an infinity is truncated instead.
+__device__ __forceinline__ uint32_t take_piece_any(float& r) {
+  if (!rounds_to_inf(r)) return take_piece(r);
+  const uint32_t u = __float_as_uint(r);
+  if ((u & 0x7f800000u) == 0x7f800000u) {
+    r = 0.f;
+    return (u >> 16) | ((u & 0x007fffffu) != 0u ? 0x40u : 0u);
+  }
+  r -= __uint_as_float(u & 0xffff0000u);
+  return u >> 16;
 }
 
 // Sum over the 64 lanes of a wave; every lane receives the total.

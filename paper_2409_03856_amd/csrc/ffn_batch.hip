@@ -80,7 +80,7 @@ __device__ __forceinline__ void wait_later(int later) {
 }
 
 // ---- x -> optional RMSNorm -> PX bf16 pieces [PX][Mpad][d]; one workgroup per padded row.
-template <int PX, bool ANY = false>
+template <int PX>
 __global__ __launch_bounds__(256) void prep_pieces_kernel(const float* __restrict__ x, int B, int d,
                                                           int mpad, float norm_eps,
                                                           uint16_t* __restrict__ xp) {
@@ -126,27 +126,28 @@ __global__ __launch_bounds__(256) void prep_pieces_kernel(const float* __restric
       v[u].w *= inv;
     }
   }
+  bool top = false;
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int i = tid + 256 * u;
-    if (i >= nv4) continue;
-    float r[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+  for (int u = 0; u < kPer; ++u)
+    top |= rounds_to_inf(v[u].x) || rounds_to_inf(v[u].y) || rounds_to_inf(v[u].z) || rounds_to_inf(v[u].w);
+  auto write = [&](auto piece_of) {
 #pragma unroll
-    for (int p = 0; p < PX; ++p) {
-      uint32_t b[4];
+    for (int u = 0; u < kPer; ++u) {
+      const int i = tid + 256 * u;
+      if (i >= nv4) continue;
+      float r[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (ANY) {  // infinities too (calibration inputs)
-          b[e] = take_piece(r[e]);
-        } else {
-          b[e] = f32_to_bf16(r[e]);
-          r[e] -= __uint_as_float(b[e] << 16);  // exact: the remainder of a bf16 rounding
-        }
+      for (int p = 0; p < PX; ++p) {
+        uint32_t b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b[e] = piece_of(r[e]);
+        reinterpret_cast<uint2*>(xp + ((size_t)p * mpad + m) * d)[i] =
+            make_uint2(b[0] | (b[1] << 16), b[2] | (b[3] << 16));
       }
-      reinterpret_cast<uint2*>(xp + ((size_t)p * mpad + m) * d)[i] =
-          make_uint2(b[0] | (b[1] << 16), b[2] | (b[3] << 16));
     }
-  }
+  };
+  if (PX > 1 && __builtin_expect(top, 0)) write(take_piece_any);
+  else write(take_piece);
 }
 
 // Segment geometry: nseg segments of np neurons over n_rows rows, np a multiple of 4 of at most
@@ -901,7 +902,7 @@ int batch_mt(int B) { return (B + 15) / 16; }
 }  // namespace
 
 hipError_t launch_prep_pieces3(const float* x, int B, int d, int mpad, uint16_t* xp, hipStream_t stream) {
-  klaunch((prep_pieces_kernel<3, true>), mpad, 256, 0, stream, x, B, d, mpad, -1.f, xp);
+  klaunch(prep_pieces_kernel<3>, mpad, 256, 0, stream, x, B, d, mpad, -1.f, xp);
   return hipGetLastError();
 }
 

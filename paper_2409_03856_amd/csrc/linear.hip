@@ -83,16 +83,23 @@ __global__ __launch_bounds__(kPrepThreads) void prep_frag_kernel(const float* __
       r[0] = a.x * inv; r[1] = a.y * inv; r[2] = a.z * inv; r[3] = a.w * inv;
       r[4] = b.x * inv; r[5] = b.y * inv; r[6] = b.z * inv; r[7] = b.w * inv;
     }
+    bool top = false;
 #pragma unroll
-    for (int p = 0; p < kPieces; ++p) {
-      if (p == pieces) break;  // uniform
-      uint32_t b[8];
+    for (int e = 0; e < 8; ++e) top |= rounds_to_inf(r[e]);
+    auto write = [&](auto piece_of) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) b[e] = take_piece(r[e]);
-      xf[(((size_t)(c >> 2) * pieces + p) * MT + mt) * kWave + 16 * (c & 3) + (m & 15)] =
-          make_uint4(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16),
-                     b[6] | (b[7] << 16));
-    }
+      for (int p = 0; p < kPieces; ++p) {
+        if (p == pieces) break;  // uniform
+        uint32_t b[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) b[e] = piece_of(r[e]);
+        xf[(((size_t)(c >> 2) * pieces + p) * MT + mt) * kWave + 16 * (c & 3) + (m & 15)] =
+            make_uint4(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16),
+                       b[6] | (b[7] << 16));
+      }
+    };
+    if (pieces > 1 && __builtin_expect(top, 0)) write(take_piece_any);
+    else write(take_piece);  // a single piece is the rounding, also to an infinity
   }
 }
 

@@ -50,3 +50,39 @@ def test_every_mode(sr, d, f, bsz):
     y, idx, cnt = sr.sirius_ffn_topk(dev_f32(x), *W, k)
     sets, _ = check_topk_sets(x, wg, k, host(idx), host(cnt))
     check_ffn(host(y), oracle.ffn_masked(x, wg, wu, wd, sets), tol=FP32_PATH_TOL)
+
+
+@pytest.mark.parametrize("d", [2048, 1280])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.float32(3.4e38)])
+def test_infinite_input_is_the_same_at_every_batch(sr, d, value):
+    """One infinite (or nearly infinite) input element: the activations that it makes infinite are kept,
+    in the calls of at most 4 tokens (unit kernels where d_model is a multiple of 2048) as in those of
+    5 and more and of one; the other tokens are untouched."""
+    f = 300
+    say(f"infinite input d={d} value={value}")
+    wg, wu, wd = ffn_weights(4000 + d, d, f, 1.0 / np.sqrt(d))
+    W = tuple(dev_bf16(w) for w in (wg, wu, wd))
+    x = decode_inputs(4100, 5, d)
+    t = float(np.median(np.abs(oracle.gate_activations(x, wg))))
+    clean = [host(a) for a in sr.sirius_ffn_cats(dev_f32(x), *W, t)]
+    x[2, 9] = value
+    one = [host(a) for a in sr.sirius_ffn_cats(dev_f32(x[2:3]), *W, t)]
+    for b in (3, 4, 5):
+        y, idx, cnt = (host(a) for a in sr.sirius_ffn_cats(dev_f32(x[:b]), *W, t))
+        assert cnt[2] == one[2][0] and np.array_equal(idx[2, :cnt[2]], one[1][0, :cnt[2]]), b
+        for m in (0, 1):
+            assert cnt[m] == clean[2][m] and np.array_equal(idx[m, :cnt[m]], clean[1][m, :cnt[m]])
+            assert np.all(np.isfinite(y[m]))
+
+
+def test_bf16_rounding_at_the_top_of_the_range(sr):
+    """The dense pass of 8 or more tokens rounds its input to bf16: a value above the largest bf16 by
+    half a step is an infinity there, at a width of the unit kernels and at one of the others."""
+    for d in (2048, 1280):
+        wg, wu, wd = ffn_weights(4200 + d, d, 64, 1.0 / np.sqrt(d))
+        x = np.zeros((8, d), dtype=np.float32)
+        x[:, 0] = 3.4e38
+        wg[:, 0] = wu[:, 0] = 0x0D80  # 2^-100: finite products for any finite input
+        say(f"bf16 rounding at the top d={d}")
+        y = host(sr.sirius_ffn_dense(dev_f32(x), *(dev_bf16(w) for w in (wg, wu, wd))))
+        assert not np.any(np.isfinite(y))
