@@ -111,6 +111,37 @@ struct LinearOut {
   int Nq, Nkv;
 };
 
+// Row j of the launch's weight rows.
+__device__ __forceinline__ const uint4* row_of(const LinearOut& o, int j, int K) {
+  const uint16_t* w = j < o.Nq ? o.Wq + (size_t)j * K
+                      : j < o.Nq + o.Nkv ? o.Wk + (size_t)(j - o.Nq) * K
+                                         : o.Wv + (size_t)(j - o.Nq - o.Nkv) * K;
+  return reinterpret_cast<const uint4*>(w);
+}
+
+// The product of token m's row with a weight row as linear_kernel (model.hip) forms it, from the x
+// pieces put together again; every lane of the wave returns it.
+template <int MT>
+__device__ __noinline__ float whole_dot(const uint4* __restrict__ xf, int m, const uint4* __restrict__ w, int K) {
+  const int lane = threadIdx.x & (kWave - 1);
+  float acc = 0.f;
+  for (int c = lane; c < K >> 3; c += kWave) {
+    __attribute__((aligned(16))) float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = kPieces - 1; p >= 0; --p) {  // lo first: exact
+      const uint4 v = xf[(((size_t)(c >> 2) * kPieces + p) * MT + (m >> 4)) * kWave + 16 * (c & 3) + (m & 15)];
+      const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[2 * e] += bf16_lo(u[e]);
+        x[2 * e + 1] += bf16_hi(u[e]);
+      }
+    }
+    acc = dot8(w[c], x, acc);
+  }
+  return wave_sum(acc);
+}
+
 // MT 16-token tiles, RT 16-row weight tiles per workgroup, KB columns per block, D blocks in flight.
 template <int MT, int RT, int KB, int D>
 __global__ __launch_bounds__(kLmThreads) void linear_mfma_kernel(const uint4* __restrict__ xf,
@@ -136,10 +167,7 @@ __global__ __launch_bounds__(kLmThreads) void linear_mfma_kernel(const uint4* __
 #pragma unroll
   for (int i = 0; i < kLd; ++i) {
     const int j = min(n0 + row0 + i * kRowStep, N - 1);  // rows past the last: never stored
-    const uint16_t* w = j < o.Nq ? o.Wq + (size_t)j * K
-                        : j < o.Nq + o.Nkv ? o.Wk + (size_t)(j - o.Nq) * K
-                                           : o.Wv + (size_t)(j - o.Nq - o.Nkv) * K;
-    src[i] = reinterpret_cast<const uint4*>(w) + ch;
+    src[i] = row_of(o, j, K) + ch;
   }
   static_assert(D % 2 == 0, "LDS and x buffers alternate");
   uint4 wr[D][kLd];
@@ -227,13 +255,14 @@ __global__ __launch_bounds__(kLmThreads) void linear_mfma_kernel(const uint4* __
     for (int mt = 0; mt < MT; ++mt) red[((wave * RT + rt) * MT + mt) * kWave + lane] = acc[rt][mt];
   __syncthreads();
   const float* rf = reinterpret_cast<const float*>(lds);
-  for (int i = tid; i < kRows * n; i += kLmThreads) {
-    const int jr = i % kRows, m = i / kRows, j = n0 + jr;
-    if (j >= N) continue;
+  auto sum_of = [&](int jr, int m) {
     const int at = (((jr >> 4) * MT + (m >> 4)) * kWave + 16 * ((m & 15) >> 2) + (jr & 15)) * 4 + (m & 3);
     float s = rf[at];
 #pragma unroll
     for (int w = 1; w < kLmWaves; ++w) s += rf[at + w * RT * MT * kWave * 4];
+    return s;
+  };
+  auto store = [&](int j, int m, float s) {
     if (j < o.Nq) {
       const size_t e = (size_t)m * o.Nq + j;
       o.yq[e] = o.resid != nullptr ? o.resid[e] + s : s;
@@ -241,6 +270,28 @@ __global__ __launch_bounds__(kLmThreads) void linear_mfma_kernel(const uint4* __
       o.yk[(size_t)m * o.Nkv + j - o.Nq] = (uint16_t)f32_to_bf16(s);
     } else {
       o.yv[(size_t)m * o.Nkv + j - o.Nq - o.Nkv] = (uint16_t)f32_to_bf16(s);
+    }
+  };
+  bool nan = false;
+  for (int i = tid; i < kRows * n; i += kLmThreads) {
+    const int jr = i % kRows, m = i / kRows;
+    if (n0 + jr >= N) continue;
+    const float s = sum_of(jr, m);
+    if (s == s) store(n0 + jr, m, s);
+    else nan = true;
+  }
+  // an infinite weight times a zero piece, or times pieces of both signs, is NaN where the product is
+  // an infinity: such sums are formed again from whole values, a wave per sum
+  if (__builtin_expect(__ballot(nan) == 0, 1)) return;
+  for (int i0 = tid - lane; i0 < kRows * n; i0 += kLmThreads) {
+    const int i = i0 + lane, jr = i % kRows, m = i / kRows;
+    const bool live = m < n && n0 + jr < N;
+    const float s = live ? sum_of(jr, m) : 0.f;
+    for (unsigned long long left = __ballot(s != s); left != 0; left &= left - 1) {
+      const int l = __builtin_ctzll(left);
+      const int jl = n0 + __shfl(jr, l, kWave), ml = __shfl(m, l, kWave);
+      const float t = whole_dot<MT>(xf, ml, row_of(o, jl, K), K);
+      if (lane == l) store(jl, ml, t);
     }
   }
 }

@@ -49,3 +49,51 @@ def test_chunk_projections(case):
         want = o[0, :7 + n]
         step = np.abs(want) * 2.0 ** -7 + 1e-5 * np.sqrt(np.mean(want * want))
         assert np.all(np.abs(host(g[0].float())[:7 + n] - want) <= step)
+
+
+@pytest.mark.parametrize("d,v,n", [(264, 700, 3), (1032, 12301, 18)])
+def test_infinite_weights(d, v, n):
+    """A weight that is an infinity gives the infinity (or, with one of the other sign or a NaN in its
+    row, the NaN) that the whole fp32 values give, as the one-token passes do; other outputs stay as
+    they were. In the LM head, and in the key and value projections (their cache rows)."""
+    import torch
+    import paper_2409_03856_amd as sr
+    h, hkv, hd, inf = 3, 1, 40, np.float32(np.inf)
+    say(f"infinite weights d={d} v={v} n={n}")
+    s = ModelShape("inf", 1, d, 96, h, hkv, hd, v, 96, 6.0)
+    w = {k: dev_bf16(b) for k, b in model_weights(77, s).items()}
+    toks = dev_i32(prompt_tokens(5, n, v))
+
+    def passes(weights):
+        m = sr.Model(weights, h, hkv, hd, 96, [-1.0])
+        pos = torch.zeros(1, dtype=torch.int32, device="cuda")
+        lg, _, _ = sr.sirius_model_forward(m, toks, pos, True)
+        one = sr.Model(weights, h, hkv, hd, 96, [-1.0])
+        rows = []
+        for i in range(n):
+            pos.fill_(i)
+            rows.append(host(sr.sirius_model_forward(one, toks[i:i + 1], pos, True)[0])[0])
+        return host(lg), np.stack(rows), m, one
+
+    clean, _, _, _ = passes(w)
+    bad = dict(w)
+    bad["lm_head"] = w["lm_head"].clone()
+    for j, cols in ((0, {1: inf}), (17, {d - 1: -inf}), (v - 1, {8: inf, 9: inf}), (40, {3: inf, 4: -inf}),
+                    (41, {2: np.nan}), (100, {c: inf for c in range(d)})):
+        for c, x in cols.items():
+            bad["lm_head"][j, c] = float(x)
+    got, want, _, _ = passes(bad)
+    rows = np.array([0, 17, v - 1, 40, 41, 100])
+    assert np.array_equal(got[:, rows], want[:, rows], equal_nan=True)
+    assert np.all(np.isinf(got[:, [0, 17]])) and np.all(np.isnan(got[:, [41, 100]]))
+    keep = np.setdiff1d(np.arange(v), rows)
+    assert np.array_equal(got[:, keep], clean[:, keep])
+    bad = dict(w)
+    for k, x in (("wk", inf), ("wv", -inf)):
+        bad[k] = w[k].clone()
+        bad[k][0, 5, 7] = float(x)
+    _, _, m, one = passes(bad)
+    for a, b in ((m.k_cache, one.k_cache), (m.v_cache, one.v_cache)):
+        a, b = host(a[0, :n].float())[:, 0], host(b[0, :n].float())[:, 0]
+        assert np.all(np.isinf(a[:, 5])) and np.array_equal(a[:, 5], b[:, 5])
+        assert np.all(np.isfinite(np.delete(a, 5, 1)))
