@@ -38,6 +38,28 @@ __device__ __align__(16) uint4 g_zero_chunk[1] = {{0u, 0u, 0u, 0u}};  // source 
 
 __device__ __forceinline__ int swz(int r, int c) { return c ^ (r & 7); }
 
+// The product of an input with a weight row, from the input's pieces (`step` apart) put together
+// again; every lane of the wave returns it.
+__device__ float whole_dot(const uint16_t* __restrict__ xp, size_t step, const uint16_t* __restrict__ w, int d) {
+  const int lane = threadIdx.x & (kWave - 1);
+  float acc = 0.f;
+  for (int c = 8 * lane; c < d; c += 8 * kWave) {
+    __attribute__((aligned(16))) float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = kPieces - 1; p >= 0; --p) {  // lo first: exact
+      const uint4 v = *reinterpret_cast<const uint4*>(xp + p * step + c);
+      const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[2 * e] += bf16_lo(u[e]);
+        x[2 * e + 1] += bf16_hi(u[e]);
+      }
+    }
+    acc = dot8(*reinterpret_cast<const uint4*>(w + c), x, acc);
+  }
+  return wave_sum(acc);
+}
+
 // xp [3][npad][d]: the inputs' pieces, zero rows past nb (npad a multiple of 64). zero_ints: words
 // that the first workgroup clears for the select.
 __global__ __launch_bounds__(kThreads, 2) void calib_gate_kernel(
@@ -132,6 +154,7 @@ __global__ __launch_bounds__(kThreads, 2) void calib_gate_kernel(
     }
   }
   // C layout: lane holds neuron fr of a tile and inputs 4 grp + e
+  bool nan = false;
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -140,9 +163,25 @@ __global__ __launch_bounds__(kThreads, 2) void calib_gate_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int m = m0 + 32 * th + 16 * a + 4 * grp + e;
-        if (m < nb && j < F) act[(size_t)m * F + j] = fabsf(silu((sum[a][n][e] + acc[a][n][e]) + low[a][n][e]));
+        const float g = (sum[a][n][e] + acc[a][n][e]) + low[a][n][e];
+        nan |= g != g;
+        if (m < nb && j < F) act[(size_t)m * F + j] = fabsf(silu(g));
       }
     }
+  // an infinite weight times a zero piece, or times pieces of both signs, is NaN where the product is
+  // an infinity: the wave forms such values again from whole inputs
+  if (__ballot(nan) == 0) return;
+  for (int i = 0; i < 32; ++i) {
+    const int at = m0 + 32 * th + 16 * (i >> 4) + (i & 3), n = n0 + 64 * nh + 16 * ((i >> 2) & 3);
+    const bool live = at + 4 * grp < nb && n + fr < F;
+    const float v = live ? act[(size_t)(at + 4 * grp) * F + n + fr] : 0.f;
+    for (unsigned long long left = __ballot(v != v); left != 0; left &= left - 1) {
+      const int l = __builtin_ctzll(left);
+      const size_t m = at + 4 * (l >> 4), j = n + (l & 15);
+      const float g = whole_dot(xp + m * d, (size_t)npad * d, wg + j * d, d);
+      if (lane == l) act[m * F + j] = fabsf(silu(g));
+    }
+  }
 }
 
 constexpr int kChunk = 1024;  // inputs per launch: bounds the pieces' workspace

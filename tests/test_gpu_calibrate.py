@@ -56,3 +56,25 @@ def test_ties_zeros_and_infinities(sr):
     # the same rank among the clean values: all of the bad input's f activations lie above it
     tb = float(host(sr.sirius_cats_calibrate(dev_f32(bad), dev_bf16(wg), 0.5 * n / (n + 1)))[0])
     assert t == tb
+
+
+@pytest.mark.parametrize("n", [5, 70])
+def test_infinite_weights(sr, n):
+    """A gate weight that is an infinity gives an infinite activation where the gate is positive (its
+    SiLU is NaN where it is negative, and NaN ranks above the infinities): every rank below them is the
+    finite activations', the ranks from there on are infinities, then NaN."""
+    d, f = 264, 300
+    say(f"calibrate with infinite weights N={n}")
+    wg, _, _ = ffn_weights(950, d, f, 1.0 / np.sqrt(d))
+    x = calibration_inputs(950, n, d)
+    wd = dev_bf16(wg)
+    wd[3, 7], wd[299, 100], wd[150, 0] = float("inf"), float("-inf"), float("inf")
+    finite = np.sort(np.abs(oracle.gate_activations(x, np.delete(wg, [3, 150, 299], axis=0))).ravel())
+    up = int(np.sum(x[:, 7] > 0) + np.sum(x[:, 100] < 0) + np.sum(x[:, 0] > 0))
+    total = n * f
+    at = lambda rank: float(host(sr.sirius_cats_calibrate(dev_f32(x), wd, (rank - 0.5) / total))[0])  # 1-based, ascending
+    assert 0 < up < 3 * n
+    for rank in (1, finite.size // 2, finite.size):
+        assert abs(at(rank) - finite[rank - 1]) <= 1e-5 * finite[rank - 1] + 2e-6
+    assert np.isposinf(at(finite.size + 1)) and np.isposinf(at(finite.size + up))
+    assert np.isnan(at(finite.size + up + 1)) and np.isnan(at(total))
