@@ -37,6 +37,7 @@
 // (85 + 6); 8 sequences of 16 tokens over 3500-7000 rows 72 + 8 us (345 + 53). The high pieces'
 // sums of a score are kept apart from the rest: 2.1e-7 off 64 bits (2.3e-7 before; 3.0e-7 in one
 // chain).
+#include <float.h>
 #include <math.h>
 
 #include "common.h"
@@ -73,13 +74,61 @@ __device__ __forceinline__ float rest_finite(float x) {
 }
 
 // e^x for x <= 0 to about one ulp: the hardware exp2 of the rounded x log2(e), times the first
-// order of what the rounding left off. Below -200 (a hidden position's -inf, a NaN) 0.
+// order of what the rounding left off. Below -200 (a hidden position's -inf) 0; a NaN stays one.
 __device__ __forceinline__ float exp_neg(float x) {
   constexpr float kHi = 1.44269502162933349609375f, kLo = 1.9259629911e-8f, kLn2 = 0.693147180559945f;
-  x = fmaxf(x, -200.f);
+  x = __builtin_elementwise_maximum(x, -200.f);
   const float t = x * kHi;
   const float d = fmaf(x, kLo, fmaf(x, kHi, -t));
   return __builtin_amdgcn_exp2f(t) * fmaf(d, kLn2, 1.f);
+}
+
+// One query row over positions c0 .. last of a chunk in fp32 products: scores whose value is NaN and
+// hidden positions weigh nothing. Keys and values lie at offsets cofs (cache) and nofs (new rows,
+// positions from p on), rs apart, in 16-byte units. Writes the output over the sum to dst, or with
+// pm set the output, the maximum and the sum of the chunk.
+__device__ __noinline__ void whole_row(const float* __restrict__ q, float scale, const uint4* __restrict__ k_cache,
+                          const uint4* __restrict__ v_cache, const uint4* __restrict__ k_new,
+                          const uint4* __restrict__ v_new, size_t cofs, size_t nofs, size_t rs, int hd, int c0,
+                          int last, int p, float* __restrict__ dst, float* __restrict__ pm, float* __restrict__ pl) {
+  const int lane = threadIdx.x & (kWave - 1);
+  auto row = [&](const uint4* cache, const uint4* fresh, int pos) {
+    return pos < p ? cache + cofs + pos * rs : fresh + nofs + (pos - p) * rs;
+  };
+  auto score = [&](int pos) {
+    const uint4* k = row(k_cache, k_new, pos);
+    float s = 0.f;
+    for (int c = 0; c < hd >> 3; ++c) {
+      __attribute__((aligned(16))) float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = q[8 * c + e] * scale;
+      s = dot8(k[c], x, s);
+    }
+    return s;
+  };
+  float m = -INFINITY;
+  for (int pos = c0 + lane; pos <= last; pos += kWave) m = fmaxf(m, score(pos));
+  for (int k = 1; k < kWave; k <<= 1) m = fmaxf(m, __shfl_xor(m, k, kWave));
+  float l = 0.f, o0 = 0.f, o1 = 0.f;  // columns lane and lane + 64
+  for (int base = c0; base <= last; base += kWave) {
+    const float s = base + lane <= last ? score(base + lane) : -INFINITY;
+    const float w = s > -INFINITY ? expf(s - m) : 0.f;
+    l += w;
+    for (int j = 0; j < min(kWave, last + 1 - base); ++j) {
+      const uint16_t* v = reinterpret_cast<const uint16_t*>(row(v_cache, v_new, base + j));
+      const float wj = __shfl(w, j, kWave);
+      if (lane < hd) o0 = fmaf(wj, bf16_lo(v[lane]), o0);
+      if (lane + kWave < hd) o1 = fmaf(wj, bf16_lo(v[lane + kWave]), o1);
+    }
+  }
+  l = wave_sum(l);
+  const float d = pm != nullptr ? 1.f : l;
+  if (lane < hd) dst[lane] = o0 / d;
+  if (lane + kWave < hd) dst[lane + kWave] = o1 / d;
+  if (pm != nullptr && lane == 0) {
+    *pm = m;
+    *pl = l;
+  }
 }
 
 // KS: 32-wide steps of the head dimension (2: hd <= 64, 4: hd <= 128). QW: 16-row query tiles
@@ -109,6 +158,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_partial_kernel(
   static_assert(kVCh == 8 || kVCh == 16, "value swizzle");
   __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
   __shared__ float s_m[4][16], s_l[4][16];
+  __shared__ int s_nan[4];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int fr = lane & 15, g = lane >> 4;
   const int split = blockIdx.x, nsplit = gridDim.x;
@@ -233,7 +283,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_partial_kernel(
       qf[i][pc] = *reinterpret_cast<const bf16x8_t*>(lds + ((((qt * KS + i) * 3 + pc) * kWave) + lane) * 16);
   const int row = 16 * qt + fr;                                 // this lane's query row
   const int lim = row < nr ? p + (r0 + row) / G : -1;           // its last visible position
-  float m = -INFINITY, l = 0.f;
+  float m = -FLT_MAX, l = 0.f;  // finite before the first visible position: -inf less it is no NaN
   floatx4_t o[2 * KS];  // columns 16 t + 4 g + e of the row
 #pragma unroll
   for (int t = 0; t < 2 * KS; ++t) o[t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -283,7 +333,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_partial_kernel(
     mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
     mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
     const float m_new = fmaxf(m, mx);
-    const float alpha = exp_neg(m - m_new);  // 0 before the first visible position
+    const float alpha = exp_neg(m - m_new);
     m = m_new;
     l *= alpha;
 #pragma unroll
@@ -324,7 +374,25 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_partial_kernel(
   // output itself: the unnormalised output over the sum, as the merge computes it)
   l += __shfl_xor(l, 16, kWave);
   l += __shfl_xor(l, 32, kWave);
+  // an infinite key or value times a zero piece, or times pieces of both signs, is NaN where the
+  // product is an infinity: then the chunk again, a wave per query row, from whole values
+  floatx4_t chk = floatx4_t{l, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < 2 * KS; ++t) chk += o[t];
+  const float c1s = (chk[0] + chk[1]) + (chk[2] + chk[3]);
+  const bool nan = __ballot(c1s != c1s) != 0;
+  if (!(l > 0.f)) m = -INFINITY;  // nothing visible
+  auto whole = [&](int r) {
+    const size_t at = (rowbase + r) * nsplit + split;
+    whole_row(q + q_row(r), scale, k_cache, v_cache, k_new, v_new, (size_t)b * Lmax * rs + (size_t)kvh * hd8,
+              (size_t)b * n * rs + (size_t)kvh * hd8, rs, hd, c0, min(c1 - 1, p + (r0 + r) / G), p,
+              out != nullptr ? out + q_row(r) : po + at * hd, out != nullptr ? nullptr : pm + at, pl + at);
+  };
   if constexpr (PW == 1) {
+    if (__builtin_expect(nan, 0)) {
+      for (int r = 16 * qt; r < min(16 * qt + 16, nr); ++r) whole(r);
+      return;
+    }
     if (row < nr) {
       float* dst = out != nullptr ? out + q_row(row) : po + ((rowbase + row) * nsplit + split) * hd;
 #pragma unroll
@@ -342,11 +410,16 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_partial_kernel(
     }
   } else {
     // the PW position groups of each query tile, merged in order through LDS
+    if (lane == 0) s_nan[wave] = nan;
     if (g == 0) {
       s_m[wave][fr] = m;
       s_l[wave][fr] = l;
     }
     __syncthreads();
+    if (__builtin_expect(s_nan[0] | s_nan[1] | s_nan[2] | s_nan[3], 0)) {  // uniform
+      for (int r = wave; r < nr; r += kAttnThreads / kWave) whole(r);
+      return;
+    }
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < PW; ++w) M = fmaxf(M, s_m[qt * PW + w][fr]);

@@ -50,3 +50,66 @@ def test_tiles(case):
     o2 = host(sr.sirius_attn_kv(dev_f32(q), dev_bf16(kn), dev_bf16(vn), Kc, Vc, dev_i32(bad)))
     assert np.all(np.isnan(o2[0])) and np.array_equal(o2[1:], out[1:])
     assert np.array_equal(host(Kc), kc) and np.array_equal(host(Vc), vc)
+
+
+def _widen(bits):
+    return (np.asarray(bits).astype(np.uint32) << 16).view(np.float32)
+
+
+# B, n, H, Hkv, head_dim, Lmax, position: one, two and four query tiles, one chunk and several
+@pytest.mark.parametrize("case", [(1, 1, 4, 1, 64, 200, 150), (1, 1, 8, 2, 128, 3000, 2500), (1, 5, 4, 1, 72, 900, 700),
+                                  (1, 16, 4, 1, 128, 2000, 1500), (1, 20, 2, 1, 40, 250, 200)],
+                         ids=lambda c: "-".join(str(x) for x in c))
+def test_infinite_keys_and_values(case):
+    """Infinities in the cache give what whole fp32 products give. A value row with an infinity: that
+    infinity in its column for every token that sees the row. A key that makes a score -infinity or
+    NaN: the position weighs nothing. One that makes it +infinity: NaN. Tokens that do not see the
+    position, and heads beside it, stay as they were (1e-5 x RMS: fp32 sums in another order)."""
+    import paper_2409_03856_amd as sr
+    b, n, h, hkv, hd, lmax, p = case
+    say(f"attention with infinities {case}")
+    g = h // hkv
+    q, kn, vn, kc, vc = attn_inputs(77 + hd, b, n, h, hkv, hd, lmax)
+    q *= 3.0
+    q[0, 0, :g, 3] = 0.0  # a NaN score: 0 times an infinity
+
+    def run(kn, vn, kc, vc):
+        return host(sr.sirius_attn_kv(dev_f32(q), dev_bf16(kn), dev_bf16(vn), dev_bf16(kc), dev_bf16(vc),
+                                      dev_i32(np.array([p]))))[0]
+
+    clean = run(kn, vn, kc, vc)
+    scale = np.sqrt(np.mean(clean * clean))
+    pinf, ninf = 0x7F80, 0xFF80
+    # values: column 5 of a cached row that holds each row's maximum weight or not
+    v2 = vc.copy()
+    v2[0, p // 2, 0, 5] = ninf
+    got = run(kn, vn, kc, v2)
+    assert np.all(np.isneginf(got[:, :g, 5]))
+    keep = np.ones(hd, bool)
+    keep[5] = False
+    assert np.max(np.abs(got[:, :g][..., keep] - clean[:, :g][..., keep])) <= 1e-5 * scale
+    assert np.array_equal(got[:, g:], clean[:, g:])
+    # the chunk's last new value row: seen by the last token only
+    vn2 = vn.copy()
+    vn2[0, n - 1, 0, 0] = pinf
+    got = run(kn, vn2, kc, vc)
+    assert np.all(np.isposinf(got[n - 1, :g, 0]))
+    assert np.max(np.abs(got[:n - 1] - clean[:n - 1]), initial=0.0) <= 1e-5 * scale
+    # keys: the sign of the query's column decides, and a zero there gives NaN: no weight
+    k2 = kc.copy()
+    k2[0, p // 3, 0, 3] = pinf
+    got = run(kn, vn, k2, vc)
+    qs = q[0, :, :g, 3]
+    assert np.all(np.isnan(got[:, :g][qs > 0]))
+    kf, vf = _widen(kc), _widen(vc)
+    kf[0, p:p + n], vf[0, p:p + n] = _widen(kn[0]), _widen(vn[0])
+    for i in range(n):
+        rows = [r for r in range(p + i + 1) if r != p // 3]
+        for j in range(g):
+            if qs[i, j] > 0:
+                continue
+            s = kf[0, rows, 0].astype(np.float64) @ q[0, i, j].astype(np.float64) / np.sqrt(hd)
+            w = np.exp(s - s.max())
+            want = (w / w.sum()) @ vf[0, rows, 0].astype(np.float64)
+            assert np.max(np.abs(got[i, j] - want)) <= 1e-4 * scale
+    assert np.array_equal(got[:, g:], clean[:, g:])
