@@ -124,12 +124,12 @@ int sirius_ffn_cats(const float* x, int B, const uint16_t* w_gate, const uint16_
  * or two threads) race and must be ordered by the caller. The array's contents carry over from
  * call to call; the kernels read only what the same call wrote.
  * Errors: as sirius_ffn_cats, plus SIRIUS_EWORKSPACE when the call would need more than
- * SIRIUS_NOALLOC_SCRATCH_BYTES, 96 MiB (sirius_workspace_size(SIRIUS_OP_FFN_CATS, ...) tells;
+ * SIRIUS_NOALLOC_SCRATCH_BYTES, 112 MiB (sirius_workspace_size(SIRIUS_OP_FFN_CATS, ...) tells;
  * every batch up to 64 at the Llama-3-8B FFN shape, 4096 x 14336, and at the 70B shape,
  * 8192 x 28672, fits), SIRIUS_EHIP when the array's device address cannot be obtained, and
  * SIRIUS_EINVAL for a device index of 64 or more.
  */
-#define SIRIUS_NOALLOC_SCRATCH_BYTES ((size_t)96 << 20)
+#define SIRIUS_NOALLOC_SCRATCH_BYTES ((size_t)112 << 20)
 int sirius_ffn_cats_noalloc(const float* x, int B, const uint16_t* w_gate, const uint16_t* w_up,
                             const uint16_t* w_down, int d_model, int d_ff, float t, float norm_eps,
                             const float* resid, float* y, int32_t* active_idx, int32_t* active_cnt,

@@ -107,3 +107,20 @@ def test_noalloc_under_graph_capture(sr):
         # eager work between replays
         _noalloc_c_abi(sr, xd, W, t, rd, y, idx, cnt)
         torch.cuda.synchronize()
+
+
+def test_noalloc_at_the_scratch_limit(sr):
+    """A wide layer at a batch that needs nearly the whole scratch: the results of sirius_ffn_cats."""
+    import torch
+    bsz, d, f = 59, 3584, 64058
+    say(f"noalloc at the scratch limit: {bsz} x {d} x {f}")
+    W = [torch.empty((f, d), dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    for i, w in enumerate(W):
+        sr.sirius_fill_normal_bf16(w, 9400 + i, 0.0, d ** -0.5)
+    x = dev_f32(decode_inputs(9400, bsz, d))
+    y, idx, cnt = sr.sirius_ffn_cats_noalloc(x, *W, 0.3)
+    y2, idx2, cnt2 = sr.sirius_ffn_cats(x, *W, 0.3)
+    assert torch.equal(y, y2) and torch.equal(cnt, cnt2)
+    for b in range(bsz):
+        n = int(cnt[b])
+        assert torch.equal(idx[b, :n], idx2[b, :n])
