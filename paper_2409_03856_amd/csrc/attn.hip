@@ -541,11 +541,16 @@ AttnLayout attn_layout(int B, int n, int H, int Hkv, int hd, int Lmax) {
   L.nsplit = Lmax <= kDirectMax ? 1
                                 : (int)std::max(1l, std::min<long>({(kTargetWgs + wgs - 1) / wgs,
                                                                     (long)ceil_div(Lmax, tile), (long)kMaxSplits}));
+  // Room for rows * nsplit partials, by a bound that grows with every size (nsplit itself falls as the
+  // batch grows), so that a workspace of the largest call serves every smaller one.
   const size_t rows = (size_t)B * Hkv * R;
+  const size_t parts = Lmax <= kDirectMax ? rows
+                                          : std::min(rows * std::min(kMaxSplits, ceil_div(Lmax, 64)),
+                                                     rows + (size_t)(kTargetWgs - 1) * std::min(R, kMaxRowsWg));
   Carve c;
-  L.pm = c.take(rows * L.nsplit * sizeof(float));
-  L.pl = c.take(rows * L.nsplit * sizeof(float));
-  L.po = c.take(rows * L.nsplit * hd * sizeof(float));
+  L.pm = c.take(parts * sizeof(float));
+  L.pl = c.take(parts * sizeof(float));
+  L.po = c.take(parts * hd * sizeof(float));
   L.total = c.off;
   return L;
 }

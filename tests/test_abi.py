@@ -320,6 +320,19 @@ def _fake_model(**kw):
     return m
 
 
+def test_attention_workspace_of_the_largest_call_serves_the_smaller_ones(L):
+    import random
+    rng = random.Random(4)
+    size = lambda b, n, k, g, hd, lmax: L.sirius_workspace_size(9, b, n, (k * g << 16) + k, hd, lmax)
+    for _ in range(4000):
+        k, g, hd, lmax = rng.randint(1, 32), rng.randint(1, 8), 8 * rng.randint(1, 16), rng.randint(64, 1 << 17)
+        b, n = rng.randint(1, 64), rng.randint(1, 64)
+        most = size(b, n, k, g, hd, lmax)
+        for c in ((rng.randint(1, b), n, k, g, hd, lmax), (b, rng.randint(1, n), k, g, hd, lmax), (1, 1, k, g, hd, lmax),
+                  (b, n, k, g, hd, rng.randint(64, lmax))):
+            assert 0 < size(*c) <= most, (c, (b, n, k, g, hd, lmax))
+
+
 def test_model_argument_errors(L):
     big = 1 << 30
     m = _fake_model()
