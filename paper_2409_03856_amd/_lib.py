@@ -77,6 +77,8 @@ class SiriusError(RuntimeError):
 def lib() -> ctypes.CDLL:
     """Load libsirius.so (built in-tree); raises if it is missing."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -105,19 +107,17 @@ def _torch():
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 _raw_stream = None
 
 
-def _stream(stream=None):
-    """The stream's handle: of `stream`, or of torch's current one on the current device. The handle
-    is read through torch's own accessor of raw handles where this torch has it: building a Stream
-    object for it costs 3 us of the 9 us that a small call spends in this binding."""
+def _handle() -> int:
+    """The handle of torch's current stream on the current device, read through torch's own accessor
+    of raw handles where this torch has it: building a Stream object for it costs 3 us of the 9 us that
+    a small call spends in this binding."""
     global _raw_stream
-    if stream is not None:
-        return ctypes.c_void_p(stream.cuda_stream)
     if _raw_stream is None:
         torch = _torch()
         get, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
@@ -126,7 +126,18 @@ def _stream(stream=None):
             _raw_stream = lambda: get(dev())  # noqa: E731
         else:
             _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
-    return ctypes.c_void_p(_raw_stream())
+    return _raw_stream()
+
+
+def _on(stream, entry, args: dict):
+    """entry(**args) with its `stream` as torch's current one, so that whatever the call allocates, fills
+    or frees is in the order of the stream that its kernels run on."""
+    torch = _torch()
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
+    del args["stream"]
+    with torch.cuda.stream(stream):
+        return entry(**args)
 
 
 def _need(cond: bool, msg: str) -> None:
@@ -141,12 +152,24 @@ def _dev_check(*ts):
             _need(t.is_contiguous(), "tensors must be contiguous")
 
 
-_ws_cache: dict = {}
+class _Workspaces(threading.local):
+    """This thread's workspaces by (device index, stream handle, operation), oldest first. Calls of two
+    threads, or on two streams, are not ordered to each other, so they never share one."""
+
+    def __init__(self):
+        self.bufs: dict = {}
+
+
+_WS_MOST = 64  # workspaces kept per thread
+_workspaces = _Workspaces()
 _size_cache: dict = {}  # workspace bytes by operation and sizes, a pure function of them
 
 
 def workspace(op: int, a: int, b: int, c: int, d: int = 0, e: int = 0, device=None):
-    """Device workspace for an operation (cached per device; grows as needed)."""
+    """Device workspace for an operation on torch's current stream, kept for this thread's later calls of
+    the operation there and grown as needed; the `_WS_MOST` latest are kept. A replaced one goes back to
+    torch's allocator in the order of its stream. Under graph capture it is allocated in the graph's own
+    pool and not kept."""
     torch = _torch()
     n = _size_cache.get((op, a, b, c, d, e))
     if n is None:
@@ -156,12 +179,19 @@ def workspace(op: int, a: int, b: int, c: int, d: int = 0, e: int = 0, device=No
         if len(_size_cache) >= 4096:
             _size_cache.clear()
         _size_cache[(op, a, b, c, d, e)] = n
-    dev = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
-    key = (dev.index, op)
-    buf = _ws_cache.get(key)
+    dev = device
+    if not isinstance(dev, torch.device):
+        dev = torch.device("cuda", torch.cuda.current_device()) if dev is None else torch.device(dev)
+    if torch._C._cuda_isCurrentStreamCapturing():
+        return torch.empty(n, dtype=torch.uint8, device=dev)
+    bufs = _workspaces.bufs
+    key = (dev.index, _handle(), op)
+    buf = bufs.get(key)
     if buf is None or buf.numel() < n:
-        buf = torch.empty(n, dtype=torch.uint8, device=dev)
-        _ws_cache[key] = buf
+        bufs.pop(key, None)
+        if len(bufs) >= _WS_MOST:
+            bufs.pop(next(iter(bufs)))
+        buf = bufs[key] = torch.empty(n, dtype=torch.uint8, device=dev)
     return buf
 
 
@@ -176,6 +206,8 @@ def _w_dims(w_gate, w_up, w_down):
 # ---------------------------------------------------------------- entry points
 
 def sirius_ffn_dense(x, w_gate, w_up, w_down, *, norm_eps=-1.0, resid=None, y=None, ws=None, stream=None):
+    if stream is not None:
+        return _on(stream, sirius_ffn_dense, locals())
     torch = _torch()
     d, f = _w_dims(w_gate, w_up, w_down)
     _need(x.dtype == torch.float32 and x.dim() == 2 and x.shape[1] == d, "x must be fp32 [B, d_model]")
@@ -186,12 +218,14 @@ def sirius_ffn_dense(x, w_gate, w_up, w_down, *, norm_eps=-1.0, resid=None, y=No
     if ws is None:
         ws = workspace(OP_FFN_DENSE, max(bsz, 1), d, f, device=x.device)
     _check(lib().sirius_ffn_dense(_ptr(x), bsz, _ptr(w_gate), _ptr(w_up), _ptr(w_down), d, f,
-                                  float(norm_eps), _ptr(resid), _ptr(y), _ptr(ws), ws.numel(), _stream(stream)))
+                                  float(norm_eps), _ptr(resid), _ptr(y), _ptr(ws), ws.numel(), _handle()))
     return y
 
 
 def sirius_ffn_condensed(x, w_gate_c, w_up_c, w_down_c, *, norm_eps=-1.0, resid=None, y=None, ws=None,
                          stream=None):
+    if stream is not None:
+        return _on(stream, sirius_ffn_condensed, locals())
     torch = _torch()
     d, k = _w_dims(w_gate_c, w_up_c, w_down_c)
     _need(x.dtype == torch.float32 and x.dim() == 2 and x.shape[1] == d, "x must be fp32 [B, d_model]")
@@ -203,7 +237,7 @@ def sirius_ffn_condensed(x, w_gate_c, w_up_c, w_down_c, *, norm_eps=-1.0, resid=
         ws = workspace(OP_FFN_CONDENSED, max(bsz, 1), d, k, device=x.device)
     _check(lib().sirius_ffn_condensed(_ptr(x), bsz, _ptr(w_gate_c), _ptr(w_up_c), _ptr(w_down_c), d, k,
                                       float(norm_eps), _ptr(resid), _ptr(y), _ptr(ws), ws.numel(),
-                                      _stream(stream)))
+                                      _handle()))
     return y
 
 
@@ -211,6 +245,8 @@ def sirius_ffn_cats(x, w_gate, w_up, w_down, t, *, norm_eps=-1.0, resid=None, y=
                     active_cnt=None, want_active=True, ws=None, stream=None):
     """Returns (y, active_idx [B, d_ff] int32, active_cnt [B] int32); the lists are None when
     want_active is False and none were passed."""
+    if stream is not None:
+        return _on(stream, sirius_ffn_cats, locals())
     torch = _torch()
     d, f = _w_dims(w_gate, w_up, w_down)
     _need(x.dtype == torch.float32 and x.dim() == 2 and x.shape[1] == d, "x must be fp32 [B, d_model]")
@@ -225,7 +261,7 @@ def sirius_ffn_cats(x, w_gate, w_up, w_down, t, *, norm_eps=-1.0, resid=None, y=
         ws = workspace(OP_FFN_CATS, max(bsz, 1), d, f, device=x.device)
     _check(lib().sirius_ffn_cats(_ptr(x), bsz, _ptr(w_gate), _ptr(w_up), _ptr(w_down), d, f, float(t),
                                  float(norm_eps), _ptr(resid), _ptr(y), _ptr(active_idx), _ptr(active_cnt),
-                                 _ptr(ws), ws.numel(), _stream(stream)))
+                                 _ptr(ws), ws.numel(), _handle()))
     return y, active_idx, active_cnt
 
 
@@ -233,6 +269,8 @@ def sirius_ffn_cats_noalloc(x, w_gate, w_up, w_down, t, *, norm_eps=-1.0, resid=
                             active_cnt=None, want_active=True, stream=None):
     """sirius_ffn_cats on the library's fixed device scratch (no workspace). Returns (y, active_idx,
     active_cnt) as sirius_ffn_cats; pass y and the lists to allocate nothing here either."""
+    if stream is not None:
+        return _on(stream, sirius_ffn_cats_noalloc, locals())
     torch = _torch()
     d, f = _w_dims(w_gate, w_up, w_down)
     _need(x.dtype == torch.float32 and x.dim() == 2 and x.shape[1] == d, "x must be fp32 [B, d_model]")
@@ -245,7 +283,7 @@ def sirius_ffn_cats_noalloc(x, w_gate, w_up, w_down, t, *, norm_eps=-1.0, resid=
     _dev_check(x, w_gate, w_up, w_down, resid, y, active_idx, active_cnt)
     _check(lib().sirius_ffn_cats_noalloc(_ptr(x), bsz, _ptr(w_gate), _ptr(w_up), _ptr(w_down), d, f, float(t),
                                          float(norm_eps), _ptr(resid), _ptr(y), _ptr(active_idx),
-                                         _ptr(active_cnt), _stream(stream)))
+                                         _ptr(active_cnt), _handle()))
     return y, active_idx, active_cnt
 
 
@@ -253,6 +291,8 @@ def sirius_ffn_topk(x, w_gate, w_up, w_down, k, *, norm_eps=-1.0, resid=None, y=
                     active_cnt=None, want_active=True, ws=None, stream=None):
     """Per-token top-k sparse FFN. x [B, d_model] fp32; weights bf16 [d_ff, d_model].
     Returns (y, active_idx [B, d_ff] or None, active_cnt [B] or None)."""
+    if stream is not None:
+        return _on(stream, sirius_ffn_topk, locals())
     torch = _torch()
     _need(x.dtype == torch.float32 and x.dim() == 2, "x must be fp32 [B, d_model]")
     d, f = _w_dims(w_gate, w_up, w_down)
@@ -269,12 +309,14 @@ def sirius_ffn_topk(x, w_gate, w_up, w_down, k, *, norm_eps=-1.0, resid=None, y=
         ws = workspace(OP_FFN_TOPK, max(bsz, 1), d, f, device=dev)
     _check(lib().sirius_ffn_topk(_ptr(x), bsz, _ptr(w_gate), _ptr(w_up), _ptr(w_down), d, f, int(k),
                                  float(norm_eps), _ptr(resid), _ptr(y), _ptr(active_idx), _ptr(active_cnt),
-                                 _ptr(ws), ws.numel(), _stream(stream)))
+                                 _ptr(ws), ws.numel(), _handle()))
     return y, active_idx, active_cnt
 
 
 def sirius_cats_calibrate(x_cal, w_gate, q, *, t_out=None, ws=None, stream=None):
     """Returns a 1-element fp32 device tensor holding the threshold."""
+    if stream is not None:
+        return _on(stream, sirius_cats_calibrate, locals())
     torch = _torch()
     f, d = int(w_gate.shape[0]), int(w_gate.shape[1])
     _need(x_cal.dtype == torch.float32 and x_cal.dim() == 2 and x_cal.shape[1] == d, "x_cal must be fp32 [N, d]")
@@ -285,7 +327,7 @@ def sirius_cats_calibrate(x_cal, w_gate, q, *, t_out=None, ws=None, stream=None)
     if ws is None:
         ws = workspace(OP_CATS_CALIBRATE, n, d, f, device=x_cal.device)
     _check(lib().sirius_cats_calibrate(_ptr(x_cal), n, _ptr(w_gate), d, f, float(q), _ptr(t_out), _ptr(ws),
-                                       ws.numel(), _stream(stream)))
+                                       ws.numel(), _handle()))
     return t_out
 
 
@@ -293,6 +335,8 @@ def sirius_griffin_select(x_prompt, w_gate, w_up, w_down, k, *, normalize_tokens
                           scores=None, want_scores=True, w_gate_c=None, w_up_c=None, w_down_c=None, ws=None,
                           stream=None):
     """Returns (sel_idx [k] int32, scores [d_ff] fp32 or None, w_gate_c, w_up_c, w_down_c)."""
+    if stream is not None:
+        return _on(stream, sirius_griffin_select, locals())
     torch = _torch()
     d, f = _w_dims(w_gate, w_up, w_down)
     _need(x_prompt.dim() == 2 and x_prompt.shape[1] == d and x_prompt.element_size() == 2,
@@ -313,7 +357,7 @@ def sirius_griffin_select(x_prompt, w_gate, w_up, w_down, k, *, normalize_tokens
         ws = workspace(OP_GRIFFIN_SELECT, 0, d, f, t_n, device=dev)
     _check(lib().sirius_griffin_select(_ptr(x_prompt), t_n, _ptr(w_gate), _ptr(w_up), _ptr(w_down), d, f, k,
                                        1 if normalize_tokens else 0, _ptr(sel_idx), _ptr(scores), _ptr(w_gate_c),
-                                       _ptr(w_up_c), _ptr(w_down_c), _ptr(ws), ws.numel(), _stream(stream)))
+                                       _ptr(w_up_c), _ptr(w_down_c), _ptr(ws), ws.numel(), _handle()))
     return sel_idx, scores, w_gate_c, w_up_c, w_down_c
 
 
@@ -321,6 +365,8 @@ def sirius_verify_accept(logits, drafted, r, temperature=1.0, *, accept_len=None
                          p_draft=None, want_p=True, ws=None, stream=None):
     """logits [B, R, V] fp32 (R = K or K + 1), drafted [B, K] int32.
     Returns (accept_len [B] int32, next_token [B] int32, p_draft [B, K] fp32 or None)."""
+    if stream is not None:
+        return _on(stream, sirius_verify_accept, locals())
     torch = _torch()
     _need(logits.dtype == torch.float32 and logits.dim() == 3, "logits must be fp32 [B, R, V]")
     _need(drafted.dtype == torch.int32 and drafted.dim() == 2 and drafted.shape[0] == logits.shape[0],
@@ -338,7 +384,7 @@ def sirius_verify_accept(logits, drafted, r, temperature=1.0, *, accept_len=None
         ws = workspace(OP_VERIFY, max(bsz, 1), 0, 0, vocab, rows, device=dev)
     _check(lib().sirius_verify_accept(_ptr(logits), bsz, k, rows, vocab, _ptr(drafted), float(r),
                                       float(temperature), _ptr(accept_len), _ptr(next_token), _ptr(p_draft),
-                                      _ptr(ws), ws.numel(), _stream(stream)))
+                                      _ptr(ws), ws.numel(), _handle()))
     return accept_len, next_token, p_draft
 
 
@@ -346,6 +392,8 @@ def sirius_tree_build_step(logits, width, cum_ll=None, temperature=1.0, *, token
                            cum_ll_out=None, ws=None, stream=None):
     """logits [B, Wc, V] fp32 at the current leaves, cum_ll [B, Wc] fp32 or None (the root).
     Returns (tokens [B, W] int32, parents [B, W] int32, cum_ll_out [B, W] fp32), best first."""
+    if stream is not None:
+        return _on(stream, sirius_tree_build_step, locals())
     torch = _torch()
     _need(logits.dtype == torch.float32 and logits.dim() == 3, "logits must be fp32 [B, Wc, V]")
     bsz, wc, vocab = (int(s) for s in logits.shape)
@@ -362,7 +410,7 @@ def sirius_tree_build_step(logits, width, cum_ll=None, temperature=1.0, *, token
         ws = workspace(OP_TREE_BUILD, max(bsz, 1), wc, w, vocab, 0, device=dev)
     _check(lib().sirius_tree_build_step(_ptr(logits), bsz, wc, vocab, _ptr(cum_ll), w, float(temperature),
                                         _ptr(tokens), _ptr(parents), _ptr(cum_ll_out), _ptr(ws), ws.numel(),
-                                        _stream(stream)))
+                                        _handle()))
     return tokens, parents, cum_ll_out
 
 
@@ -370,6 +418,8 @@ def sirius_tree_verify(logits, tokens, parents, r, temperature=1.0, *, bonus=Fal
                        accept_len=None, next_token=None, q=None, want_q=True, ws=None, stream=None):
     """logits [B, K*W (+W with bonus), V] fp32, tokens / parents [B, K, W] int32.
     Returns (best_leaf [B], accept_len [B], next_token [B] int32, q [B, K, W] fp32 or None)."""
+    if stream is not None:
+        return _on(stream, sirius_tree_verify, locals())
     torch = _torch()
     _need(tokens.dtype == torch.int32 and tokens.dim() == 3, "tokens must be int32 [B, K, W]")
     _need(parents.dtype == torch.int32 and tuple(parents.shape) == tuple(tokens.shape),
@@ -391,7 +441,7 @@ def sirius_tree_verify(logits, tokens, parents, r, temperature=1.0, *, bonus=Fal
         ws = workspace(OP_TREE_VERIFY, max(bsz, 1), k, w, vocab, 1 if bonus else 0, device=dev)
     _check(lib().sirius_tree_verify(_ptr(logits), bsz, k, w, vocab, 1 if bonus else 0, _ptr(tokens), _ptr(parents),
                                     float(r), float(temperature), _ptr(best_leaf), _ptr(accept_len),
-                                    _ptr(next_token), _ptr(q), _ptr(ws), ws.numel(), _stream(stream)))
+                                    _ptr(next_token), _ptr(q), _ptr(ws), ws.numel(), _handle()))
     return best_leaf, accept_len, next_token, q
 
 
@@ -404,6 +454,8 @@ def sirius_attn_kv(q, k_new, v_new, k_cache, v_cache, cache_pos, *, out=None, ws
     """q [B, n, H, hd] fp32; k_new, v_new [B, n, Hkv, hd] bf16; caches [B, Lmax, Hkv, hd] bf16
     (updated in place: rows cache_pos[b] .. + n - 1 take the new keys and values);
     cache_pos [B] int32 on the GPU. Returns out [B, n, H, hd] fp32."""
+    if stream is not None:
+        return _on(stream, sirius_attn_kv, locals())
     torch = _torch()
     _need(q.dtype == torch.float32 and q.dim() == 4, "q must be fp32 [B, n, H, hd]")
     bsz, n, h, hd = (int(s) for s in q.shape)
@@ -423,36 +475,42 @@ def sirius_attn_kv(q, k_new, v_new, k_cache, v_cache, cache_pos, *, out=None, ws
     if ws is None:
         ws = workspace(OP_ATTN_KV, max(bsz, 1), n, h * 65536 + hkv, hd, lmax, device=q.device)
     _check(lib().sirius_attn_kv(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache), _ptr(cache_pos),
-                                bsz, n, h, hkv, hd, lmax, _ptr(out), _ptr(ws), ws.numel(), _stream(stream)))
+                                bsz, n, h, hkv, hd, lmax, _ptr(out), _ptr(ws), ws.numel(), _handle()))
     return out
 
 
 def sirius_kv_rollback(cache_pos, accept_len, n, *, stream=None):
     """cache_pos[b] += min(accept_len[b] + 1, n), on the GPU."""
+    if stream is not None:
+        return _on(stream, sirius_kv_rollback, locals())
     torch = _torch()
     _need(cache_pos.dtype == torch.int32 and accept_len.dtype == torch.int32, "int32 tensors expected")
     _need(cache_pos.shape == accept_len.shape and cache_pos.dim() == 1, "cache_pos and accept_len must be [B]")
     _dev_check(cache_pos, accept_len)
     _check(lib().sirius_kv_rollback(_ptr(cache_pos), _ptr(accept_len), int(cache_pos.shape[0]), int(n),
-                                    _stream(stream)))
+                                    _handle()))
     return cache_pos
 
 
 def sirius_rmsnorm(h, eps=1e-5, *, out=None, stream=None):
+    if stream is not None:
+        return _on(stream, sirius_rmsnorm, locals())
     torch = _torch()
     _need(h.dtype == torch.float32 and h.dim() == 2, "h must be fp32 [B, d_model]")
     if out is None:
         out = torch.empty_like(h)
     _dev_check(h, out)
-    _check(lib().sirius_rmsnorm(_ptr(h), int(h.shape[0]), int(h.shape[1]), float(eps), _ptr(out), _stream(stream)))
+    _check(lib().sirius_rmsnorm(_ptr(h), int(h.shape[0]), int(h.shape[1]), float(eps), _ptr(out), _handle()))
     return out
 
 
 def sirius_fill_normal_bf16(out, seed, mean=0.0, std=1.0, *, stream=None):
+    if stream is not None:
+        return _on(stream, sirius_fill_normal_bf16, locals())
     _dev_check(out)
     _need(out.element_size() == 2, "out must be a 16-bit (bf16) tensor")
     _check(lib().sirius_fill_normal_bf16(_ptr(out), out.numel(), int(seed) & 0xFFFFFFFFFFFFFFFF, float(mean),
-                                         float(std), _stream(stream)))
+                                         float(std), _handle()))
     return out
 
 
@@ -546,6 +604,8 @@ def sirius_model_forward(model: Model, tokens, cache_pos, sparse: bool, *, logit
                          ws=None, stream=None):
     """tokens [n] int32, cache_pos [1] int32 (device). Returns (logits [n, V] fp32, active_idx
     [L, n, d_ff], active_cnt [L, n]) -- the lists None unless want_active (sparse only)."""
+    if stream is not None:
+        return _on(stream, sirius_model_forward, locals())
     torch = _torch()
     _need(tokens.dtype == torch.int32 and tokens.dim() == 1, "tokens must be int32 [n]")
     _need(cache_pos.dtype == torch.int32 and tuple(cache_pos.shape) == (1,), "cache_pos must be int32 [1]")
@@ -562,7 +622,7 @@ def sirius_model_forward(model: Model, tokens, cache_pos, sparse: bool, *, logit
         ws = _model_ws(model, n)
     _check(lib().sirius_model_forward(model.ptr, _ptr(tokens), n, _ptr(cache_pos), 1 if sparse else 0,
                                       _ptr(logits), _ptr(aidx), _ptr(acnt), _ptr(ws), ws.numel(),
-                                      _stream(stream)))
+                                      _handle()))
     return logits, aidx, acnt
 
 
@@ -571,6 +631,8 @@ def sirius_generate(model: Model, seq, cache_pos, n: int, r: float, periods: int
     """seq [n + 1] int32 (seq[0] = the first input), cache_pos [1] int32, both on the device and
     updated. Returns (out_tokens [periods * n], out_count [1], trace dict or None); out_count is
     zeroed here unless passed in."""
+    if stream is not None:
+        return _on(stream, sirius_generate, locals())
     torch = _torch()
     _need(seq.dtype == torch.int32 and tuple(seq.shape) == (n + 1,), "seq must be int32 [n + 1]")
     _need(cache_pos.dtype == torch.int32 and tuple(cache_pos.shape) == (1,), "cache_pos must be int32 [1]")
@@ -599,5 +661,5 @@ def sirius_generate(model: Model, seq, cache_pos, n: int, r: float, periods: int
     _check(lib().sirius_generate(model.ptr, _ptr(seq), _ptr(cache_pos), int(n), float(r), int(periods),
                                  _ptr(out_tokens), _ptr(out_count),
                                  None if tc is None else ctypes.byref(tc), _ptr(ws), ws.numel(),
-                                 _stream(stream)))
+                                 _handle()))
     return out_tokens, out_count, tr
