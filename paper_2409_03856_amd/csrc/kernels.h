@@ -242,8 +242,8 @@ struct StepSource {
   float* h_out = nullptr;
 };
 // Whether every workgroup of the projection can form its row itself for less than a launch.
-bool step_takes_partials(int K, int nseg);
-bool step_takes_logits(int V, int N);  // N output rows
+bool step_takes_partials(int K, int nseg, int N);  // N output rows
+bool step_takes_logits(int V, int N);
 // One token's products: RMSNorm (unit weight, bit for bit rmsnorm_vec_kernel's result) of the row
 // [K], then q = xn Wq^T [Nq] fp32 and, for Nkv > 0, k = xn Wk^T, v = xn Wv^T [Nkv] bf16 in one launch.
 // K % 8 == 0, K <= 8192, 16-byte aligned rows.

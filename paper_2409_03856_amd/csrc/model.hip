@@ -347,9 +347,13 @@ hipError_t launch_norm_qkv(const StepSource& src, int K, float eps, const uint16
 }
 
 // What every workgroup of the launch reads for itself comes from L2 at about 8 TB/s over the chip:
-// at most 2 us of partials (the launch that it saves takes 3-4) and 1 us of logits.
-bool step_takes_partials(int K, int nseg) {
-  return K <= kLinMaxPartK && (size_t)kPartBlocks * nseg * K * sizeof(float) <= (size_t)16 << 20;
+// at most 1.5 us of partials and 1 us of logits. The kPartBlocks workgroups that take partials also
+// take all N rows, where the separate sum (3-4 us) leaves up to 2048 workgroups to them: at most three
+// rows per wave. At 256 x 688 the fold saves 1.5 us per projection of 300-1000 rows, 0 at 2000 and
+// costs 3 at 8000 and 10 at 16000; at 512 x 1024 (2 us of partials) it saves nothing at 300.
+bool step_takes_partials(int K, int nseg, int N) {
+  return K <= kLinMaxPartK && N <= 3 * kPartBlocks * kLinWaves &&
+         (size_t)kPartBlocks * nseg * K * sizeof(float) <= (size_t)12 << 20;
 }
 bool step_takes_logits(int V, int N) {
   return (size_t)std::min(ceil_div(N, kLinWaves), 2048) * V * sizeof(float) <= (size_t)8 << 20;

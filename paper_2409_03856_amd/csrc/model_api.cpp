@@ -148,7 +148,8 @@ hipError_t forward_one(const sirius_model* m, const int32_t* token, const DraftB
   float* att = reinterpret_cast<float*>(ws + L.att);
   char* sub = ws + L.sub;
   const sirius::Decode1Layout DL = sirius::decode1_layout(d, F);
-  const bool partials = aidx == nullptr && sirius::step_takes_partials(d, DL.nseg);
+  // an FFN's partials stay in the workspace where the projection that follows (n rows) takes them
+  auto left = [&](int n) { return aidx == nullptr && sirius::step_takes_partials(d, DL.nseg, n); };
   const float* part = reinterpret_cast<const float*>(sub + DL.part);
   sirius::StepSource src;
   src.embed = m->embed;
@@ -164,7 +165,7 @@ hipError_t forward_one(const sirius_model* m, const int32_t* token, const DraftB
   }
   hipError_t e;
   // the source of the projection that follows an FFN
-  auto after_ffn = [&]() {
+  auto after_ffn = [&](bool partials) {
     src = sirius::StepSource{};
     src.x = h;
     if (partials) {
@@ -182,13 +183,14 @@ hipError_t forward_one(const sirius_model* m, const int32_t* token, const DraftB
                                     cache_pos, 1, 1, H, Hkv, hd, m->max_len, att, sub, AL, s)) != hipSuccess)
       return e;
     if ((e = sirius::launch_linear(att, m->wo + l * st.o, hq, d, h, h, s)) != hipSuccess) return e;
+    const bool partials = left(l + 1 < m->n_layers ? hq + 2 * hkv : m->vocab);
     if ((e = sirius::launch_ffn_decode1(
              h, m->w_gate + l * st.ffn, m->w_up + l * st.ffn, m->w_down + l * st.ffn, d, F,
              sparse ? sirius::kFfnModeThreshold : sirius::kFfnModeDense, sparse ? m->thresholds[l] : 0.f,
              m->norm_eps, h, partials ? nullptr : h, aidx ? aidx + l * a_lstride : nullptr,
              acnt ? acnt + l * c_lstride : nullptr, sub, DL, s)) != hipSuccess)
       return e;
-    after_ffn();
+    after_ffn(partials);
   }
   return sirius::launch_norm_qkv(src, d, m->norm_eps, m->lm_head, m->vocab, nullptr, nullptr, 0, logits,
                                  nullptr, nullptr, s);

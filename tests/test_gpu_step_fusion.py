@@ -76,3 +76,29 @@ def test_dense_one_token_pass_and_unknown_token():
     two, _, _ = sr.sirius_model_forward(m, dev_i32(np.array([7, 8], np.int32)), pos, False)
     a, b = host(one)[0], host(two)[0]
     assert np.max(np.abs(a - b)) <= 1e-4 * np.sqrt(np.mean(b * b))
+
+
+@pytest.mark.parametrize("d,f,vocab,sums", [(256, 688, 1000, 0), (256, 688, 1536, 0), (256, 688, 1537, 1),
+                                            (256, 688, 32000, 1), (512, 1024, 1000, 2)])
+def test_partials_are_folded_into_few_rows_only(d, f, vocab, sums):
+    """The 128 workgroups of a launch that adds the FFN's partials itself serve at most 1536 output rows:
+    the LM head of a larger vocabulary follows a separate sum (one per FFN whose partials are summed so),
+    and partials that would be read for 1.5 us and more are summed once."""
+    import torch
+    import paper_2409_03856_amd as sr
+    say(f"fold of partials d={d} f={f} v={vocab}")
+    s = ModelShape("fusion", 2, d, f, 4, 2, 64, vocab, 64, 6.0)
+    m = sr.Model({k: dev_bf16(b) for k, b in model_weights(5, s).items()}, 4, 2, 64, 64, [0.1] * 2)
+    pos = torch.zeros(1, dtype=torch.int32, device="cuda")
+    tok = dev_i32(np.array([3], np.int32))
+    sr.sirius_model_forward(m, tok, pos, True)
+    sr.sirius_profile_reset()
+    sr.sirius_profile_enable(True)
+    try:
+        sr.sirius_model_forward(m, tok, pos, True)
+        torch.cuda.synchronize()
+        n = sr.sirius_profile_query("cats_reduce")[1]
+    finally:
+        sr.sirius_profile_enable(False)
+        sr.sirius_profile_reset()
+    assert n == sums
