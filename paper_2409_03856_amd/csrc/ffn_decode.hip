@@ -37,7 +37,6 @@ namespace {
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / kWave;  // 16
 constexpr int kSegs = 256;                // one workgroup per CU
-constexpr int kMinRows = 8;               // rows per segment at least (small d_ff)
 constexpr int kMaxRows = 256;             // rows per segment at most: d_ff <= 65536
 constexpr int kMaxD = 8192;               // x staged in LDS: 32 KiB
 constexpr int kDownUnroll = 8;            // W_down row chunks in flight per thread
@@ -327,11 +326,9 @@ hipError_t launch_mode(int cpl, int G, hipStream_t s, const float* x, const uint
 
 }  // namespace
 
-Decode1Layout decode1_layout(int d, int F) {
+Decode1Layout decode1_layout(int d, int F, int min_rows) {
   Decode1Layout L{};
-  // A small layer is bound by latency: a row per wave, and half the partials for what follows.
-  const int rows = (long)d * F <= (1l << 20) ? kWaves : kMinRows;
-  L.nseg = std::max(1, std::min(kSegs, ceil_div(F, rows)));
+  L.nseg = std::max(1, std::min(kSegs, ceil_div(F, min_rows)));
   L.rmax = ceil_div(F, L.nseg);
   Carve c;
   L.uidx = c.take((size_t)L.nseg * L.rmax * 4);

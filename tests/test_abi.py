@@ -320,6 +320,17 @@ def _fake_model(**kw):
     return m
 
 
+def test_single_token_ffn_keeps_segments_of_eight_neurons(L):
+    """A call by itself: partials of d_ff / 8 segments (at most 256), each of d_model floats, and the kept
+    lists, each region in whole 256 bytes."""
+    up = lambda n: (n + 255) // 256 * 256
+    for d, f in ((64, 128), (512, 1376), (768, 1365), (1024, 1024), (4096, 14336)):
+        seg = min(256, -(-f // 8))
+        want = up(seg * -(-f // seg) * 4) + up(seg * 4) + up(seg * d * 4)
+        for op in (0, 1):
+            assert L.sirius_workspace_size(op, 1, d, f, 0, 0) == want, (op, d, f)
+
+
 def test_attention_workspace_of_the_largest_call_serves_the_smaller_ones(L):
     import random
     rng = random.Random(4)
