@@ -11,19 +11,22 @@
 //
 //  tree_topw_kernel    grid (segments, B * Wc): each workgroup reads one segment of 2048 or 4096
 //                      logits of one leaf's row, every thread a contiguous run of 8 or 16 (all
-//                      loads in flight). W rounds of a DPP wave maximum over the lanes' largest
-//                      remaining values give each wave's W best (the lowest lane wins a tie, so
-//                      the lowest token does); one wave ranks the four lists by counting. The
-//                      softmax statistics (max, sum of exp((v - max) / T) in fp64) merge on the
-//                      common maximum.
+//                      loads in flight). Lists of 4 and 8: W rounds of a DPP wave maximum over the
+//                      lanes' largest remaining values give each wave's W best (the lowest lane
+//                      wins a tie, so the lowest token does); one wave ranks the four lists by
+//                      counting. Lists of 16: the keys above a bound from group maxima, ranked by
+//                      counting. The softmax statistics (max, sum of exp((v - max) / T) in fp64)
+//                      merge on the common maximum.
 //  tree_select_kernel  one workgroup per tree, one wave per leaf: the segment statistics merge on
 //                      the common maximum into log-likelihood (v - max) / T - log(sum), W rounds of
 //                      a DPP wave maximum over the segment lists' heads give the leaf's W best
 //                      tokens, and the Wc x W scored candidates are ranked by counting.
 //
 // Bound: two launches of short dependent chains (a 4 x 128256 step reads 2 MB). Lists are as long
-// as the class of W (4, 8 or 16), so that a narrow tree pays for its own width only: 5.2 and 4.8 us there (8.9 and
-// 8.9 with lists of 16, per-pass group bounds and a merge of the statistics per butterfly step).
+// as the class of W (4, 8 or 16), so that a narrow tree pays for its own width only: W = 4 takes 5.2
+// and 4.8 us there (8.9 and 8.9 with lists of 16, per-pass group bounds and a merge of the statistics
+// per butterfly step). Eight trees of 16 leaves with W = 16 take 68 us (88 with passes of a running
+// list, 128 with wave rounds).
 #include <math.h>
 
 #include "common.h"
@@ -110,12 +113,92 @@ __device__ __forceinline__ void wave_stats(float& m, double& s, float c) {
 
 typedef float f32x4_unaligned_t __attribute__((ext_vector_type(4), aligned(4)));
 
+__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
+  const uint32_t lo = __shfl_xor((uint32_t)v, m, kWave);
+  const uint32_t hi = __shfl_xor((uint32_t)(v >> 32), m, kWave);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// The workgroup's W best of E keys per thread (0 = none), best first, into s_best[0 .. kKW) with 0 past
+// the last. The threads form G interleaved groups (G the power of two at or above W): the W best are at
+// least the W-th largest group maximum, so only the keys at or above that bound (usually a handful)
+// are gathered and ranked by counting.
+constexpr int kRankBatch = 16;  // LDS reads in flight per step of a rank-by-counting loop
+template <int E>
+__device__ void bound_best(const uint64_t (&key)[E], int W, uint64_t* __restrict__ s_best) {
+  __shared__ uint64_t s_cand[kTopThreads * E + kRankBatch];
+  __shared__ uint64_t s_g[kTopWaves * kKW];  // group maxima per wave
+  __shared__ uint64_t s_bound;
+  __shared__ int s_scan[kTopWaves];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+  int G = 1;
+  while (G < W) G <<= 1;
+  uint64_t gk = 0;
+#pragma unroll
+  for (int j = 0; j < E; ++j) gk = key[j] > gk ? key[j] : gk;
+  for (int k = G; k < kWave; k <<= 1) {
+    const uint64_t o = shfl_xor_u64(gk, k);
+    gk = o > gk ? o : gk;
+  }
+  if (lane < G) s_g[wave * kKW + lane] = gk;
+  if (tid == 0) s_bound = 0;
+  if (tid < kKW) s_best[tid] = 0;
+  __syncthreads();
+  if (tid < G) {
+    uint64_t gm[kKW];
+#pragma unroll
+    for (int g = 0; g < kKW; ++g) {
+      uint64_t x = 0;
+#pragma unroll
+      for (int w = 0; w < kTopWaves; ++w) {
+        const uint64_t y = s_g[w * kKW + g];
+        x = y > x ? y : x;
+      }
+      gm[g] = g < G ? x : 0;
+    }
+    uint64_t mine = 0;
+#pragma unroll
+    for (int g = 0; g < kKW; ++g) mine = g == tid ? gm[g] : mine;
+    int r = 0;
+#pragma unroll
+    for (int g = 0; g < kKW; ++g) r += gm[g] > mine;
+    if (mine != 0 && r == W - 1) s_bound = mine;
+  }
+  __syncthreads();
+  const uint64_t bound = s_bound;
+  int n = 0, ncand = 0;
+#pragma unroll
+  for (int j = 0; j < E; ++j) n += (key[j] != 0 && key[j] >= bound);
+  int pos = block_exclusive_scan_256(n, s_scan, &ncand);
+#pragma unroll
+  for (int j = 0; j < E; ++j)
+    if (key[j] != 0 && key[j] >= bound) s_cand[pos++] = key[j];
+  const int npad = (ncand + kRankBatch - 1) / kRankBatch * kRankBatch;
+  if (tid < npad - ncand) s_cand[ncand + tid] = 0;  // empty: never counted as larger
+  __syncthreads();
+  for (int i = tid; i < ncand; i += kTopThreads) {
+    const uint64_t k0 = s_cand[i];
+    int r = 0;
+    for (int j = 0; j < npad; j += kRankBatch) {
+      uint64_t buf[kRankBatch];
+#pragma unroll
+      for (int q = 0; q < kRankBatch; ++q) buf[q] = s_cand[j + q];
+#pragma unroll
+      for (int q = 0; q < kRankBatch; ++q) r += (int)(buf[q] > k0);
+    }
+    if (r < W) s_best[r] = k0;
+  }
+  __syncthreads();
+}
+
 // E logits per thread; lists of KW entries (W <= KW).
 template <int E, int KW>
 __global__ __launch_bounds__(kTopThreads) void tree_topw_kernel(
     const float* __restrict__ logits, int V, int W, float c, float* __restrict__ rm,
     double* __restrict__ rs, uint64_t* __restrict__ rk) {
-  __shared__ uint64_t s_c[kTopWaves * KW];
+  // one list per wave, ranked into one at the end; the longest lists are formed by the workgroup at once
+  constexpr bool kBound = KW == kKW;
+  __shared__ uint64_t s_c[kBound ? KW : kTopWaves * KW];
   __shared__ float s_m[kTopWaves];
   __shared__ double s_s[kTopWaves];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
@@ -135,7 +218,7 @@ __global__ __launch_bounds__(kTopThreads) void tree_topw_kernel(
 #pragma unroll
     for (int j = 0; j < E; ++j) v[j] = (e0 + j < V) ? L[e0 + j] : -INFINITY;
   }
-  if (tid < kTopWaves * KW) s_c[tid] = 0;
+  if (!kBound && tid < kTopWaves * KW) s_c[tid] = 0;
   // softmax statistics of the thread: exps summed pairwise in fp32 (at most 16 terms, each <= 1)
   float m = -INFINITY;
 #pragma unroll
@@ -150,29 +233,38 @@ __global__ __launch_bounds__(kTopThreads) void tree_topw_kernel(
 #pragma unroll
     for (int g = 0; g < E / 4; g += 2 * k) t[g] += t[g + k];
   double s = m > -INFINITY ? (double)t[0] : 0.0;  // -inf logits add nothing
-  uint32_t o[E], lm = 0;
+  const size_t at = (size_t)row * splits + split;
+  if constexpr (kBound) {
+    uint64_t key[E];
 #pragma unroll
-  for (int j = 0; j < E; ++j) {
-    o[j] = (e0 + j < V) ? ordered_bits(v[j]) : 0u;
-    lm = o[j] > lm ? o[j] : lm;
-  }
-  __syncthreads();
-  // the wave's W best, best first
-  for (int r = 0; r < W; ++r) {
-    const uint32_t best = wave_max_u32(lm);
-    if (best == 0u) break;  // uniform: nothing left
-    const bool win = lane == __builtin_ctzll(__ballot(lm == best));
-    int jj = 0;
-#pragma unroll
-    for (int j = E - 1; j >= 0; --j) jj = o[j] == best ? j : jj;
-    if (win) s_c[wave * KW + r] = ((uint64_t)best << 32) | (uint64_t)(~(uint32_t)(e0 + jj));
-    uint32_t next = 0;
+    for (int j = 0; j < E; ++j) key[j] = e0 + j < V ? make_key(v[j], e0 + j) : 0;
+    bound_best<E>(key, W, s_c);
+    if (tid < KW) rk[at * KW + tid] = s_c[tid];
+  } else {
+    uint32_t o[E], lm = 0;
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      o[j] = (win && j == jj) ? 0u : o[j];
-      next = o[j] > next ? o[j] : next;
+      o[j] = (e0 + j < V) ? ordered_bits(v[j]) : 0u;
+      lm = o[j] > lm ? o[j] : lm;
     }
-    lm = next;
+    __syncthreads();
+    // the wave's W best, best first
+    for (int r = 0; r < W; ++r) {
+      const uint32_t best = wave_max_u32(lm);
+      if (best == 0u) break;  // uniform: nothing left
+      const bool win = lane == __builtin_ctzll(__ballot(lm == best));
+      int jj = 0;
+#pragma unroll
+      for (int j = E - 1; j >= 0; --j) jj = o[j] == best ? j : jj;
+      if (win) s_c[wave * KW + r] = ((uint64_t)best << 32) | (uint64_t)(~(uint32_t)(e0 + jj));
+      uint32_t next = 0;
+#pragma unroll
+      for (int j = 0; j < E; ++j) {
+        o[j] = (win && j == jj) ? 0u : o[j];
+        next = o[j] > next ? o[j] : next;
+      }
+      lm = next;
+    }
   }
   wave_stats(m, s, c);
   if (lane == 0) {
@@ -181,20 +273,21 @@ __global__ __launch_bounds__(kTopThreads) void tree_topw_kernel(
   }
   __syncthreads();
   if (wave != 0) return;
-  const size_t at = (size_t)row * splits + split;
-  // rank the four lists by counting (non-empty keys are distinct)
-  constexpr int kN = kTopWaves * KW;
-  const uint64_t key = lane < kN ? s_c[lane] : 0;
-  int rank = 0, n = 0;
+  if constexpr (!kBound) {
+    // rank the four lists by counting (non-empty keys are distinct)
+    constexpr int kN = kTopWaves * KW;
+    const uint64_t key = lane < kN ? s_c[lane] : 0;
+    int rank = 0, n = 0;
 #pragma unroll
-  for (int i = 0; i < kN; ++i) {
-    const uint64_t k = s_c[i];
-    rank += (int)(k > key);
-    n += (int)(k != 0);
+    for (int i = 0; i < kN; ++i) {
+      const uint64_t k = s_c[i];
+      rank += (int)(k > key);
+      n += (int)(k != 0);
+    }
+    if (key != 0 && rank < W) rk[at * KW + rank] = key;
+    if (lane >= n && lane < KW) rk[at * KW + lane] = 0;
+    if (lane < KW && lane >= W) rk[at * KW + lane] = 0;
   }
-  if (key != 0 && rank < W) rk[at * KW + rank] = key;
-  if (lane >= n && lane < KW) rk[at * KW + lane] = 0;
-  if (lane < KW && lane >= W) rk[at * KW + lane] = 0;
   if (lane == 0) {
     float am = s_m[0];
 #pragma unroll
@@ -303,8 +396,9 @@ int list_len(int W) { return W <= 4 ? 4 : (W <= 8 ? 8 : kKW); }
 TreeBuildLayout tree_build_layout(int B, int Wc, int W, int V) {
   TreeBuildLayout L{};
   const int rows = std::max(1, B * Wc);
-  // eight logits per thread (twice the workgroups) while a leaf's segments fit the select's lanes
-  L.splits = ceil_div(V, kTopThreads * (V <= kShortRow ? 8 : 16));
+  // eight logits per thread (twice the workgroups) while a leaf's segments fit the select's lanes; the
+  // longest lists cost a workgroup the same whatever it reads
+  L.splits = ceil_div(V, kTopThreads * (V <= kShortRow && list_len(W) < kKW ? 8 : 16));
   const size_t n = (size_t)rows * L.splits;
   Carve c;
   L.rm = c.take(n * sizeof(float));
@@ -326,17 +420,18 @@ hipError_t launch_tree_build(const float* logits, int B, int Wc, int V, const fl
   const dim3 grid(L.splits, B * Wc);
   {
     ProfScope prof("tree_topw", stream);
-#define SIRIUS_TOPW(KW)                                                                              \
-  if (V <= kShortRow)                                                                                \
-    klaunch((tree_topw_kernel<8, KW>), grid, kTopThreads, 0, stream, logits, V, W, c, rm, rs, rk);   \
-  else                                                                                               \
-    klaunch((tree_topw_kernel<16, KW>), grid, kTopThreads, 0, stream, logits, V, W, c, rm, rs, rk)
-    if (W <= 4) {
-      SIRIUS_TOPW(4);
-    } else if (W <= 8) {
-      SIRIUS_TOPW(8);
+#define SIRIUS_TOPW(E, KW) \
+  klaunch((tree_topw_kernel<E, KW>), grid, kTopThreads, 0, stream, logits, V, W, c, rm, rs, rk)
+    // Wave rounds up to lists of 8, group bounds for lists of 16: at 8 x 16 leaves of 128256 tokens the
+    // rounds take 95 us for W = 16 and the bounds 51.
+    if (W > 8) {
+      SIRIUS_TOPW(16, 16);
+    } else if (W > 4) {
+      if (V <= kShortRow) SIRIUS_TOPW(8, 8);
+      else SIRIUS_TOPW(16, 8);
     } else {
-      SIRIUS_TOPW(16);
+      if (V <= kShortRow) SIRIUS_TOPW(8, 4);
+      else SIRIUS_TOPW(16, 4);
     }
 #undef SIRIUS_TOPW
     hipError_t e = hipGetLastError();

@@ -320,6 +320,16 @@ def _fake_model(**kw):
     return m
 
 
+def test_wide_trees_take_segments_of_4096_logits(L):
+    """Widths above 8 rank a segment's candidates at once, which costs a workgroup the same for 2048 logits
+    as for 4096: one statistics pair and one list of 16 keys per 4096."""
+    up = lambda n: (n + 255) // 256 * 256
+    for w in (9, 16):
+        for wc, v in ((1, 4097), (16, 128256), (4, 152000)):
+            n = 8 * wc * -(-v // 4096)
+            assert L.sirius_workspace_size(6, 8, wc, w, v, 0) == up(4 * n) + up(8 * n) + up(8 * 16 * n), (wc, w, v)
+
+
 def test_single_token_ffn_keeps_segments_of_eight_neurons(L):
     """A call by itself: partials of d_ff / 8 segments (at most 256), each of d_model floats, and the kept
     lists, each region in whole 256 bytes."""

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("wc,width,vocab", [(2, 4, 2051), (3, 5, 131072), (2, 8, 131073), (1, 9, 600001),
-                                            (3, 16, 280005), (16, 3, 4099), (1, 1, 524293)])
+                                            (3, 16, 280005), (16, 3, 4099), (1, 1, 524293),
+                                            (16, 16, 4097), (2, 9, 131072), (1, 16, 37)])
 def test_lists(wc, width, vocab):
     import paper_2409_03856_amd as sr
     say(f"tree lists Wc={wc} W={width} V={vocab}")
