@@ -159,11 +159,11 @@ struct Seg {
   int nseg, np;
 };
 constexpr int kSegTarget = 256;
-__host__ __device__ inline Seg seg_of(int n_rows) {
-  const int rounds = (n_rows + kSegTarget * kSegN - 1) / (kSegTarget * kSegN);
+__host__ __device__ inline Seg seg_of(int n_rows, int most) {  // segments of at most `most` neurons
+  const int rounds = (n_rows + kSegTarget * most - 1) / (kSegTarget * most);
   int np = (n_rows + kSegTarget * rounds - 1) / (kSegTarget * rounds);
   np = (np + 3) & ~3;
-  if (np > kSegN) np = kSegN;
+  if (np > most) np = most;
   if (np < 4) np = 4;
   return Seg{(n_rows + np - 1) / np, np};
 }
@@ -509,11 +509,13 @@ template <int MT, int RT>
 struct FrLds {
   static constexpr int kBuf = 16 * RT * kFrPitch;
   static constexpr int kRed = kFrWaves * RT * kWave * 16;            // one token tile's partials
-  static constexpr int kRes = 16 * RT * 16 * MT * 4;
+  // token pitch of the results: the 64 rows that a wave then reads at one token in 16 banks of 64
+  static constexpr int kResPitch = 16 * MT + 4;
+  static constexpr int kRes = 16 * RT * kResPitch * 4;
   static constexpr int kBytes = 2 * kBuf > kRed + kRes ? 2 * kBuf : kRed + kRes;
 };
 
-// nrows (<= 16 RT) rows from row_of(r), r < nrows; returns res[16 MT * row + token] in lds. xf: px
+// nrows (<= 16 RT) rows from row_of(r), r < nrows; returns res[kResPitch * row + token] in lds. xf: px
 // pieces in operand order (prep_frag_kernel).
 template <int PX, int MT, int RT, class RowOf>
 __device__ __forceinline__ const float* frag_pass(unsigned char* lds, int nrows, RowOf row_of,
@@ -596,7 +598,7 @@ __device__ __forceinline__ const float* frag_pass(unsigned char* lds, int nrows,
       for (int w = 1; w < kFrWaves; ++w) v += red[w * RT * kWave + i];
       // C layout: lane l holds weight row l & 15 of the tile and tokens 4 (l >> 4) + e
       const int t = i >> 6, l = i & (kWave - 1);
-      *reinterpret_cast<floatx4_t*>(&res[(16 * t + (l & 15)) * (16 * MT) + 16 * mt + 4 * (l >> 4)]) = v;
+      *reinterpret_cast<floatx4_t*>(&res[(16 * t + (l & 15)) * S::kResPitch + 16 * mt + 4 * (l >> 4)]) = v;
     }
   }
   __syncthreads();
@@ -610,6 +612,7 @@ __global__ __launch_bounds__(kFrThreads, 2) void gu_frag_kernel(
     const uint16_t* __restrict__ wu, int d, int F, int hs, int np, int sp,
     uint16_t* __restrict__ hhi, uint16_t* __restrict__ hlo) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_u[];
+  constexpr int kPitch = FrLds<MT, RT>::kResPitch;
   const int n0 = blockIdx.x * np;
   const float* res = frag_pass<1, MT, RT>(
       lds_u, 2 * np,
@@ -621,7 +624,7 @@ __global__ __launch_bounds__(kFrThreads, 2) void gu_frag_kernel(
     const int m = i / sp, j = i - m * sp;
     const bool real = j < np && n0 + j < F && m < B;
     store_h(hhi, hlo, (size_t)m * hs + (size_t)blockIdx.x * sp + j,
-            real ? silu(res[j * (16 * MT) + m]) * res[(np + j) * (16 * MT) + m] : 0.f);
+            real ? silu(res[j * kPitch + m]) * res[(np + j) * kPitch + m] : 0.f);
   }
   if (blockIdx.x == gridDim.x - 1) zero_h_tail(hhi, hlo, hs, gridDim.x * sp, 16 * MT);
 }
@@ -638,7 +641,7 @@ __global__ __launch_bounds__(kFrThreads, 2) void cats_frag_kernel(
     const unsigned long long* __restrict__ cut, uint16_t* __restrict__ hhi,
     uint16_t* __restrict__ hlo, int hs, int sp, int32_t* __restrict__ uidx,
     int32_t* __restrict__ ucnt, int32_t* __restrict__ bidx, int32_t* __restrict__ bcnt) {
-  constexpr int kMpad = 16 * MT;
+  constexpr int kMpad = 16 * MT, kPitch = FrLds<MT, RT>::kResPitch;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_u[];
   __shared__ float s_a[kMpad][kSegPad];         // a = SiLU(g) per token and position
   __shared__ unsigned long long s_keep[kMpad];  // kept positions per token
@@ -657,7 +660,7 @@ __global__ __launch_bounds__(kFrThreads, 2) void cats_frag_kernel(
         xf, d);
     for (int i = tid; i < kMpad * sp; i += kFrThreads) {
       const int m = i / sp, k = i - m * sp;
-      const float h = (m < B && k < nr) ? silu(res[k * kMpad + m]) * res[(np + k) * kMpad + m] : 0.f;
+      const float h = (m < B && k < nr) ? silu(res[k * kPitch + m]) * res[(np + k) * kPitch + m] : 0.f;
       store_h(hhi, hlo, (size_t)m * hs + (size_t)seg * sp + k, h);
     }
     // the kept list of every neuron, as the threshold path writes it for t < 0
@@ -673,7 +676,7 @@ __global__ __launch_bounds__(kFrThreads, 2) void cats_frag_kernel(
         lds_u, np, [&](int r) { return wg + (size_t)(r0 + min(r, nr - 1)) * d; }, xf, d);
     for (int i = tid; i < kMpad * np; i += kFrThreads) {
       const int j = i % np, m = i / np;
-      const float a = silu(res[j * kMpad + m]);
+      const float a = silu(res[j * kPitch + m]);
       if (MODE == kModeAct) {
         if (m < B && j < nr) act[(size_t)m * F + r0 + j] = a;
       } else {
@@ -728,7 +731,7 @@ __global__ __launch_bounds__(kFrThreads, 2) void cats_frag_kernel(
     float h = 0.f;
     if (m < B && k < nu) {
       const int j = s_u[k];
-      if ((s_keep[m] >> j) & 1ull) h = s_a[m][j] * res[k * kMpad + m];
+      if ((s_keep[m] >> j) & 1ull) h = s_a[m][j] * res[k * kPitch + m];
     }
     store_h(hhi, hlo, (size_t)m * hs + (size_t)seg * sp + k, h);  // 0 past nu
   }
@@ -899,6 +902,21 @@ __global__ __launch_bounds__(kBT) void down_ring_kernel(
 
 int batch_mt(int B) { return (B + 15) / 16; }
 
+constexpr int kSegSmall = 32;  // segments of at most this many neurons take fewer row tiles
+// the dense unit kernel takes one 16-token tile and d_model = 2048, 4096, 6144 or 8192
+bool gu_unit_ok(int B, int d) { return B <= 16 && d % kUnitK == 0 && d <= 4 * kUnitK; }
+
+// Neurons per segment at most. gu_frag_kernel<1 or 2, RT> fits twice on a CU with short segments, so
+// that one workgroup's loads run through the other's prologue and epilogue, which a short row does not
+// outweigh: at 24 tokens 1024 x 38000 59.7 us against 67.6 with full segments, 1536 x 14336 41.9 against
+// 43.2, 2048 x 28672 76.4 against 84.3 (x 14336 46.5 against 46.1). Not where full segments hold 48
+// neurons or fewer and short ones would waste positions (1024 x 9000 24.2 against 23.6), nor at 40
+// tokens, one workgroup per CU either way (1024 x 14336 40.6 against 38.1).
+int dense_seg_cap(int px, int B, int d, int F) {
+  const bool narrow = (d <= 1536 && F > kSegTarget * 48) || (d <= 2304 && F > kSegTarget * kSegN);
+  return px == 1 && B <= 32 && narrow && !gu_unit_ok(B, d) ? kSegSmall : kSegN;
+}
+
 }  // namespace
 
 hipError_t launch_prep_pieces3(const float* x, int B, int d, int mpad, uint16_t* xp, hipStream_t stream) {
@@ -918,7 +936,7 @@ BatchLayout batch_layout(int B, int d, int F, int px) {
   const int ncols = d / kDnCols;
   // one layout for every mode: segments of np consecutive neurons, each owning sp positions
   // (whole MFMA tiles) of h, the kept list and the down blocks
-  const Seg s = seg_of(F);
+  const Seg s = seg_of(F, dense_seg_cap(px, B, d, F));
   L.nseg = s.nseg;
   L.np = s.np;
   L.sp = seg_positions(L.np);
@@ -958,8 +976,6 @@ hipError_t launch_gu_unit_n(const BatchLayout& L, hipStream_t stream, const uint
           F, L.hs, L.np, L.sp, hhi, hlo);
   return hipGetLastError();
 }
-// the unit kernel takes one 16-token tile and d_model = 2048, 4096, 6144 or 8192
-bool gu_unit_ok(int B, int d) { return B <= 16 && d % kUnitK == 0 && d <= 4 * kUnitK; }
 hipError_t launch_gu_unit(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
                           const uint16_t* wg, const uint16_t* wu, int d, int F, uint16_t* hhi,
                           uint16_t* hlo) {
@@ -971,8 +987,6 @@ hipError_t launch_gu_unit(const BatchLayout& L, hipStream_t stream, const uint16
     default: return hipErrorInvalidValue;
   }
 }
-constexpr int kSegSmall = 32;  // segments of at most this many neurons take fewer row tiles
-
 template <int MT, int RT>
 hipError_t launch_gu_frag_n(const BatchLayout& L, hipStream_t stream, const uint16_t* xp, int B,
                             const uint16_t* wg, const uint16_t* wu, int d, int F, uint16_t* hhi,

@@ -27,7 +27,8 @@ def sr():
 
 @pytest.mark.parametrize("d,f,bsz", [(256, 1, 2), (256, 1025, 5), (512, 4099, 3), (512, 14336, 16), (256, 14337, 17),
                                      (768, 8193, 33), (768, 9001, 7), (256, 12289, 48), (512, 24571, 49),
-                                     (256, 12288, 64), (2048, 4097, 15), (1280, 3584, 64)])
+                                     (256, 12288, 64), (2048, 4097, 15), (1280, 3584, 64),
+                                     (1536, 12289, 9), (2048, 14337, 20)])
 def test_every_mode(sr, d, f, bsz):
     say(f"operand-order batch d={d} f={f} B={bsz}")
     wg, wu, wd = ffn_weights(3000 + d + f + bsz, d, f, 1.0 / np.sqrt(d))
