@@ -456,8 +456,8 @@ int sirius_fill_normal_bf16(uint16_t* out, size_t n, uint64_t seed, float mean, 
  * at other shapes); "embed", "norm_qkv", "linear" (one token),
  * "linear_prep", "linear_mfma" (chunks), "draft_tail",
  * "period_tail" (the small decoder);
- * "calib_prep", "calib_gate", "select_hist", "select_pick"; "topk_gate",
- * "topk_cut"; "verify_stats", "verify_scan", "tree_stats", "tree_scan",
+ * "calib_prep", "calib_gate", "select_clear", "select_hist", "select_pick";
+ * "topk_gate", "topk_cut"; "verify_stats", "verify_scan", "tree_stats", "tree_scan",
  * "tree_topw", "tree_select"; "griffin_z", "griffin_rownorm", "griffin_score",
  * "griffin_topk", "condense"; "rmsnorm", "fill_normal"; "attn_partial",
  * "attn_combine", "kv_rollback".

@@ -316,9 +316,7 @@ int sirius_cats_calibrate(const float* x_cal, int N, const uint16_t* w_gate, int
   const CalibLayout L = calib_layout(N, d_model, d_ff);
   char* base = static_cast<char*>(ws);
   float* absact = reinterpret_cast<float*>(base + L.act);
-  int nzero = 0;
-  int* zero = sirius::select_zero_ints(base + L.sel, &nzero);
-  hipError_t e = sirius::launch_gate_absact(x_cal, N, w_gate, d_model, d_ff, absact, base + L.xp, zero, nzero, s);
+  hipError_t e = sirius::launch_gate_absact(x_cal, N, w_gate, d_model, d_ff, absact, base + L.xp, base + L.sel, s);
   if (e != hipSuccess) return hip_status(e, fn);
   return hip_status(sirius::launch_select_kth_largest(absact, (int)M, k, t_out, base + L.sel, s), fn);
 }

@@ -7,6 +7,8 @@
 // 4096 x 14336 gate, bound by the MFMA rate (64 us at the rate of a large library product) and by
 // the LDS reads that feed it (16 rows of each operand per 16 x 16 x 32 product), not by HBM.
 //
+// Calls of a few inputs take the vector kernel of the top-k gate pass (ffn_gemv.hip) instead.
+//
 //  calib_gate_kernel   64 inputs x 128 neurons per workgroup, two workgroups per CU. K moves in
 //                      stages of 64 columns (whole 128-byte lines) by direct global-to-LDS loads
 //                      into two slots, the next stage in flight while one is multiplied; a wave
@@ -192,8 +194,21 @@ size_t gate_absact_ws(int N, int d) {
   return (size_t)kPieces * std::min(kChunk, ceil_div(N, kTok) * kTok) * d * 2;
 }
 
-hipError_t launch_gate_absact(const float* x, int N, const uint16_t* wg, int d, int F, float* absact,
-                              char* ws, int* zero_ints, int nzero, hipStream_t stream) {
+// At most four inputs that leave room for two workgroups' copies of them in LDS: the vector kernel
+// streams the gate at HBM rate, where the MFMA kernel fills its 64-input tiles with zeros on d_ff / 128
+// workgroups. The whole call for 1, 2 and 4 inputs of 4096 x 14336 34, 38 and 56 us against 77, 78 and
+// 80; 2 of 8192 x 28672 104 against 176, but 3, one workgroup per CU, 195 against 173.
+bool calib_few(int N, int d) { return N <= 4 && N * d <= 16384; }
+
+hipError_t launch_gate_absact(const float* x, int N, const uint16_t* wg, int d, int F, float* act,
+                              char* ws, char* sel_ws, hipStream_t stream) {
+  if (calib_few(N, d)) {
+    hipError_t e = launch_select_clear(sel_ws, stream);
+    if (e != hipSuccess) return e;
+    return launch_gate_act(x, N, wg, d, F, -1.f, act, stream, "calib_gate");
+  }
+  int nzero = 0;
+  int* zero_ints = select_zero_ints(sel_ws, &nzero);
   uint16_t* xp = reinterpret_cast<uint16_t*>(ws);
   for (int n0 = 0; n0 < N; n0 += kChunk) {
     const int nb = std::min(kChunk, N - n0);
@@ -206,7 +221,7 @@ hipError_t launch_gate_absact(const float* x, int N, const uint16_t* wg, int d, 
     ProfScope prof("calib_gate", stream);
     const int grid = kXcd * ceil_div(ceil_div(F, kNeu), kXcd) * ntok;
     klaunch(calib_gate_kernel, grid, kThreads, 0, stream, xp, nb, npad, wg, d, F, ntok,
-            absact + (size_t)n0 * F, zero_ints, nzero);
+            act + (size_t)n0 * F, zero_ints, nzero);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -690,7 +690,7 @@ hipError_t launch_reduce(const float* part, int gr, int B, int d, const float* r
 }
 
 hipError_t launch_gate_act(const float* x, int N, const uint16_t* wg, int d, int F,
-                           float norm_eps, float* act, hipStream_t stream) {
+                           float norm_eps, float* act, hipStream_t stream, const char* scope) {
   const int bc = std::max(1, std::min(8, kXLdsFloats / d));
   const int cpl = pow2_at_least(ceil_div(d / 8, kWave), 16);
   const int nseg = gate_segments(F);
@@ -699,7 +699,7 @@ hipError_t launch_gate_act(const float* x, int N, const uint16_t* wg, int d, int
   for (int b0 = 0; b0 < N; b0 += bc) {
     const int nb = std::min(bc, N - b0);
     const int bm = pow2_at_least(nb, 8);
-    ProfScope prof("topk_gate", stream);
+    ProfScope prof(scope, stream);
     hipError_t e = launch_gate_mode<kModeAct>(
         bm, cpl, dim3(nseg), (size_t)nb * d * sizeof(float), stream, x + (size_t)b0 * d, nb,
         reinterpret_cast<const uint4*>(wg), nullptr, d, F, 0.f, norm_eps, rmax, nullptr, nullptr,

@@ -51,13 +51,15 @@ hipError_t launch_ffn_gemv(const float* x, int B, const uint16_t* wg, const uint
 // Signed gate activations SiLU(W_gate xn) for N inputs into act [N, F] (top-k first pass);
 // xn = RMSNorm(x) when norm_eps >= 0.
 hipError_t launch_gate_act(const float* x, int N, const uint16_t* wg, int d, int F,
-                           float norm_eps, float* act, hipStream_t stream);
+                           float norm_eps, float* act, hipStream_t stream, const char* scope = "topk_gate");
 
-// Gate activations |SiLU(W_gate x)| for N inputs into absact [N, F] (calibration), on MFMA with
-// gate_absact_ws(N, d) bytes of workspace; zero_ints[0 .. nzero) are cleared on the way.
+// Gate activations for N inputs into act [N, F] (calibration), their sign kept or not: on MFMA with
+// gate_absact_ws(N, d) bytes of workspace, or by gate_kernel for the few inputs of calib_few. The
+// counters of the select's workspace sel_ws are cleared on the way.
+bool calib_few(int N, int d);
 size_t gate_absact_ws(int N, int d);
-hipError_t launch_gate_absact(const float* x, int N, const uint16_t* wg, int d, int F, float* absact,
-                              char* ws, int* zero_ints, int nzero, hipStream_t stream);
+hipError_t launch_gate_absact(const float* x, int N, const uint16_t* wg, int d, int F, float* act,
+                              char* ws, char* sel_ws, hipStream_t stream);
 // x [B][d] as three exact bf16 pieces xp [3][mpad][d], zero rows from B on; d % 4 == 0, d <= 8192.
 hipError_t launch_prep_pieces3(const float* x, int B, int d, int mpad, uint16_t* xp, hipStream_t stream);
 
@@ -157,8 +159,9 @@ hipError_t launch_batch_act(const float* x, int B, const uint16_t* wg, int d, in
                             float norm_eps, float* act, char* ws, const BatchLayout& L,
                             hipStream_t stream);
 
-// ---- radix select of the k-th largest of n non-negative floats (v 16-byte aligned). The counters
-// that select_zero_ints names must be zero when the call runs.
+// ---- radix select of the k-th largest magnitude of n floats (v 16-byte aligned). The counters
+// that select_zero_ints names (launch_select_clear clears them) must be zero when the call runs.
+hipError_t launch_select_clear(char* ws, hipStream_t stream);
 hipError_t launch_select_kth_largest(const float* v, int n, int k, float* out_value, char* ws,
                                      hipStream_t stream);
 size_t select_ws_bytes();

@@ -1,4 +1,4 @@
-// Radix select of the k-th largest of n non-negative fp32 values on gfx950.
+// Radix select of the k-th largest magnitude of n fp32 values on gfx950.
 //
 // Non-negative IEEE floats order like their bit patterns, so the k-th largest is found digit by
 // digit, most significant first (bits 30-20, 19-9, 8-0): a grid-wide histogram of the current
@@ -85,6 +85,10 @@ __device__ __forceinline__ SelectState state_of(int pass, int k, const SelectSta
   return s;
 }
 
+__global__ __launch_bounds__(kSelThreads) void select_clear_kernel(int* __restrict__ ghist) {
+  for (int i = threadIdx.x; i < kPasses * kBins; i += kSelThreads) ghist[i] = 0;
+}
+
 template <int PASS>
 __global__ __launch_bounds__(kSelThreads) void select_hist_kernel(const float* __restrict__ v, int n,
                                                                   int k, SelectState* st, int* ghist) {
@@ -99,7 +103,7 @@ __global__ __launch_bounds__(kSelThreads) void select_hist_kernel(const float* _
   const uint32_t fixed = PASS == 0 ? 0u : s.prefix >> shift_of(PASS > 0 ? PASS - 1 : 0);
   int* hc = h + (tid & (kCopies - 1)) * kNb;
   auto count = [&](float f) {
-    const uint32_t u = __float_as_uint(f);
+    const uint32_t u = __float_as_uint(f) & 0x7fffffffu;
     if (PASS == 0 || (u >> shift_of(PASS > 0 ? PASS - 1 : 0)) == fixed)
       atomicAdd(&hc[(u >> kShift) & (kNb - 1)], 1);
   };
@@ -142,6 +146,12 @@ size_t select_ws_bytes() { return 256 + kPasses * kBins * sizeof(int); }
 int* select_zero_ints(char* ws, int* count) {
   *count = kPasses * kBins;
   return reinterpret_cast<int*>(ws + 256);
+}
+
+hipError_t launch_select_clear(char* ws, hipStream_t stream) {
+  ProfScope prof("select_clear", stream);
+  klaunch(select_clear_kernel, 1, kSelThreads, 0, stream, reinterpret_cast<int*>(ws + 256));
+  return hipGetLastError();
 }
 
 hipError_t launch_select_kth_largest(const float* v, int n, int k, float* out_value, char* ws,

@@ -22,7 +22,7 @@ def sr():
 
 
 @pytest.mark.parametrize("d,f,n", [(8, 1, 1), (72, 127, 63), (264, 129, 65), (4104, 100, 64), (256, 700, 1100),
-                                   (8192, 260, 3)])
+                                   (8192, 260, 3), (8192, 260, 2), (4096, 131, 4), (4104, 131, 4), (5456, 77, 3), (16, 9, 5)])
 def test_edges(sr, d, f, n):
     say(f"calibrate d={d} f={f} N={n}")
     wg, _, _ = ffn_weights(800 + d, d, f, 1.0 / np.sqrt(d))
@@ -58,7 +58,7 @@ def test_ties_zeros_and_infinities(sr):
     assert t == tb
 
 
-@pytest.mark.parametrize("n", [5, 70])
+@pytest.mark.parametrize("n", [3, 5, 70])
 def test_infinite_weights(sr, n):
     """A gate weight that is an infinity gives an infinite activation where the gate is positive (its
     SiLU is NaN where it is negative, and NaN ranks above the infinities): every rank below them is the
@@ -78,3 +78,25 @@ def test_infinite_weights(sr, n):
         assert abs(at(rank) - finite[rank - 1]) <= 1e-5 * finite[rank - 1] + 2e-6
     assert np.isposinf(at(finite.size + 1)) and np.isposinf(at(finite.size + up))
     assert np.isnan(at(finite.size + up + 1)) and np.isnan(at(total))
+
+
+@pytest.mark.parametrize("d,n,few", [(4096, 4, True), (8192, 2, True), (256, 1, True), (4104, 4, False), (8192, 3, False),
+                                     (256, 5, False)])
+def test_few_inputs_are_not_padded_to_tiles(sr, d, n, few):
+    """At most four inputs of 64 KiB in all take the vector kernel: no launch that splits them for MFMA."""
+    import torch
+    f = 300
+    say(f"calibration route d={d} N={n}")
+    wg, _, _ = ffn_weights(970, d, f, 1.0 / np.sqrt(d))
+    x, w = dev_f32(calibration_inputs(970, n, d)), dev_bf16(wg)
+    sr.sirius_cats_calibrate(x, w, 0.5)
+    sr.sirius_profile_reset()
+    sr.sirius_profile_enable(True)
+    try:
+        sr.sirius_cats_calibrate(x, w, 0.5)
+        torch.cuda.synchronize()
+        prep = sr.sirius_profile_query("calib_prep")[1]
+    finally:
+        sr.sirius_profile_enable(False)
+        sr.sirius_profile_reset()
+    assert prep == (0 if few else 1)
