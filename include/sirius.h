@@ -454,7 +454,7 @@ int sirius_fill_normal_bf16(uint16_t* out, size_t n, uint64_t seed, float mean, 
  * "topk_up", "topk_down" (small batches at other shapes); "ffn_mfma_prep",
  * "ffn_mfma_gate_up", "ffn_mfma_down", "ffn_mfma_reduce" (8 or more tokens
  * at other shapes); "embed", "norm_qkv", "linear" (one token),
- * "linear_prep", "linear_mfma" (chunks), "draft_tail",
+ * "linear_pair", "linear_prep", "linear_mfma" (chunks), "draft_tail",
  * "period_tail" (the small decoder);
  * "calib_prep", "calib_gate", "select_clear", "select_hist", "select_pick";
  * "topk_gate", "topk_cut"; "verify_stats", "verify_scan", "tree_stats", "tree_scan",

@@ -258,6 +258,11 @@ hipError_t launch_norm_qkv(const StepSource& src, int K, float eps, const uint16
 // y[j] = x . W[j] (+ resid[j]) for j < N; W [N][K] bf16; K % 8 == 0, K <= 8192.
 hipError_t launch_linear(const float* x, const uint16_t* W, int K, int N, const float* resid, float* y,
                          hipStream_t s);
+// The same for two tokens (eps < 0: no norm), where linear_pair_ok(K, Nq + 2 Nkv).
+bool linear_pair_ok(int K, int N);
+hipError_t launch_linear_pair(const float* x, int K, float eps, const uint16_t* Wq, int Nq, const uint16_t* Wk,
+                              const uint16_t* Wv, int Nkv, const float* resid, float* yq, uint16_t* yk,
+                              uint16_t* yv, hipStream_t s);
 // The same products (norm_eps >= 0: of the normalised rows) for a chunk of 2..64 tokens on MFMA,
 // every weight read once per call; linear_mfma_ws(n, K) bytes of workspace, K % 8 == 0, K <= 8192.
 size_t linear_mfma_ws(int n, int K);

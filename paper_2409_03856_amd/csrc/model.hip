@@ -8,8 +8,8 @@
 //                      order, as rmsnorm_vec_kernel, so bit for bit its result), then the
 //                      products of up to three matrices in one launch: q = xn Wq^T (fp32),
 //                      k = xn Wk^T and v = xn Wv^T (bf16) -- a layer's attention inputs, or the
-//                      final norm and the LM head (q only). Chunks of more tokens run in
-//                      linear.hip
+//                      final norm and the LM head (q only)
+//  linear_pair_kernel  both for two tokens at small layers. Other chunks run in linear.hip
 //  draft_tail_kernel   the sparse model's greedy draft: argmax of one logit row (lowest index
 //                      on ties) into the chunk buffer, and the cache position advanced by one
 //                      (wound back by n - 1 after the last draft, so the full model's pass
@@ -278,6 +278,85 @@ __global__ __launch_bounds__(kLinThreads) void norm_qkv_kernel(
   }
 }
 
+// Two tokens' products in one launch: norm_qkv_kernel's (eps >= 0) or linear_kernel's sums for both
+// rows of x, each weight read once.
+constexpr int kPairMaxK = 2048;
+__global__ __launch_bounds__(kLinThreads) void linear_pair_kernel(
+    const float* __restrict__ x, int K, float eps, const uint4* __restrict__ Wq, int Nq,
+    const uint4* __restrict__ Wk, const uint4* __restrict__ Wv, int Nkv, const float* resid, float* yq,
+    uint16_t* __restrict__ yk, uint16_t* __restrict__ yv) {
+  constexpr int kPer = kPairMaxK / 4 / kLinThreads;
+  __shared__ float4 s_x4[2][kPairMaxK / 4];
+  __shared__ float s_w[2][kLinWaves];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+  const int k4 = K >> 2, k8 = K >> 3;
+  const float4* x4 = reinterpret_cast<const float4*>(x);
+  float4 v[2][kPer];
+  float ss[2] = {0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = tid + kLinThreads * u;
+      v[i][u] = e < k4 ? x4[i * k4 + e] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  float inv[2] = {1.f, 1.f};
+  if (eps >= 0.f) {  // uniform
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        ss[i] = fmaf(v[i][u].x, v[i][u].x, ss[i]);
+        ss[i] = fmaf(v[i][u].y, v[i][u].y, ss[i]);
+        ss[i] = fmaf(v[i][u].z, v[i][u].z, ss[i]);
+        ss[i] = fmaf(v[i][u].w, v[i][u].w, ss[i]);
+      }
+      ss[i] = wave_sum(ss[i]);
+      if (lane == 0) s_w[i][wave] = ss[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float tot = ((s_w[i][0] + s_w[i][1]) + s_w[i][2]) + s_w[i][3];
+      inv[i] = 1.0f / sqrtf(tot / (float)K + eps);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = tid + kLinThreads * u;
+      if (e < k4)
+        s_x4[i][e] = make_float4(v[i][u].x * inv[i], v[i][u].y * inv[i], v[i][u].z * inv[i], v[i][u].w * inv[i]);
+    }
+  __syncthreads();
+  const float* xs0 = reinterpret_cast<const float*>(s_x4[0]);
+  const float* xs1 = reinterpret_cast<const float*>(s_x4[1]);
+  const int N = Nq + 2 * Nkv;
+  for (int j = blockIdx.x * kLinWaves + wave; j < N; j += gridDim.x * kLinWaves) {
+    const int part = j < Nq ? 0 : (j < Nq + Nkv ? 1 : 2);  // uniform over the wave
+    const int jr = part == 0 ? j : (part == 1 ? j - Nq : j - Nq - Nkv);
+    const uint4* wr = (part == 0 ? Wq : (part == 1 ? Wk : Wv)) + (size_t)jr * k8;
+    float a0 = 0.f, a1 = 0.f;
+    for (int c = lane; c < k8; c += kWave) {
+      const uint4 w = wr[c];
+      a0 = dot8(w, xs0 + 8 * c, a0);
+      a1 = dot8(w, xs1 + 8 * c, a1);
+    }
+    a0 = wave_sum(a0);
+    a1 = wave_sum(a1);
+    if (lane < 2) {
+      const float s = lane == 0 ? a0 : a1;
+      if (part == 0) {
+        const size_t o = (size_t)lane * Nq + jr;
+        yq[o] = resid != nullptr ? resid[o] + s : s;
+      } else {
+        (part == 1 ? yk : yv)[(size_t)lane * Nkv + jr] = (uint16_t)f32_to_bf16(s);
+      }
+    }
+  }
+}
+
 __global__ __launch_bounds__(kTailThreads) void draft_tail_kernel(
     const float* __restrict__ logits, int V, int32_t* __restrict__ seq, int slot,
     int32_t* __restrict__ cache_pos, int pos_delta, int32_t* __restrict__ trace_drafted) {
@@ -365,6 +444,22 @@ hipError_t launch_linear(const float* x, const uint16_t* W, int K, int N, const 
   ProfScope prof("linear", s);
   klaunch(linear_kernel, std::min(ceil_div(N, kLinWaves), 2048), kLinThreads, 0, s, x,
           reinterpret_cast<const uint4*>(W), K, N, resid, y);
+  return hipGetLastError();
+}
+
+// Up to two million weights the launch that prepares the MFMA operands costs more than the vector sums:
+// a two-token pass of two 1024 x 2816 layers takes 74.6 us so and 92.2 by MFMA, of the 256 x 688 decoder
+// 58.8 and 70.4; of 2048-wide layers, whose products are larger, the MFMA kernels take less.
+bool linear_pair_ok(int K, int N) { return K <= kPairMaxK && (size_t)K * N <= (size_t)2 << 20; }
+
+hipError_t launch_linear_pair(const float* x, int K, float eps, const uint16_t* Wq, int Nq, const uint16_t* Wk,
+                              const uint16_t* Wv, int Nkv, const float* resid, float* yq, uint16_t* yk,
+                              uint16_t* yv, hipStream_t s) {
+  if ((K & 7) != 0 || !linear_pair_ok(K, Nq + 2 * Nkv) || Nq < 1 || Nkv < 0) return hipErrorInvalidValue;
+  ProfScope prof("linear_pair", s);
+  klaunch(linear_pair_kernel, ceil_div(Nq + 2 * Nkv, kLinWaves), kLinThreads, 0, s, x, K, eps,
+          reinterpret_cast<const uint4*>(Wq), Nq, reinterpret_cast<const uint4*>(Wk),
+          reinterpret_cast<const uint4*>(Wv), Nkv, resid, yq, yk, yv);
   return hipGetLastError();
 }
 

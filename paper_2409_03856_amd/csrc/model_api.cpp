@@ -227,6 +227,8 @@ hipError_t forward(const sirius_model* m, const int32_t* tokens, int n, int32_t*
   auto project = [&](const float* x, int K, float eps, const uint16_t* wq, int nq, const uint16_t* wk,
                      const uint16_t* wv, int nkv, const float* resid, float* yq, uint16_t* yk,
                      uint16_t* yv) {
+    if (n == 2 && sirius::linear_pair_ok(K, nq + 2 * nkv))
+      return sirius::launch_linear_pair(x, K, eps, wq, nq, wk, wv, nkv, resid, yq, yk, yv, s);
     return sirius::launch_linear_mfma(x, n, K, eps, wq, nq, wk, wv, nkv, resid, yq, yk, yv, ws + L.xf, s);
   };
   if ((e = sirius::launch_embed(tokens, n, m->embed, d, m->vocab, h, s)) != hipSuccess) return e;

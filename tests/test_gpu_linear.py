@@ -22,6 +22,10 @@ CASES = [
     (520, 2, 1, 128, 12289, 33),   # the 64-row form with one row in its last tile, three token tiles
     (776, 4, 4, 32, 12352, 64),    # four token tiles, whole 64-row tiles
     (2056, 2, 2, 8, 12300, 9),     # K tail in the fifth 512-column block
+    (1032, 3, 1, 24, 2031, 2),     # two tokens: every product of at most two million weights
+    (1032, 3, 1, 24, 2033, 2),     # the LM head above them
+    (2048, 5, 5, 56, 77, 2),       # the widest rows of the pair kernel
+    (8, 1, 1, 8, 3, 2),            # the narrowest
 ]
 
 
@@ -97,3 +101,26 @@ def test_infinite_weights(d, v, n):
         a, b = host(a[0, :n].float())[:, 0], host(b[0, :n].float())[:, 0]
         assert np.all(np.isinf(a[:, 5])) and np.array_equal(a[:, 5], b[:, 5])
         assert np.all(np.isfinite(np.delete(a, 5, 1)))
+
+
+def test_two_tokens_of_a_small_layer_take_one_launch_per_product():
+    """Products of up to two million weights for two tokens are one launch each; the others keep the
+    operand preparation in front."""
+    import torch
+    import paper_2409_03856_amd as sr
+    say("launches of a two-token pass")
+    s = ModelShape("pair", 2, 256, 300, 4, 2, 64, 9000, 64, 6.0)
+    m = sr.Model({k: dev_bf16(b) for k, b in model_weights(5, s).items()}, 4, 2, 64, 64, [0.1] * 2)
+    pos = torch.zeros(1, dtype=torch.int32, device="cuda")
+    toks = dev_i32(prompt_tokens(5, 2, 9000))
+    sr.sirius_model_forward(m, toks, pos, False)
+    sr.sirius_profile_reset()
+    sr.sirius_profile_enable(True)
+    try:
+        sr.sirius_model_forward(m, toks, pos, False)
+        torch.cuda.synchronize()
+        count = {k: sr.sirius_profile_query(k)[1] for k in ("linear_prep", "linear_mfma", "embed")}
+    finally:
+        sr.sirius_profile_enable(False)
+        sr.sirius_profile_reset()
+    assert count == {"linear_prep": 1, "linear_mfma": 1, "embed": 1}
