@@ -17,10 +17,44 @@ CASES = [
     (3, 512, 300, 8, 2, 64, 2600),     # the widest row that takes partials, eight pairs per thread
     (2, 512, 2600, 4, 4, 32, 700),     # more partials than the rule takes
     (2, 520, 400, 2, 1, 40, 333),      # wider than the rule takes
-    (2, 136, 90, 3, 1, 24, 9000),      # a vocabulary past the draft rule at these rows or inside it
-    (1, 72, 17, 1, 1, 8, 60001),       # one partial row group, a vocabulary past the rule
+    (2, 136, 90, 3, 1, 24, 9000),      # few rows per launch: a larger vocabulary inside the draft rule
+    (1, 72, 17, 1, 1, 8, 60001),       # one partial row group, 24 rows: the largest vocabulary inside it
     (2, 264, 1500, 2, 2, 128, 5),      # a vocabulary of five
+    (2, 256, 688, 8, 4, 64, 8192),     # the draft rule's last vocabulary at 1024 rows, partials taken
+    (2, 256, 688, 8, 4, 64, 8193),     # and the first past it: every draft a launch of its own
+    (1, 520, 400, 8, 4, 64, 12000),    # past it, rows too wide for partials
 ]
+
+
+def drafts_folded(case):
+    """Each workgroup of the first projection (4 rows each, 2048 at most) reads all the logits: 8 MiB in all."""
+    _, _, _, h, hkv, hd, v = case
+    return 4 * v * min(-(-(h + 2 * hkv) * hd // 4), 2048) <= 8 << 20
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_drafts_on_both_sides_of_the_logits_rule(case):
+    """Past the rule a period's n drafts are n launches; inside it the last one alone."""
+    import torch
+    import paper_2409_03856_amd as sr
+    layers, d, f, h, hkv, hd, v = case
+    assert drafts_folded(case) == (case not in CASES[-2:])
+    s = ModelShape("fusion", layers, d, f, h, hkv, hd, v, 64, 6.0)
+    m = sr.Model({k: dev_bf16(b) for k, b in model_weights(3, s).items()}, h, hkv, hd, 64, [0.2] * layers)
+    n = 4
+    call = lambda: sr.sirius_generate(m, torch.zeros(n + 1, dtype=torch.int32, device="cuda"),
+                                      torch.zeros(1, dtype=torch.int32, device="cuda"), n, 0.1, 1)
+    call()
+    sr.sirius_profile_reset()
+    sr.sirius_profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        launches = sr.sirius_profile_query("draft_tail")[1]
+    finally:
+        sr.sirius_profile_enable(False)
+        sr.sirius_profile_reset()
+    assert launches == (1 if drafts_folded(case) else n)
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
