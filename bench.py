@@ -428,7 +428,7 @@ def main():
                  "batch_reduce",
                  "verify_stats", "verify_scan", "tree_topw", "tree_select", "tree_stats", "tree_scan", "topk_gate", "topk_cut", "topk_decode",
                  "topk_reduce", "attn_partial", "attn_combine", "kv_rollback", "griffin_z", "griffin_topk", "griffin_score", "condense",
-                 "select_hist", "select_pick", "select_init", "rmsnorm"]:
+                 "select_hist", "select_pick", "rmsnorm"]:
         tot, n = sr.sirius_profile_query(name)
         if n:
             kern[name] = {"avg_us": round(tot * 1e3 / n, 3), "launches": n}

@@ -61,21 +61,14 @@ constexpr int kLdsRing = 150 * 1024;     // LDS the rings may take
 constexpr int kDnCols = 256;             // output columns per down workgroup
 constexpr int kDnBlock = 64;             // rows per down block
 
-// vmcnt wait until at most `later` blocks of L loads each are still in flight (later <= 10)
+// vmcnt wait until at most `later` (0, 1 or 2) blocks of L loads each are still in flight
 template <int L>
 __device__ __forceinline__ void wait_later(int later) {
+  static_assert(2 * L <= 63, "vmcnt counts up to 63 loads");
   switch (later) {
     case 0: wait_vm<0>(); break;
     case 1: wait_vm<L>(); break;
-    case 2: wait_vm<(2 * L > 63 ? 63 : 2 * L)>(); break;
-    case 3: wait_vm<(3 * L > 63 ? 63 : 3 * L)>(); break;
-    case 4: wait_vm<(4 * L > 63 ? 63 : 4 * L)>(); break;
-    case 5: wait_vm<(5 * L > 63 ? 63 : 5 * L)>(); break;
-    case 6: wait_vm<(6 * L > 63 ? 63 : 6 * L)>(); break;
-    case 7: wait_vm<(7 * L > 63 ? 63 : 7 * L)>(); break;
-    case 8: wait_vm<(8 * L > 63 ? 63 : 8 * L)>(); break;
-    case 9: wait_vm<(9 * L > 63 ? 63 : 9 * L)>(); break;
-    default: wait_vm<(10 * L > 63 ? 63 : 10 * L)>(); break;
+    default: wait_vm<2 * L>(); break;
   }
 }
 
@@ -760,7 +753,7 @@ struct DnShape {
   static constexpr int kSlotsMax = kLdsRing / kSlotBytes;
   static constexpr int kSlots = kSlotsMax > 4 ? 4 : kSlotsMax;
   static_assert(kPieces % kWave == 0 && kWPieces % kWave == 0, "whole wave instructions");
-  static_assert(kSlots >= 3, "at least two blocks in flight");
+  static_assert(kSlots >= 3 && kSlots <= 4, "two or three blocks in flight, wait_later's counts");
 };
 
 __device__ __forceinline__ int dr_pos(int row, int chunk) { return chunk ^ (((row >> 3) & 3) << 1); }

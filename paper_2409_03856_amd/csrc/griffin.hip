@@ -6,7 +6,7 @@
 //                         accumulation). Workgroup tiles of 64 to 256 tokens x 64 or 112
 //                         neurons (eight waves, two per SIMD, one workgroup per CU), chosen
 //                         by the rounds of 256 tiles that a prompt makes of them,
-//                         K through a five-slot LDS ring of 32-wide stages filled by direct
+//                         K through an LDS ring (five slots) of 32-wide stages filled by direct
 //                         global-to-LDS loads, the next stage's operands read while the
 //                         current one is multiplied; the token tiles of a neuron tile run on
 //                         one XCD together so its weights are read from HBM once. For the
@@ -101,16 +101,16 @@ __device__ __forceinline__ float z_silu(float g) {
 // four consecutive rows of one token column, so it holds the gate and up products of two
 // neurons side by side: every lane forms z from its own registers. Wave (wm, wn) multiplies
 // weight blocks WB wn .. by token rows 16 MB wm ..: WB x MB v_mfma_f32_16x16x32_bf16 per K
-// stage into 112 fp32 accumulators per lane at the largest tile. The two waves of a SIMD take turns on its MFMA
-// unit.
+// stage into 4 MB WB fp32 accumulators per lane (112 at the 256 x 112 tile). The two waves of a SIMD
+// take turns on its MFMA unit.
 //
-// K goes through a five-slot LDS ring of 32-wide stages (30 KiB each) filled by direct
-// global-to-LDS 16-byte loads (three or four per thread per stage, no staging registers): while
-// stage b is multiplied, stages b + 2 .. b + 5 are in flight and the operands of stage b + 1 are
+// K goes through an LDS ring of kSlots (five) 32-wide stages of kSlotBytes (12 to 30 KiB by the tile)
+// filled by direct global-to-LDS 16-byte loads (kLoads or one fewer per thread and stage, no staging
+// registers): while stage b is multiplied, the stages after b + 1 are in flight and the operands of stage b + 1 are
 // read from LDS into a second register set, so the LDS reads of the next stage overlap this
 // stage's MFMAs. One barrier per stage: after it, every wave has finished reading stage b (its
 // register copy is complete) and every load of stage b + 1 has landed, so stage b's slot is
-// refilled with stage b + 5.
+// refilled with stage b + kSlots.
 //
 // Rows past T or d_ff load a valid row (T - 1, d_ff - 1) whose products are never used; in a K
 // tail (d_model % 32 != 0) the chunks past d_model are loaded from a block of zeros.
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
   // this thread's loads of a stage: slot piece g = q * 512 + tid, row g / 4, position g % 4,
   // holding chunk z_pos(row, position) of that row; a wave instruction covers 16 whole rows, so
   // the row kind (token or weight) is uniform over it
-  const bool full_wave = wave < kZFullWaves;  // issues a fourth load per stage
+  const bool full_wave = wave < kZFullWaves;  // issues the last of a stage's kZLoads loads
   const uint16_t* src[kZLoads];
   int chunk_k[kZLoads];  // K offset of the chunk within a stage (elements)
   int lds_off[kZLoads];

@@ -143,7 +143,7 @@ hipError_t launch_ffn_any(const float* x, int B, const uint16_t* wg, const uint1
                           const uint16_t* wd, int d, int F, int mode, float t, float norm_eps,
                           const float* resid, float* y, int32_t* active_idx, int32_t* active_cnt,
                           char* ws, hipStream_t s);
-// sparse: the segment layout (per-segment union blocks), used by every call with px = 3
+// px: bf16 pieces of the input (1: rounded; 3: exact)
 BatchLayout batch_layout(int B, int d, int F, int px);
 // mode: kFfnMode*; with active_idx (sparse modes) the per-token kept lists are written; top-k
 // takes the activations act [B][F] and the per-token cut keys (launch_cut).
@@ -154,7 +154,7 @@ hipError_t launch_ffn_batch(const float* x, int B, const uint16_t* wg, const uin
                             hipStream_t stream, const float* act = nullptr,
                             const unsigned long long* cut = nullptr);
 // Top-k gate pass of a batch: act [B][F] = SiLU(W_gate xn) from the exact (three-piece) input;
-// L = batch_layout(B, d, F, 3, true).
+// L = batch_layout(B, d, F, 3).
 hipError_t launch_batch_act(const float* x, int B, const uint16_t* wg, int d, int F,
                             float norm_eps, float* act, char* ws, const BatchLayout& L,
                             hipStream_t stream);

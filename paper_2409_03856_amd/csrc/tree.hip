@@ -50,8 +50,8 @@ __device__ __forceinline__ float from_ordered(uint32_t o) {
   return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
 }
 // larger key = larger logit, then lower token
-__device__ __forceinline__ uint64_t make_key(float v, int i) {
-  return ((uint64_t)ordered_bits(v) << 32) | (uint64_t)(~(uint32_t)i);
+__device__ __forceinline__ uint64_t ordered_key(uint32_t o, int i) {
+  return ((uint64_t)o << 32) | (uint64_t)(~(uint32_t)i);
 }
 __device__ __forceinline__ int key_token(uint64_t k) { return (int)(~(uint32_t)k); }
 __device__ __forceinline__ float key_value(uint64_t k) { return from_ordered((uint32_t)(k >> 32)); }
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kTopThreads) void tree_topw_kernel(
   if constexpr (kBound) {
     uint64_t key[E];
 #pragma unroll
-    for (int j = 0; j < E; ++j) key[j] = e0 + j < V ? make_key(v[j], e0 + j) : 0;
+    for (int j = 0; j < E; ++j) key[j] = e0 + j < V ? ordered_key(ordered_bits(v[j]), e0 + j) : 0;
     bound_best<E>(key, W, s_c);
     if (tid < KW) rk[at * KW + tid] = s_c[tid];
   } else {
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kTopThreads) void tree_topw_kernel(
       int jj = 0;
 #pragma unroll
       for (int j = E - 1; j >= 0; --j) jj = o[j] == best ? j : jj;
-      if (win) s_c[wave * KW + r] = ((uint64_t)best << 32) | (uint64_t)(~(uint32_t)(e0 + jj));
+      if (win) s_c[wave * KW + r] = ordered_key(best, e0 + jj);
       uint32_t next = 0;
 #pragma unroll
       for (int j = 0; j < E; ++j) {
