@@ -30,13 +30,12 @@
 //  kv_rollback_kernel   cache_pos[b] += min(accept_len[b] + 1, n).
 //
 // Bound: HBM for one token (2 L Hkv hd 2 bytes) and launch latency at short contexts; at 16 tokens
-// of 4 heads per key/value head the matrix work (12 n G L hd flops with the pieces) and the
-// exponentials weigh as much as the bytes. Llama-3-8B
-// heads, one token over 2048 rows: 7.9 us and 4.8 for the merge (12.0 + 4.7 with fp32 vector
-// products and chunks by capacity); 16 sequences of one token over 1500-3000 rows 35 + 4 us
-// (85 + 6); 8 sequences of 16 tokens over 3500-7000 rows 72 + 8 us (345 + 53). The high pieces'
-// sums of a score are kept apart from the rest: 2.1e-7 off 64 bits (2.3e-7 before; 3.0e-7 in one
-// chain).
+// of 4 heads per key/value head the matrix work (12 n G L hd flops with the pieces; the matrix units
+// are busy for 31 % of the time) and the exponentials weigh as much as the bytes. Llama-3-8B heads,
+// one token over 2048 rows: 7.8 us and 3.9 for the merge (12.0 + 4.7 with fp32 vector products and
+// chunks by capacity); 16 sequences of one token over 1500-3000 rows 31 + 4 us (85 + 6); 8 sequences
+// of 16 tokens over 3500-7000 rows 65 + 7 us (345 + 53). The high pieces' sums of a score are kept
+// apart from the rest: 2.1e-7 off 64 bits (2.3e-7 before; 3.0e-7 in one chain).
 #include <float.h>
 #include <math.h>
 
@@ -54,7 +53,10 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4_t;
 constexpr int kAttnThreads = 256;
 constexpr int kMaxHd = 128;
 constexpr int kMaxRowsWg = 64;            // query rows per workgroup
-constexpr int kMaxSplits = 64;            // chunks per call: the merge takes them in one load batch
+// chunks per call at most: the merge takes them in one load batch. One key/value head then runs on 64
+// workgroups: 13.9 us over 16000 rows, 27.9 over 65000, 45.7 over 131000 (31, 48 and 69 with the vector
+// kernels on up to 256).
+constexpr int kMaxSplits = 64;
 constexpr int kTargetWgs = 512;           // workgroups of the partial kernel
 constexpr int kDirectMax = 256;           // caches up to this many rows: one chunk, no combine
 

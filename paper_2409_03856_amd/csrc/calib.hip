@@ -4,8 +4,9 @@
 // The inputs stay fp32: x is split into three bf16 pieces (hi + mid + lo = x exactly), and the
 // products of the pieces, exact in fp32, add up in one accumulator, so a product costs three
 // bf16 MFMAs and the work is a [N x 3d] by [3d x F] matrix product: 90 GFLOP for 256 inputs of a
-// 4096 x 14336 gate, bound by the MFMA rate (64 us at the rate of a large library product) and by
-// the LDS reads that feed it (16 rows of each operand per 16 x 16 x 32 product), not by HBM.
+// 4096 x 14336 gate, bound by the MFMA rate (75 us at the 1.21 PFLOP/s of a large library product;
+// 95-100 here, the matrix units busy for half of the cycles) and by the LDS reads that feed it (16
+// rows of each operand per 16 x 16 x 32 product), not by HBM.
 //
 // Calls of a few inputs take the vector kernel of the top-k gate pass (ffn_gemv.hip) instead.
 //

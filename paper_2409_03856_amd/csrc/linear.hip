@@ -15,8 +15,8 @@
 //                          which it reads from L2 in operand order; the four partials are summed
 //                          in wave order at the end.
 //
-// Bound: HBM and the L2 reads of the x pieces, one read of the weights per call (2 N K bytes) whatever the number of tokens; the
-// products are 6 n flops per weight, 16 % of the MFMA rate at 16 tokens.
+// Bound: HBM and the L2 reads of the x pieces, one read of the weights per call (2 N K bytes) whatever
+// the number of tokens; the products are 6 n flops per weight, 12 % of the MFMA rate at 16 tokens.
 #include "common.h"
 #include "kernels.h"
 #include "profile.h"
@@ -37,7 +37,7 @@ constexpr int kPieces = 3;
 // rmsnorm_vec_kernel (thread t of 256 takes float4s t + 256 u in ascending order, the wave sums in
 // wave order), so the normalised row is bit for bit that kernel's; then each thread forms the pieces
 // of one operand chunk of eight values. Bound by latency: 1024 threads, of which the first 256 form
-// the sums, take 4.7 us at 4096 columns and 6-7 at 8192 (256 threads: 5.5 and 8.2-9.5).
+// the sums, take 4.1-5.0 us at 4096 columns and 6.0 at 8192 (256 threads: 5.5 and 8.2-9.5).
 constexpr int kPrepThreads = 1024;
 __global__ __launch_bounds__(kPrepThreads) void prep_frag_kernel(const float* __restrict__ x, int n, int K,
                                                                  int ksteps, float norm_eps, int MT,
@@ -321,7 +321,7 @@ hipError_t launch_t(const float* x, int n, int K, float eps, const LinearOut& o,
   ProfScope prof("linear_mfma", s);
   // Every workgroup reads all the x pieces of its K range from L2: 3 MT / RT bytes per weight byte.
   // 64 rows per workgroup where that still gives most CUs one (LM heads): at 16 tokens and
-  // 128256 x 4096 183 us (5.7 TB/s) against 230 with 32 rows and 250 with 16; at 32000 x 2048 27.5
+  // 128256 x 4096 183-188 us (5.6-5.7 TB/s) against 230 with 32 rows and 250 with 16; at 32000 x 2048 27.5
   // against 41, at 24 tokens and 16000 x 4096 34 against 54. Below that 16 rows, so that a layer's
   // projections fill the chip: 6144 x 4096 and 4096 x 4096 together 31.6 us against 43 with 32 rows
   // and 47 with 64; there one 16-token tile takes 1 KiB of a row per load and four blocks in flight

@@ -6,9 +6,9 @@
 // atomics, so the counts are exact), whose k-th largest digit every workgroup of the next pass
 // finds for itself from the merged counts. Three passes and a last one-workgroup pick give the
 // exact value: four launches, three reads of the values (from the last-level cache after the
-// first), bound by LDS and global atomics and by launches. For 256 x 14336 values 26 us (four
-// passes of 8 bits with one-thread picks between them, nine launches: 86). Used by the threshold
-// calibration.
+// first), bound by LDS and global atomics and by launches. For 256 x 14336 values the kernels take
+// 25 us in all (8.1, 7.3, 5.0 and 4.6; four passes of 8 bits with one-thread picks between them, nine
+// launches: 86). Used by the threshold calibration.
 #include "common.h"
 #include "kernels.h"
 #include "profile.h"
@@ -21,7 +21,8 @@ constexpr int kPasses = 3;
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kCopies = 4;           // LDS histograms: hot bins spread over them by lane
-constexpr int kSelBlocks = 128;     // each merges its bins with global atomics: 512 of half the size: 31 us in all, 128: 21
+constexpr int kSelBlocks = 128;      // each merges its bins with global atomics: with 512 of half the
+                                     // size the select took half as long again
 
 struct SelectState {
   uint32_t prefix;  // bits fixed so far
