@@ -110,22 +110,27 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-_raw_stream = None
+_raw_stream = _capturing = None  # torch's current stream's handle; whether it is being captured
+
+
+def _bind_torch():
+    """Both are read through torch's own accessors where this torch has them: building a Stream object
+    for its handle costs 3 us of the 9 us that a small call spends in this binding."""
+    global _raw_stream, _capturing
+    torch = _torch()
+    get, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    torch.cuda.current_stream()  # initialises torch's GPU state
+    _capturing = getattr(torch._C, "_cuda_isCurrentStreamCapturing", torch.cuda.is_current_stream_capturing)
+    if get is not None and dev is not None:
+        _raw_stream = lambda: get(dev())  # noqa: E731
+    else:
+        _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
 
 
 def _handle() -> int:
-    """The handle of torch's current stream on the current device, read through torch's own accessor
-    of raw handles where this torch has it: building a Stream object for it costs 3 us of the 9 us that
-    a small call spends in this binding."""
-    global _raw_stream
+    """The handle of torch's current stream on the current device."""
     if _raw_stream is None:
-        torch = _torch()
-        get, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
-        torch.cuda.current_stream()  # initialises torch's GPU state
-        if get is not None and dev is not None:
-            _raw_stream = lambda: get(dev())  # noqa: E731
-        else:
-            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+        _bind_torch()
     return _raw_stream()
 
 
@@ -170,7 +175,6 @@ def workspace(op: int, a: int, b: int, c: int, d: int = 0, e: int = 0, device=No
     the operation there and grown as needed; the `_WS_MOST` latest are kept. A replaced one goes back to
     torch's allocator in the order of its stream. Under graph capture it is allocated in the graph's own
     pool and not kept."""
-    torch = _torch()
     n = _size_cache.get((op, a, b, c, d, e))
     if n is None:
         n = int(lib().sirius_workspace_size(op, a, b, c, d, e))
@@ -179,19 +183,23 @@ def workspace(op: int, a: int, b: int, c: int, d: int = 0, e: int = 0, device=No
         if len(_size_cache) >= 4096:
             _size_cache.clear()
         _size_cache[(op, a, b, c, d, e)] = n
-    dev = device
-    if not isinstance(dev, torch.device):
-        dev = torch.device("cuda", torch.cuda.current_device()) if dev is None else torch.device(dev)
-    if torch._C._cuda_isCurrentStreamCapturing():
-        return torch.empty(n, dtype=torch.uint8, device=dev)
+    index = getattr(device, "index", None)
+    if type(index) is not int:  # no torch.device with an index
+        torch = _torch()
+        device = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
+        index = device.index
+    key = (index, _handle(), op)
     bufs = _workspaces.bufs
-    key = (dev.index, _handle(), op)
     buf = bufs.get(key)
-    if buf is None or buf.numel() < n:
-        bufs.pop(key, None)
-        if len(bufs) >= _WS_MOST:
-            bufs.pop(next(iter(bufs)))
-        buf = bufs[key] = torch.empty(n, dtype=torch.uint8, device=dev)
+    capturing = _capturing()
+    if buf is None or buf.numel() < n or capturing:
+        torch = _torch()
+        buf = torch.empty(n, dtype=torch.uint8, device=device)
+        if not capturing:
+            bufs.pop(key, None)
+            if len(bufs) >= _WS_MOST:
+                bufs.pop(next(iter(bufs)))
+            bufs[key] = buf
     return buf
 
 
