@@ -43,7 +43,7 @@ __device__ __forceinline__ int swz(int r, int c) { return c ^ (r & 7); }
 
 // The product of an input with a weight row, from the input's pieces (`step` apart) put together
 // again; every lane of the wave returns it.
-__device__ float whole_dot(const uint16_t* __restrict__ xp, size_t step, const uint16_t* __restrict__ w, int d) {
+__device__ __noinline__ float whole_dot(const uint16_t* __restrict__ xp, size_t step, const uint16_t* __restrict__ w, int d) {
   const int lane = threadIdx.x & (kWave - 1);
   float acc = 0.f;
   for (int c = 8 * lane; c < d; c += 8 * kWave) {
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kThreads, 2) void calib_gate_kernel(
     }
   // an infinite weight times a zero piece, or times pieces of both signs, is NaN where the product is
   // an infinity: the wave forms such values again from whole inputs
-  if (__ballot(nan) == 0) return;
+  if (__builtin_expect(__ballot(nan) == 0, 1)) return;
   for (int i = 0; i < 32; ++i) {
     const int at = m0 + 32 * th + 16 * (i >> 4) + (i & 3), n = n0 + 64 * nh + 16 * ((i >> 2) & 3);
     const bool live = at + 4 * grp < nb && n + fr < F;
